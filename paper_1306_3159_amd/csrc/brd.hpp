@@ -68,13 +68,17 @@ struct GmresScalars {
 constexpr int kFgMaxRestart = 1024;
 
 // Levels handled by the single-work-group coarse tail (index 0 = first tail
-// level, last = coarsest). LDS byte offsets of u, f, r per level.
+// level, last = coarsest). LDS byte offsets: each level's work arrays, its result in
+// natural order (levels 1 ..), the coarsest solve's two FP64 vectors and its spectral
+// tables (nspec doubles).
 struct TailDesc {
     int nlev;
-    int m;
+    int nspec;
     int nx[kMaxLevels], ny[kMaxLevels], nz[kMaxLevels];
-    double s[kMaxLevels], diag[kMaxLevels], inv_diag[kMaxLevels];
-    unsigned off_u[kMaxLevels], off_f[kMaxLevels], off_r[kMaxLevels];
+    double s[kMaxLevels], diag[kMaxLevels];
+    double inv_diag[kMaxLevels][4];  // box: by the faces a cell touches, rounded as 1 / (diag + f s) in T
+    unsigned off_u[kMaxLevels], off_nat[kMaxLevels];
+    unsigned off_ab, off_spec;
     unsigned lds_bytes;
 };
 
@@ -174,7 +178,7 @@ struct InstDev {
     const int* tptr;
     const int* tblob;
     const double* tw;
-    const double* cinv;                   // coarsest (pseudo-)inverse for alpha
+    const double* spec;                   // coarsest solve's spectral tables for alpha
     TailDesc tail;
 };
 
@@ -186,6 +190,23 @@ struct LevelDims {
 
 // ---- helpers -------------------------------------------------------------
 __device__ __forceinline__ int wrapi(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
+
+// u plus the trilinear correction of one fine cell from its four coarse rows (J0, K0),
+// (J1, K0), (J0, K1), (J1, K1): m is a row's value at the cell's own coarse x, n the one at
+// the neighbour on the cell's side. Evaluated as written, with no contraction beyond the
+// explicit FMAs, so that every form of the correction (per level, blocked, LDS tail) rounds
+// alike.
+template <typename T>
+__device__ __forceinline__ T tri_add(T u, T m00, T n00, T m10, T n10, T m01, T n01, T m11, T n11) {
+#pragma clang fp contract(off)
+    const T a00 = fma((T)0.75, m00, (T)0.25 * n00);
+    const T a10 = fma((T)0.75, m10, (T)0.25 * n10);
+    const T a01 = fma((T)0.75, m01, (T)0.25 * n01);
+    const T a11 = fma((T)0.75, m11, (T)0.25 * n11);
+    const T b0 = fma((T)0.75, a00, (T)0.25 * a10);
+    const T b1 = fma((T)0.75, a01, (T)0.25 * a11);
+    return u + fma((T)0.75, b0, (T)0.25 * b1);
+}
 
 // number of box faces cell (x, y, z) touches (at most one per axis for edges >= 2)
 __device__ __forceinline__ int box_faces(int x, int y, int z, int nx, int ny, int nz) {

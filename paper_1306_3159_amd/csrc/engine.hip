@@ -93,7 +93,7 @@ struct Plan {
     BlobGeom geom{};
     size_t off_grid[9]{};
     size_t off_lvl[kMaxLevels][5]{};
-    size_t off_cinv[4]{};
+    size_t off_spec[4]{};
     size_t off_part = 0, part_cap = 0;
     size_t off_sc = 0, off_gs = 0, off_dsc = 0;
     size_t off_q = 0, off_kappa = 0, off_base = 0, off_wts = 0, off_tile = 0, off_counts = 0, off_offsets = 0,
@@ -119,6 +119,7 @@ size_t fg_bytes(const Plan& P, int restart) {
 
 size_t net_bytes();
 size_t learned_bytes(int N, long long nnz);
+size_t spec_doubles(const LevelDims& C);
 
 int make_plan(const blob_rd_params* p, Plan* P, std::string* why) {
     if (!p) {
@@ -203,7 +204,7 @@ int make_plan(const blob_rd_params* p, Plan* P, std::string* why) {
     }
     P->off_lvl[P->nlev - 1][0] = take((size_t)P->m * P->esz);  // coarsest u (natural)
     P->off_lvl[P->nlev - 1][2] = take((size_t)P->m * P->esz);  // coarsest f (natural)
-    for (int k = 0; k < 4; ++k) P->off_cinv[k] = take((size_t)P->m * P->m * 8);
+    for (int k = 0; k < 4; ++k) P->off_spec[k] = take(spec_doubles(P->lev[P->nlev - 1]) * 8);
     P->part_cap = nblocks(ncell) + 64;
     P->off_part = take(P->part_cap * 3 * 8);
     P->off_sc = take(sizeof(Scalars));
@@ -251,70 +252,51 @@ int make_plan(const blob_rd_params* p, Plan* P, std::string* why) {
     return 0;
 }
 
-// Dense (pseudo-)inverse of the coarsest operator alpha I - D L_H (row-major m x m).
-// Periodic with alpha = 0 it returns (A + e e^T/m)^{-1} - e e^T/m, the pseudo-inverse
-// on mean-zero vectors. In a box with fixed faces (box) a neighbour beyond a face is
-// the ghost -u, which adds s to the diagonal; the operator is then invertible for
-// every alpha >= 0. LU with partial pivoting, then column-wise solves.
-std::vector<double> coarse_inverse(const LevelDims& C, double D, double alpha, bool box) {
-    const int nx = C.nx, ny = C.ny, nz = C.nz, m = nx * ny * nz;
-    const double s = D / (C.h * C.h);
-    std::vector<double> A((size_t)m * m, 0.0);
-    auto id = [&](int x, int y, int z) {
-        if (box && (x < 0 || x >= nx || y < 0 || y >= ny || z < 0 || z >= nz)) return -1;
-        x = (x + nx) % nx;
-        y = (y + ny) % ny;
-        z = (z + nz) % nz;
-        return (z * ny + y) * nx + x;
-    };
-    for (int z = 0; z < nz; ++z)
-        for (int y = 0; y < ny; ++y)
-            for (int x = 0; x < nx; ++x) {
-                const int r = id(x, y, z);
-                A[(size_t)r * m + r] += alpha + 6.0 * s;
-                const int nb[6] = {id(x - 1, y, z), id(x + 1, y, z), id(x, y - 1, z),
-                                   id(x, y + 1, z), id(x, y, z - 1), id(x, y, z + 1)};
-                for (int k = 0; k < 6; ++k) {
-                    if (nb[k] < 0) A[(size_t)r * m + r] += s;  // ghost -u beyond a face
-                    else A[(size_t)r * m + nb[k]] -= s;
-                }
+// Orthonormal eigenvectors (row = mode) and eigenvalues of one axis of -h^2 L on n cells: the
+// real Fourier basis of a periodic axis, and sines about the cell centres in a box whose ghost
+// beyond a face is -u (the diagonal of an end cell is then 3).
+void axis_modes(int n, bool box, double* v, double* lam) {
+    const double pi = 3.14159265358979323846;
+    for (int k = 0; k < n; ++k) {
+        if (box) {
+            lam[k] = 4.0 * std::pow(std::sin(0.5 * pi * (k + 1) / n), 2);
+            const double c = std::sqrt((k == n - 1 ? 1.0 : 2.0) / n);
+            for (int x = 0; x < n; ++x) v[k * n + x] = c * std::sin(pi * (((long long)(k + 1) * (2 * x + 1)) % (4 * n)) / (2.0 * n));
+        } else {
+            // modes 0, (cos 1, sin 1), (cos 2, sin 2), ...; the last one alternates for even n
+            const int w = (k + 1) / 2;
+            lam[k] = 4.0 * std::pow(std::sin(pi * w / n), 2);
+            const double c = std::sqrt((k == 0 || 2 * w == n ? 1.0 : 2.0) / n);
+            for (int x = 0; x < n; ++x) {
+                const double t = 2.0 * pi * ((w * x) % n) / n;
+                v[k * n + x] = c * ((k & 1) || k == 0 ? std::cos(t) : std::sin(t));
             }
-    const bool sing = alpha == 0.0 && !box;
-    const double e = 1.0 / m;
-    if (sing)
-        for (auto& v : A) v += e;
-    std::vector<int> piv(m);
-    for (int k = 0; k < m; ++k) {
-        int pr = k;
-        for (int i = k + 1; i < m; ++i)
-            if (std::fabs(A[(size_t)i * m + k]) > std::fabs(A[(size_t)pr * m + k])) pr = i;
-        piv[k] = pr;
-        if (pr != k)
-            for (int j = 0; j < m; ++j) std::swap(A[(size_t)k * m + j], A[(size_t)pr * m + j]);
-        const double d = A[(size_t)k * m + k];
-        if (d == 0.0) throw Err(BLOB_RD_ESINGULAR, "singular coarsest operator");
-        for (int i = k + 1; i < m; ++i) {
-            const double l = A[(size_t)i * m + k] / d;
-            A[(size_t)i * m + k] = l;
-            for (int j = k + 1; j < m; ++j) A[(size_t)i * m + j] -= l * A[(size_t)k * m + j];
         }
     }
-    std::vector<double> inv((size_t)m * m);
-    std::vector<double> col(m);
-    for (int c = 0; c < m; ++c) {
-        std::fill(col.begin(), col.end(), 0.0);
-        col[c] = 1.0;
-        for (int k = 0; k < m; ++k)
-            if (piv[k] != k) std::swap(col[k], col[piv[k]]);
-        for (int i = 0; i < m; ++i)
-            for (int j = 0; j < i; ++j) col[i] -= A[(size_t)i * m + j] * col[j];
-        for (int i = m - 1; i >= 0; --i) {
-            for (int j = i + 1; j < m; ++j) col[i] -= A[(size_t)i * m + j] * col[j];
-            col[i] /= A[(size_t)i * m + i];
-        }
-        for (int r = 0; r < m; ++r) inv[(size_t)r * m + c] = col[r] - (sing ? e : 0.0);
-    }
-    return inv;
+}
+
+// Spectral tables of the coarsest operator alpha I - D L_H, a sum of one operator per axis:
+// the axes' eigenvectors (x, y, z) and the inverse eigenvalue of every mode in natural order.
+// Periodic with alpha = 0 the constant mode's is zero: the pseudo-inverse on mean-zero vectors.
+size_t spec_doubles(const LevelDims& C) {
+    return (size_t)C.nx * C.nx + (size_t)C.ny * C.ny + (size_t)C.nz * C.nz + (size_t)C.nx * C.ny * C.nz;
+}
+std::vector<double> coarse_spectrum(const LevelDims& C, double D, double alpha, bool box) {
+    const double s = D / (C.h * C.h);
+    std::vector<double> out(spec_doubles(C)), lx(C.nx), ly(C.ny), lz(C.nz);
+    double* v = out.data();
+    axis_modes(C.nx, box, v, lx.data());
+    axis_modes(C.ny, box, v + (size_t)C.nx * C.nx, ly.data());
+    axis_modes(C.nz, box, v + (size_t)C.nx * C.nx + (size_t)C.ny * C.ny, lz.data());
+    double* w = v + (size_t)C.nx * C.nx + (size_t)C.ny * C.ny + (size_t)C.nz * C.nz;
+    for (int z = 0; z < C.nz; ++z)
+        for (int y = 0; y < C.ny; ++y)
+            for (int x = 0; x < C.nx; ++x) {
+                const bool null_mode = !box && alpha == 0.0 && x == 0 && y == 0 && z == 0;
+                w[((size_t)z * C.ny + y) * C.nx + x] =
+                    null_mode ? 0.0 : 1.0 / (alpha + s * (lx[x] + ly[y] + lz[z]));
+            }
+    return out;
 }
 
 }  // namespace
@@ -361,9 +343,9 @@ struct blob_rd {
     char* ws = nullptr;
     double sum_kappa = 0.0;
     bool has_kappa = false;
-    double cinv_alpha[4];
-    int cinv_used = 0;
-    int cinv_next = 0;
+    double spec_alpha[4];
+    int spec_used = 0;
+    int spec_next = 0;
     // host mirrors (pinned)
     Scalars* hsc = nullptr;
     GmresScalars* hgs = nullptr;
@@ -510,17 +492,17 @@ void sync_read(blob_rd* H, void* host, const void* dev, size_t bytes) {
     HIPCHK(hipStreamSynchronize(H->st));
 }
 
-const double* select_cinv(blob_rd* H, double alpha) {
-    for (int k = 0; k < H->cinv_used; ++k)
-        if (H->cinv_alpha[k] == alpha) return H->at<double>(H->P.off_cinv[k]);
-    const int slot = H->cinv_next;
-    H->cinv_next = (H->cinv_next + 1) % 4;
-    if (H->cinv_used < 4) {
-        ++H->cinv_used;
+const double* select_spec(blob_rd* H, double alpha) {
+    for (int k = 0; k < H->spec_used; ++k)
+        if (H->spec_alpha[k] == alpha) return H->at<double>(H->P.off_spec[k]);
+    const int slot = H->spec_next;
+    H->spec_next = (H->spec_next + 1) % 4;
+    if (H->spec_used < 4) {
+        ++H->spec_used;
     } else {
         // graphs captured for the evicted alpha point at this slot: drop them
         HIPCHK(hipStreamSynchronize(H->st));
-        const double old = H->cinv_alpha[slot];
+        const double old = H->spec_alpha[slot];
         for (size_t i = 0; i < H->graphs.size();) {
             if (H->graphs[i].alpha == old) {
                 (void)hipGraphExecDestroy(H->graphs[i].exec);
@@ -538,9 +520,9 @@ const double* select_cinv(blob_rd* H, double alpha) {
             }
         }
     }
-    H->cinv_alpha[slot] = alpha;
-    std::vector<double> inv = coarse_inverse(H->P.lev[H->P.nlev - 1], H->prm.D, alpha, H->box);
-    double* dst = H->at<double>(H->P.off_cinv[slot]);
+    H->spec_alpha[slot] = alpha;
+    std::vector<double> inv = coarse_spectrum(H->P.lev[H->P.nlev - 1], H->prm.D, alpha, H->box);
+    double* dst = H->at<double>(H->P.off_spec[slot]);
     HIPCHK(hipMemcpyAsync(dst, inv.data(), inv.size() * 8, hipMemcpyHostToDevice, H->st));
     HIPCHK(hipStreamSynchronize(H->st));
     return dst;
@@ -571,13 +553,15 @@ TailDesc make_tail(const blob_rd* H, int t, double alpha) {
     TailDesc d{};
     const int L = P.nlev - 1;
     d.nlev = L - t + 1;
-    d.m = P.m;
+    d.nspec = (int)spec_doubles(P.lev[L]);
     unsigned o = 0;
-    auto take = [&](size_t n) {
+    auto take = [&](size_t bytes) {
         unsigned r = o;
-        o += (unsigned)((n * sizeof(T) + 15) & ~(size_t)15);
+        o += (unsigned)((bytes + 15) & ~(size_t)15);
         return r;
     };
+    d.off_ab = take(2 * (size_t)P.m * 8);
+    d.off_spec = take((size_t)d.nspec * 8);
     for (int k = 0; k < d.nlev; ++k) {
         const LevelDims& ld = P.lev[t + k];
         d.nx[k] = ld.nx;
@@ -586,11 +570,14 @@ TailDesc make_tail(const blob_rd* H, int t, double alpha) {
         const double s = H->prm.D / (ld.h * ld.h);
         d.s[k] = s;
         d.diag[k] = alpha + 6.0 * s;
-        d.inv_diag[k] = 1.0 / (alpha + 6.0 * s);
+        d.inv_diag[k][0] = 1.0 / (alpha + 6.0 * s);
+        if (H->box)
+            for (int f = 0; f < 4; ++f) d.inv_diag[k][f] = (T)1 / ((T)d.diag[k] + (T)f * (T)s);
         const size_t n = (size_t)ld.nx * ld.ny * ld.nz;
-        d.off_u[k] = take(n);
-        d.off_f[k] = take(n);
-        d.off_r[k] = (k + 1 < d.nlev) ? take(n) : 0;
+        // red and black values, each with a stored zero; below the first level also both
+        // right-hand sides and the red residual
+        if (k + 1 < d.nlev) d.off_u[k] = take((n + 2 + (k > 0 ? n + n / 2 : 0)) * sizeof(T));
+        if (k > 0) d.off_nat[k] = take(n * sizeof(T));
     }
     d.lds_bytes = o;
     return d;
@@ -628,7 +615,7 @@ void box_coefs(const blob_rd* H, int l, double alpha, BoxCoef* diag, BoxCoef* in
 // level of the LDS tail (then the box tail kernel) or to the coarsest level (the
 // dense box inverse); no temporally blocked levels.
 template <typename T>
-void vcycle_box(blob_rd* H, double alpha, const double* r, const Scalars* sc, const double* cinv, bool entered) {
+void vcycle_box(blob_rd* H, double alpha, const double* r, const Scalars* sc, const double* spec, bool entered) {
     const Plan& P = H->P;
     const int L = P.nlev - 1;
     const int t = std::min(H->tail_level[sizeof(T) == 4 ? 0 : 1], L);
@@ -655,8 +642,8 @@ void vcycle_box(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
                                    inv[l + 1], sc);
         H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kPreRestrictBytes;
     }
-    if (t < L) launch_tail_box<T>(st, lv(t, 2), lv(t, 3), lv(t, 0), lv(t, 1), make_tail<T>(H, t, alpha), cinv, sc);
-    else launch_coarse<T>(st, lv(L, 2), lv(L, 0), cinv, P.m, sc);
+    if (t < L) launch_tail<T>(st, lv(t, 2), lv(t, 3), lv(t, 0), lv(t, 1), make_tail<T>(H, t, alpha), spec, true, sc);
+    else launch_coarse<T>(st, lv(L, 2), lv(L, 0), spec, P.lev[L].nx, P.lev[L].ny, P.lev[L].nz, sc);
     for (int l = t - 1; l >= 0; --l) {
         const LevelDims& d = P.lev[l];
         const double s = H->prm.D / (d.h * d.h);
@@ -677,10 +664,10 @@ void vcycle_box(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
 // the closing red half-sweep of level 0 when that level has its own launches;
 // returns the number of partials written to H->part(), 0 when not fused.
 template <typename T>
-unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, const double* cinv,
+unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, const double* spec,
                 bool entered = false, const double* dot_q = nullptr, bool from_f = false) {
     if (H->box) {
-        vcycle_box<T>(H, alpha, r, sc, cinv, entered);
+        vcycle_box<T>(H, alpha, r, sc, spec, entered);
         return 0;
     }
     const Plan& P = H->P;
@@ -750,7 +737,7 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
             H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kPreRestrictBytes;
         }
         const TailDesc td = make_tail<T>(H, t, alpha);
-        launch_tail<T>(st, lv(t, 2), lv(t, 3), lv(t, 0), lv(t, 1), td, cinv, sc);
+        launch_tail<T>(st, lv(t, 2), lv(t, 3), lv(t, 0), lv(t, 1), td, spec, false, sc);
         for (int l = t - 1; l >= 0; --l) {
             const LevelDims& d = P.lev[l];
             const double s = D / (d.h * d.h), diag = alpha + 6.0 * s;
@@ -789,7 +776,7 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
                                1.0 / (alpha + 6.0 * sc_), sc, b[2]);
         H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kPreRestrictBytes;
     }
-    launch_coarse<T>(st, lv(L, 2), lv(L, 0), cinv, P.m, sc);
+    launch_coarse<T>(st, lv(L, 2), lv(L, 0), spec, P.lev[L].nx, P.lev[L].ny, P.lev[L].nz, sc);
     for (int l = L - 1; l >= 0; --l) {
         const LevelDims& d = P.lev[l];
         const double s = D / (d.h * d.h), diag = alpha + 6.0 * s;
@@ -808,9 +795,9 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
 }
 
 template <typename T>
-void precond_zdots(blob_rd* H, double alpha, const double* r, const double* q, const double* cinv,
+void precond_zdots(blob_rd* H, double alpha, const double* r, const double* q, const double* spec,
                    bool entered = false) {
-    unsigned np = vcycle<T>(H, alpha, r, H->sc(), cinv, entered, q);
+    unsigned np = vcycle<T>(H, alpha, r, H->sc(), spec, entered, q);
     if (np) {
         H->alg_bytes += (double)H->P.ncell * 16;  // r, q read by the fused sweep
     } else {
@@ -886,7 +873,7 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
     box_coefs(H, 0, alpha, nullptr, &binv);
     const double eBe = alpha * (double)P.ncell + H->sum_kappa * H->inv_h3();
     const double eBe_inv = (with_blobs && project && eBe > 0.0) ? 1.0 / eBe : 0.0;
-    const double* cinv = select_cinv(H, alpha);
+    const double* spec = select_spec(H, alpha);
     hipLaunchKernelGGL(k_sc_init, dim3(1), dim3(1), 0, st, H->sc(), project, 1.0 / (double)P.ncell, eBe_inv,
                        rtol * rtol, abs_tol * abs_tol, x_zero ? 1 : 0);
     unsigned np = 0;
@@ -906,7 +893,7 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
         H->alg_bytes += (double)P.ncell * 40;
     }
     launch_fin(st, FIN_INIT, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
-    precond_zdots<T>(H, alpha, r, q, cinv);
+    precond_zdots<T>(H, alpha, r, q, spec);
     int& hist = H->last_iters[(with_blobs ? 2 : 0) + project];
     int chunk = hist > 0 ? std::min(hist, maxit) : std::min(4, maxit);
     int done_iters = 0;
@@ -930,7 +917,7 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
                                 H->at<T>(P.off_lvl[0][0]), d.nx, d.ny, d.nz, 1.0 / (alpha + 6.0 * s), H->part(),
                                 H->sc(), &np, H->box ? &binv : nullptr);
         launch_fin(s_, FIN_UPDATE, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
-        precond_zdots<T>(H, alpha, r, q, cinv, true);
+        precond_zdots<T>(H, alpha, r, q, spec, true);
         // direction (z, p r/w), stencil (p, q), update (x, r r/w, p, q) with the V-cycle entry (f, red u)
         H->alg_bytes += (double)P.ncell * (P.esz + 16 + 16 + 48 + 1.5 * P.esz);
         H->st = keep;
@@ -1598,10 +1585,10 @@ void batch_run_vcycle(blob_rd* H);
 // V-cycle rounds take this handle, the executor runs the levels with the other
 // members' cycles (the same kernel bodies and order, so the same results).
 template <typename T>
-void fg_vcycle(blob_rd* H, double alpha, const double* r, const double* cinv, bool from_f) {
+void fg_vcycle(blob_rd* H, double alpha, const double* r, const double* spec, bool from_f) {
     if (!(H->batch && H->batch_v)) {
         // from a right side r the entry need not store the first red sweep either
-        vcycle<T>(H, alpha, r, nullptr, cinv, r == nullptr, nullptr, r ? cycle_opens_from_f<T>(H) : from_f);
+        vcycle<T>(H, alpha, r, nullptr, spec, r == nullptr, nullptr, r ? cycle_opens_from_f<T>(H) : from_f);
         return;
     }
     const Plan& P = H->P;
@@ -1625,7 +1612,7 @@ void fg_vcycle(blob_rd* H, double alpha, const double* r, const double* cinv, bo
 // V (r - A x).
 template <typename T>
 void fg_cycles(blob_rd* H, double alpha, const double* base, const SpreadMult* M, double scale, double* x,
-               bool from_zero, int n, const double* cinv) {
+               bool from_zero, int n, const double* spec) {
     const Plan& P = H->P;
     const LevelDims& d = P.lev[0];
     const double inv_diag = 1.0 / (alpha + 6.0 * H->prm.D / (d.h * d.h));
@@ -1648,12 +1635,12 @@ void fg_cycles(blob_rd* H, double alpha, const double* base, const SpreadMult* M
                 launch_spread_enter<T>(H->st, spread_lists(H), *M, base, scale, f0, f1, from_f ? nullptr : z0, d.nx,
                                        d.ny, inv_diag);
             H->alg_bytes += (double)P.ncell * (8 + (from_f ? 1.0 : 1.5) * P.esz);
-            fg_vcycle<T>(H, alpha, nullptr, cinv, from_f);
+            fg_vcycle<T>(H, alpha, nullptr, spec, from_f);
             launch_split_to_nat<T>(H->st, z0, z1, x, d.nx, d.ny, d.nz, 0.0);
             H->alg_bytes += (double)P.ncell * (P.esz + 8);
         } else {
             fg_resid(H, alpha, base, M, scale, x, q);
-            fg_vcycle<T>(H, alpha, q, cinv, false);
+            fg_vcycle<T>(H, alpha, q, spec, false);
             launch_split_to_nat<T>(H->st, z0, z1, x, d.nx, d.ny, d.nz, 1.0);
             H->alg_bytes += (double)P.ncell * (P.esz + 16);
         }
@@ -1697,7 +1684,7 @@ void fg_precond(blob_rd* H, double alpha, const FgOpts& o, const double* vg, con
     hipStream_t st = H->st;
     const int N = P.N;
     const double h3 = H->prm.h * H->prm.h * H->prm.h;
-    const double* cinv = select_cinv(H, alpha);
+    const double* spec = select_spec(H, alpha);
     const bool sing = singular(H, alpha);
     const LevelDims& d = P.lev[0];
     const SpreadLists L = spread_lists(H);
@@ -1733,11 +1720,11 @@ void fg_precond(blob_rd* H, double alpha, const FgOpts& o, const double* vg, con
             launch_spread_enter<T>(st, L, m1, vg, H->inv_h3(), f0, f1, from_f ? nullptr : z0, d.nx, d.ny,
                                    inv_diag0);
         H->alg_bytes += (double)P.ncell * (8 + (from_f ? 1.0 : 1.5) * P.esz);
-        fg_vcycle<T>(H, alpha, nullptr, cinv, from_f);
+        fg_vcycle<T>(H, alpha, nullptr, spec, from_f);
         launch_copy2<T>(st, z0, z1, cs0, cs1, P.ncell / 2);
         H->alg_bytes += (double)P.ncell * 2 * P.esz;
     } else {
-        fg_cycles<T>(H, alpha, vg, sing ? &m1 : nullptr, H->inv_h3(), zg, true, o.n, cinv);
+        fg_cycles<T>(H, alpha, vg, sing ? &m1 : nullptr, H->inv_h3(), zg, true, o.n, spec);
     }
     // 2. Schur-complement system for the (fluctuating) multipliers, right side J c* - vf
     double* jv = H->nv(6);
@@ -1801,7 +1788,7 @@ void fg_precond(blob_rd* H, double alpha, const FgOpts& o, const double* vg, con
             launch_spread_enter<T>(st, L, SpreadMult{vk, nullptr, 0.0, 0.0}, nullptr, H->inv_h3(), f0, f1,
                                    from_f ? nullptr : z0, d.nx, d.ny, inv_diag);
             H->alg_bytes += (double)nh * P.esz * ((k == 0 ? 2 : 0) + (from_f ? 0 : 1));
-            fg_vcycle<T>(H, alpha, nullptr, cinv, from_f);
+            fg_vcycle<T>(H, alpha, nullptr, spec, from_f);
             launch_interp_split<T>(st, z0, z1, N, P.geom, H->at<int>(P.off_base), H->at<double>(P.off_wts),
                                    H->at<int>(P.off_perm), V + (size_t)(k + 1) * N);
             launch_gmres_arnoldi(st, V, Hm, H->at<double>(P.off_cs), H->at<double>(P.off_sn), gv, N, k, o.m,
@@ -1831,11 +1818,11 @@ void fg_precond(blob_rd* H, double alpha, const FgOpts& o, const double* vg, con
             launch_resid_spread_enter<T>(st, L, m2, vg, cs0, cs1, -H->inv_h3(), f0, f1, from_f ? nullptr : z0, d.nx,
                                          d.ny, d.nz, alpha, s0, inv_diag0);
             H->alg_bytes += (double)P.ncell * (8 + P.esz * (from_f ? 2.0 : 2.5));
-            fg_vcycle<T>(H, alpha, nullptr, cinv, from_f);
+            fg_vcycle<T>(H, alpha, nullptr, spec, from_f);
         } else {
             double* q = H->grid(G_Q);
             fg_resid(H, alpha, vg, &m2, -H->inv_h3(), zg, q);
-            fg_vcycle<T>(H, alpha, q, cinv, false);
+            fg_vcycle<T>(H, alpha, q, spec, false);
         }
         double* jz = H->nv(5);
         launch_interp_split<T>(st, z0, z1, N, P.geom, H->at<int>(P.off_base), H->at<double>(P.off_wts),
@@ -1859,11 +1846,11 @@ void fg_precond(blob_rd* H, double alpha, const FgOpts& o, const double* vg, con
         launch_resid_enter<T>(st, vg, cs0, cs1, f0, f1, from_f ? nullptr : z0, d.nx, d.ny, d.nz, alpha, s0, inv_diag0);
         launch_resid_spread_enter<T>(st, L, m2, vg, cs0, cs1, -H->inv_h3(), f0, f1, from_f ? nullptr : z0, d.nx, d.ny,
                                      d.nz, alpha, s0, inv_diag0);
-        fg_vcycle<T>(H, alpha, nullptr, cinv, from_f);
+        fg_vcycle<T>(H, alpha, nullptr, spec, from_f);
         launch_split_add_to_nat<T>(st, cs0, cs1, z0, z1, zg, d.nx, d.ny, d.nz, nullptr, 0.0);
         H->alg_bytes += (double)P.ncell * (16 + P.esz * (from_f ? 4.0 : 4.5));
     } else {
-        fg_cycles<T>(H, alpha, vg, &m2, -H->inv_h3(), zg, false, o.n, cinv);
+        fg_cycles<T>(H, alpha, vg, &m2, -H->inv_h3(), zg, false, o.n, spec);
         if (sing) {
             // 4. mean concentration: mean over blobs of vf - J c
             fg_interp(H, zg, jv);
@@ -1927,7 +1914,7 @@ int fg_solve(blob_rd* H, double alpha, const FgOpts& o, const double* f, double*
     if (ahead)
         for (auto& e : H->fg_ev)
             if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    (void)select_cinv(H, alpha);  // its upload, if any, happens outside any capture
+    (void)select_spec(H, alpha);  // its upload, if any, happens outside any capture
     if (warm) {
         // (c, lam) hold the initial guess; the scale of the residual is |b| = |[f; phi]|
         unsigned np = 0;
@@ -2309,7 +2296,7 @@ int blob_rd_create(const blob_rd_params* p, blob_rd_t* out) {
         }
         HIPCHK(hipGetLastError());
         HIPCHK(hipStreamSynchronize(st));
-        select_cinv(H, 0.0);
+        select_spec(H, 0.0);
         // LDS budget of the coarse tail: the device limit per block, capped at 160 KiB.
         int dev = 0, lds = 0;
         HIPCHK(hipGetDevice(&dev));
@@ -2318,14 +2305,8 @@ int blob_rd_create(const blob_rd_params* p, blob_rd_t* out) {
         H->tail_level[0] = tail_start(P, 4, budget);
         H->tail_level[1] = tail_start(P, 8, budget);
         const int Lc = P.nlev - 1;
-        if (H->tail_level[0] < Lc) {
-            const size_t need = make_tail<float>(H, H->tail_level[0], 0.0).lds_bytes;
-            if (need > 48 * 1024) HIPCHK(H->box ? tail_box_set_lds<float>(need) : tail_set_lds<float>(need));
-        }
-        if (H->tail_level[1] < Lc) {
-            const size_t need = make_tail<double>(H, H->tail_level[1], 0.0).lds_bytes;
-            if (need > 48 * 1024) HIPCHK(H->box ? tail_box_set_lds<double>(need) : tail_set_lds<double>(need));
-        }
+        if (H->tail_level[0] < Lc) HIPCHK(tail_set_lds<float>(budget));
+        if (H->tail_level[1] < Lc) HIPCHK(tail_set_lds<double>(budget));
         if (H->blocked) {
             HIPCHK(blocked_set_lds<float>());
             HIPCHK(blocked_set_lds<double>());
@@ -2495,13 +2476,13 @@ int blob_rd_vcycle(blob_rd_t H, double alpha, const double* r, double* z) {
     return guarded(H, nullptr, [&]() {
         const Plan& P = H->P;
         const LevelDims& d = P.lev[0];
-        const double* cinv = select_cinv(H, alpha);
+        const double* spec = select_spec(H, alpha);
         if (P.esz == 4) {
-            vcycle<float>(H, alpha, r, nullptr, cinv);
+            vcycle<float>(H, alpha, r, nullptr, spec);
             launch_split_to_nat<float>(H->st, H->at<float>(P.off_lvl[0][0]), H->at<float>(P.off_lvl[0][1]), z, d.nx,
                                        d.ny, d.nz, 0.0);
         } else {
-            vcycle<double>(H, alpha, r, nullptr, cinv);
+            vcycle<double>(H, alpha, r, nullptr, spec);
             launch_split_to_nat<double>(H->st, H->at<double>(P.off_lvl[0][0]), H->at<double>(P.off_lvl[0][1]), z,
                                         d.nx, d.ny, d.nz, 0.0);
         }
@@ -2972,7 +2953,7 @@ void batch_describe(BatchServer& B, int i, blob_rd* H, bool blobs) {
     D.tptr = H->at<int>(P.off_tptr);
     D.tblob = H->at<int>(P.off_tblob);
     D.tw = H->at<double>(P.off_tw);
-    D.cinv = select_cinv(H, B.alpha);
+    D.spec = select_spec(H, B.alpha);
     D.tail = P.esz == 4 ? make_tail<float>(H, t, B.alpha) : make_tail<double>(H, t, B.alpha);
 }
 
@@ -3056,8 +3037,6 @@ void batch_setup(BatchServer& B, char* ws, size_t ws_bytes, const int32_t* kind)
     HIPCHK(hipMemcpyAsync(B.d_inst, B.h_inst, (size_t)n * sizeof(InstDev), hipMemcpyHostToDevice, B.st));
     HIPCHK(hipMemcpyAsync(B.d_gate, B.h_gate, (size_t)n * sizeof(int), hipMemcpyHostToDevice, B.st));
     HIPCHK(hipStreamSynchronize(B.st));
-    if (B.esz == 4) HIPCHK(tail_set_lds_batched<float>(std::max<unsigned>(B.tail_lds, 1)));
-    else HIPCHK(tail_set_lds_batched<double>(std::max<unsigned>(B.tail_lds, 1)));
     hipStream_t cap;
     HIPCHK(hipStreamCreateWithFlags(&cap, hipStreamNonBlocking));
     HIPCHK(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
@@ -3732,7 +3711,7 @@ int blob_rd_time_kernel(blob_rd_t H, int kernel, int reps, double* avg_ms, doubl
         const Plan& P = H->P;
         const LevelDims& d = P.lev[0];
         const double alpha = 0.0, s = H->prm.D / (d.h * d.h), diag = alpha + 6.0 * s;
-        const double* cinv = select_cinv(H, alpha);
+        const double* spec = select_spec(H, alpha);
         // a box handle times its own kernels (the box forms of the same steps)
         const bool box = H->box;
         BoxCoef bdg0, binv0, binv1;
@@ -3833,8 +3812,8 @@ int blob_rd_time_kernel(blob_rd_t H, int kernel, int reps, double* avg_ms, doubl
                                                 d.ny, d.nz, nullptr);
                     break;
                 default:
-                    if (f32) vcycle<float>(H, alpha, H->grid(G_R), nullptr, cinv);
-                    else vcycle<double>(H, alpha, H->grid(G_R), nullptr, cinv);
+                    if (f32) vcycle<float>(H, alpha, H->grid(G_R), nullptr, spec);
+                    else vcycle<double>(H, alpha, H->grid(G_R), nullptr, spec);
             }
         };
         float ms = 0.f;
@@ -4273,9 +4252,9 @@ int blob_rd_solve_absorbing_fgmres_noalloc(blob_rd_t H, double alpha, const blob
     if (!H->noalloc) return g_last_error = "no scratch on this handle's device", BLOB_RD_EDEVICE;
     // a new alpha evicting a cached coarse inverse would also drop captured CG graphs
     bool cached = false;
-    for (int k = 0; k < H->cinv_used; ++k) cached = cached || H->cinv_alpha[k] == alpha;
-    if (!cached && H->cinv_used == 4) {
-        const double old = H->cinv_alpha[H->cinv_next];
+    for (int k = 0; k < H->spec_used; ++k) cached = cached || H->spec_alpha[k] == alpha;
+    if (!cached && H->spec_used == 4) {
+        const double old = H->spec_alpha[H->spec_next];
         bool captured = false;
         for (const auto& g : H->graphs) captured = captured || g.alpha == old;
         for (const auto& g : H->fg_graphs) captured = captured || g.alpha == old;
@@ -4319,9 +4298,9 @@ int blob_rd_schur_apply_cycles(blob_rd_t H, double alpha, const double* x, doubl
         launch_nvec_copy_scale(H->st, x, xt, P.N, 1.0, 0.0);
         if (singular(H, alpha)) launch_nvec_project(H->st, xt, P.N);
         spread_to(H, xt, 0.0, nullptr, H->grid(G_T2), H->inv_h3(), nullptr);
-        const double* cinv = select_cinv(H, alpha);
-        if (P.esz == 4) fg_cycles<float>(H, alpha, H->grid(G_T2), nullptr, 0.0, H->grid(G_U), true, cycles, cinv);
-        else fg_cycles<double>(H, alpha, H->grid(G_T2), nullptr, 0.0, H->grid(G_U), true, cycles, cinv);
+        const double* spec = select_spec(H, alpha);
+        if (P.esz == 4) fg_cycles<float>(H, alpha, H->grid(G_T2), nullptr, 0.0, H->grid(G_U), true, cycles, spec);
+        else fg_cycles<double>(H, alpha, H->grid(G_T2), nullptr, 0.0, H->grid(G_U), true, cycles, spec);
         fg_interp(H, H->grid(G_U), y);
         if (singular(H, alpha)) launch_nvec_project(H->st, y, P.N);
         HIPCHK(hipGetLastError());

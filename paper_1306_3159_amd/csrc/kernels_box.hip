@@ -546,220 +546,6 @@ void launch_prolong_red_box(hipStream_t st, const T* cu0, const T* cu1, int coar
                        ny, nz, sc);
 }
 
-// ---------------------------------------------------------------------------
-// Coarse tail of the box V-cycle: every level from t down in LDS of one work-group
-// (natural layout), the steps of the per-level box kernels in their order: zero
-// guess, R B R B pre-smoothing, red residual, restriction, the coarsest dense
-// solve, correction, B R B R post-smoothing. The per-cell diagonal is
-// alpha + s (6 + faces) = d.diag[l] + faces * s.
-namespace {
-
-// j -> (a, b, c) for row-major dims (na, nb, *); shifts and masks when both are powers of two
-struct TailPos {
-    int na, nb, la, lab;
-    bool p2;
-    __device__ __forceinline__ TailPos(int a, int b) : na(a), nb(b) {
-        p2 = ((a & (a - 1)) == 0) && ((b & (b - 1)) == 0);
-        la = __ffs(a) - 1;
-        lab = la + __ffs(b) - 1;
-    }
-    __device__ __forceinline__ void operator()(int j, int& a, int& b, int& c) const {
-        if (p2) {
-            a = j & (na - 1);
-            b = (j >> la) & (nb - 1);
-            c = j >> lab;
-        } else {
-            a = j % na;
-            const int t = j / na;
-            b = t % nb;
-            c = t / nb;
-        }
-    }
-};
-
-template <typename T>
-__device__ __forceinline__ T tail_nb_box(const T* u, int x, int y, int z, int nx, int ny, int nz) {
-    const int row = (z * ny + y) * nx + x;
-    const int plane = nx * ny;
-    const T xm = x > 0 ? u[row - 1] : (T)0;
-    const T xp = x + 1 < nx ? u[row + 1] : (T)0;
-    const T ym = y > 0 ? u[row - nx] : (T)0;
-    const T yp = y + 1 < ny ? u[row + nx] : (T)0;
-    const T zm = z > 0 ? u[row - plane] : (T)0;
-    const T zp = z + 1 < nz ? u[row + plane] : (T)0;
-    return ((xm + xp) + (ym + yp)) + (zm + zp);
-}
-
-// inverse diagonals of a level for 0..3 faces, selected without a runtime-indexed array
-template <typename T>
-struct TailInv {
-    T i0, i1, i2, i3;
-    __device__ __forceinline__ TailInv(T dg0, T s)
-        : i0((T)1 / dg0), i1((T)1 / (dg0 + s)), i2((T)1 / (dg0 + 2 * s)), i3((T)1 / (dg0 + 3 * s)) {}
-    __device__ __forceinline__ T operator()(int f) const { return f == 0 ? i0 : (f == 1 ? i1 : (f == 2 ? i2 : i3)); }
-};
-
-template <typename T>
-__device__ __forceinline__ void tail_gs_box(T* u, const T* f, int nx, int ny, int nz, int color, T s,
-                                            const TailInv<T>& inv) {
-    const int hx = nx >> 1, nh = hx * ny * nz;
-    const TailPos dec(hx, ny);
-    for (int j = threadIdx.x; j < nh; j += blockDim.x) {
-        int i, y, z;
-        dec(j, i, y, z);
-        const int x = 2 * i + ((y + z + color) & 1);
-        const int k = (z * ny + y) * nx + x;
-        u[k] = (f[k] + s * tail_nb_box(u, x, y, z, nx, ny, nz)) * inv(box_faces(x, y, z, nx, ny, nz));
-    }
-    __syncthreads();
-}
-
-}  // namespace
-
-template <typename T>
-__global__ void __launch_bounds__(kFinBlock) k_tail_box(const T* __restrict__ f0g, const T* __restrict__ f1g,
-                                                        T* __restrict__ u0g, T* __restrict__ u1g, TailDesc d,
-                                                        const double* __restrict__ cinv, const Scalars* sc) {
-    if (sc && sc->done) return;
-    extern __shared__ __align__(16) unsigned char smem[];
-    auto U_ = [&](int l) { return reinterpret_cast<T*>(smem + d.off_u[l]); };
-    auto F_ = [&](int l) { return reinterpret_cast<T*>(smem + d.off_f[l]); };
-    auto R_ = [&](int l) { return reinterpret_cast<T*>(smem + d.off_r[l]); };
-    const int L = d.nlev - 1;  // coarsest, natural, m cells
-    {
-        // split (red, black) global arrays of the first tail level -> natural LDS
-        const int nx = d.nx[0], ny = d.ny[0], hx = nx >> 1, nh = hx * ny * d.nz[0];
-        T* F0 = F_(0);
-        const TailPos dec(hx, ny);
-        for (int j = threadIdx.x; j < nh; j += blockDim.x) {
-            int i, y, z;
-            dec(j, i, y, z);
-            const int row = (z * ny + y) * nx, par = (y + z) & 1;
-            F0[row + 2 * i + par] = f0g[j];
-            F0[row + 2 * i + (par ^ 1)] = f1g[j];
-        }
-    }
-    __syncthreads();
-    for (int l = 0; l < L; ++l) {
-        const int nx = d.nx[l], ny = d.ny[l], nz = d.nz[l], n = nx * ny * nz;
-        T* U = U_(l);
-        T* F = F_(l);
-        T* R = R_(l);
-        const T s = (T)d.s[l], dg0 = (T)d.diag[l];
-        const TailInv<T> inv(dg0, s);
-        for (int j = threadIdx.x; j < n; j += blockDim.x) U[j] = (T)0;
-        __syncthreads();
-        tail_gs_box(U, F, nx, ny, nz, 0, s, inv);
-        tail_gs_box(U, F, nx, ny, nz, 1, s, inv);
-        tail_gs_box(U, F, nx, ny, nz, 0, s, inv);
-        tail_gs_box(U, F, nx, ny, nz, 1, s, inv);
-        const TailPos dec(nx, ny);
-        for (int j = threadIdx.x; j < n; j += blockDim.x) {
-            int x, y, z;
-            dec(j, x, y, z);
-            const T dg = dg0 + (T)box_faces(x, y, z, nx, ny, nz) * s;
-            R[j] = ((x + y + z) & 1) ? (T)0 : F[j] - (dg * U[j] - s * tail_nb_box(U, x, y, z, nx, ny, nz));
-        }
-        __syncthreads();
-        const int cx = nx >> 1, cy = ny >> 1, nc = cx * cy * (nz >> 1);
-        T* Fc = F_(l + 1);
-        const TailPos cdec(cx, cy);
-        for (int j = threadIdx.x; j < nc; j += blockDim.x) {
-            int X, Y, Z;
-            cdec(j, X, Y, Z);
-            T acc = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const T wz = box_rweight<T>(c, Z, nz);
-                if (wz == (T)0) continue;
-                T accb = 0;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const T wy = box_rweight<T>(b, Y, ny);
-                    if (wy == (T)0) continue;
-                    const T* rr = R + ((2 * Z - 1 + c) * ny + (2 * Y - 1 + b)) * nx;
-                    T acca = 0;
-#pragma unroll
-                    for (int a = 0; a < 4; ++a) {
-                        const T wx = box_rweight<T>(a, X, nx);
-                        if (wx != (T)0) acca += wx * rr[2 * X - 1 + a];
-                    }
-                    accb += wy * acca;
-                }
-                acc += wz * accb;
-            }
-            Fc[j] = acc;
-        }
-        __syncthreads();
-    }
-    {
-        // one wave per row of the dense inverse
-        const T* Fl = F_(L);
-        T* Ul = U_(L);
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-        for (int i = wv; i < d.m; i += nw) {
-            const double* row = cinv + (size_t)i * d.m;
-            double acc = 0.0;
-            for (int j = lane; j < d.m; j += 64) acc += row[j] * (double)Fl[j];
-            acc = wave_sum(acc);
-            if (lane == 0) Ul[i] = (T)acc;
-        }
-    }
-    __syncthreads();
-    for (int l = L - 1; l >= 0; --l) {
-        const int nx = d.nx[l], ny = d.ny[l], nz = d.nz[l], n = nx * ny * nz;
-        const int cx = nx >> 1, cy = ny >> 1, cz = nz >> 1;
-        const T* C = U_(l + 1);
-        T* U = U_(l);
-        const T* F = F_(l);
-        const TailPos dec(nx, ny);
-        for (int j = threadIdx.x; j < n; j += blockDim.x) {
-            int x, y, z;
-            dec(j, x, y, z);
-            int I0, I1, J0, J1, K0, K1;
-            T a0, a1, b0, b1, c0, c1;
-            box_pweights<T>(x, cx, I0, I1, a0, a1);
-            box_pweights<T>(y, cy, J0, J1, b0, b1);
-            box_pweights<T>(z, cz, K0, K1, c0, c1);
-            auto line = [&](int J, int K) {
-                const T* cr = C + (K * cy + J) * cx;
-                return a0 * cr[I0] + a1 * cr[I1];
-            };
-            U[j] += c0 * (b0 * line(J0, K0) + b1 * line(J1, K0)) + c1 * (b0 * line(J0, K1) + b1 * line(J1, K1));
-        }
-        __syncthreads();
-        const T s = (T)d.s[l];
-        const TailInv<T> inv((T)d.diag[l], s);
-        tail_gs_box(U, F, nx, ny, nz, 1, s, inv);
-        tail_gs_box(U, F, nx, ny, nz, 0, s, inv);
-        tail_gs_box(U, F, nx, ny, nz, 1, s, inv);
-        tail_gs_box(U, F, nx, ny, nz, 0, s, inv);
-    }
-    {
-        const int nx = d.nx[0], ny = d.ny[0], hx = nx >> 1, nh = hx * ny * d.nz[0];
-        const T* U0 = U_(0);
-        const TailPos dec(hx, ny);
-        for (int j = threadIdx.x; j < nh; j += blockDim.x) {
-            int i, y, z;
-            dec(j, i, y, z);
-            const int row = (z * ny + y) * nx, par = (y + z) & 1;
-            u0g[j] = U0[row + 2 * i + par];
-            u1g[j] = U0[row + 2 * i + (par ^ 1)];
-        }
-    }
-}
-
-template <typename T>
-void launch_tail_box(hipStream_t st, const T* f0, const T* f1, T* u0, T* u1, const TailDesc& d, const double* cinv,
-                     const Scalars* sc) {
-    hipLaunchKernelGGL(k_tail_box<T>, dim3(1), dim3(kFinBlock), d.lds_bytes, st, f0, f1, u0, u1, d, cinv, sc);
-}
-
-template <typename T>
-hipError_t tail_box_set_lds(size_t bytes) {
-    return hipFuncSetAttribute((const void*)k_tail_box<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-
 #define BRD_BOX_INST(T)                                                                                              \
     template void launch_enter_box<T>(hipStream_t, const double*, T*, T*, T*, int, int, int, const BoxCoef&,         \
                                       const Scalars*);                                                               \
@@ -769,10 +555,7 @@ hipError_t tail_box_set_lds(size_t bytes) {
                                           const BoxCoef&, const Scalars*);                                           \
     template void launch_restrict_box<T>(hipStream_t, const T*, int, int, int, T*, T*, T*, int, const BoxCoef&,      \
                                          const Scalars*);                                                            \
-    template void launch_prolong_red_box<T>(hipStream_t, const T*, const T*, int, T*, int, int, int, const Scalars*); \
-    template void launch_tail_box<T>(hipStream_t, const T*, const T*, T*, T*, const TailDesc&, const double*,       \
-                                     const Scalars*);                                                                \
-    template hipError_t tail_box_set_lds<T>(size_t);
+    template void launch_prolong_red_box<T>(hipStream_t, const T*, const T*, int, T*, int, int, int, const Scalars*);
 BRD_BOX_INST(float)
 BRD_BOX_INST(double)
 #undef BRD_BOX_INST

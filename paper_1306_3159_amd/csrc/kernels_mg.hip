@@ -611,23 +611,6 @@ __device__ __forceinline__ T coarse_at(const T* __restrict__ c0, const T* __rest
     return ((X + Y + Z) & 1) ? c1[j] : c0[j];
 }
 
-// u plus the trilinear correction of one fine cell from its four coarse rows (J0, K0),
-// (J1, K0), (J0, K1), (J1, K1): m is a row's value at the cell's own coarse x, n the one at
-// the neighbour on the cell's side. Evaluated as written, with no contraction beyond the
-// explicit FMAs, so that every form of the correction (per level, blocked, LDS tail) rounds
-// alike.
-template <typename T>
-__device__ __forceinline__ T tri_add(T u, T m00, T n00, T m10, T n10, T m01, T n01, T m11, T n11) {
-#pragma clang fp contract(off)
-    const T a00 = fma((T)0.75, m00, (T)0.25 * n00);
-    const T a10 = fma((T)0.75, m10, (T)0.25 * n10);
-    const T a01 = fma((T)0.75, m01, (T)0.25 * n01);
-    const T a11 = fma((T)0.75, m11, (T)0.25 * n11);
-    const T b0 = fma((T)0.75, a00, (T)0.25 * a10);
-    const T b1 = fma((T)0.75, a01, (T)0.25 * a11);
-    return u + fma((T)0.75, b0, (T)0.25 * b1);
-}
-
 template <typename T>
 __global__ void __launch_bounds__(kMaxTuneBlock) k_prolong(const T* __restrict__ cu0, const T* __restrict__ cu1, int nat,
                                                     T* __restrict__ u0, T* __restrict__ u1, int nx, int ny, int nz,
@@ -950,244 +933,6 @@ hipError_t blocked_set_lds() {
 }
 
 // ---------------------------------------------------------------------------
-// Coarsest grid: u = C f with C the dense FP64 (pseudo-)inverse, m <= 512.
-template <typename T>
-__global__ void __launch_bounds__(kMaxCoarse) k_coarse(const T* __restrict__ f, T* __restrict__ u,
-                                                       const double* __restrict__ cinv, int m, const Scalars* sc) {
-    if (sc && sc->done) return;
-    __shared__ double fs[kMaxCoarse];
-    for (int j = threadIdx.x; j < m; j += blockDim.x) fs[j] = (double)f[j];
-    __syncthreads();
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    for (int i = wv; i < m; i += nw) {
-        const double* row = cinv + (size_t)i * m;
-        double acc = 0.0;
-        for (int j = lane; j < m; j += 64) acc += row[j] * fs[j];
-        acc = wave_sum(acc);
-        if (lane == 0) u[i] = (T)acc;
-    }
-}
-
-template <typename T>
-void launch_coarse(hipStream_t st, const T* f, T* u, const double* cinv, int m, const Scalars* sc) {
-    hipLaunchKernelGGL(k_coarse<T>, dim3(1), dim3(kMaxCoarse), 0, st, f, u, cinv, m, sc);
-}
-
-// ---------------------------------------------------------------------------
-// Coarse tail: the whole V-cycle below level t in one work-group with every
-// level in LDS (natural layout [z][y][x]). It performs exactly the operations
-// of the per-level kernels, in the same order and with the same summation
-// order, so it is interchangeable with them: zero initial guess, R B R B
-// pre-smoothing, residual, full weighting, coarse dense solve, trilinear
-// correction, B R B R post-smoothing.
-// Thread-strided loops over each level's cells; cell coordinates are decoded
-// on the fly (shifts and masks for power-of-two dimensions), so no per-thread
-// cell tables are kept live across the barriers.
-__device__ __forceinline__ bool tail_pow2(int a) { return (a & (a - 1)) == 0; }
-
-// j -> (a, b, c) for row-major dims (na, nb, *).
-__device__ __forceinline__ void tail_decode(int j, int na, int nb, bool p2, int la, int lab, int& a, int& b, int& c) {
-    if (p2) {
-        a = j & (na - 1);
-        b = (j >> la) & (nb - 1);
-        c = j >> lab;
-    } else {
-        a = j % na;
-        const int t = j / na;
-        b = t % nb;
-        c = t / nb;
-    }
-}
-
-// Decoder of one (na, nb) plane shape: uniform across the work-group.
-struct TailDec {
-    int na, nb, la, lab;
-    bool p2;
-    __device__ __forceinline__ TailDec(int a, int b) : na(a), nb(b) {
-        p2 = tail_pow2(a) && tail_pow2(b);
-        la = __ffs(a) - 1;
-        lab = la + __ffs(b) - 1;
-    }
-    __device__ __forceinline__ void operator()(int j, int& x, int& y, int& z) const {
-        tail_decode(j, na, nb, p2, la, lab, x, y, z);
-    }
-};
-
-template <typename T>
-__device__ __forceinline__ T tail_nb(const T* u, int x, int y, int z, int nx, int ny, int nz) {
-    const int row = (z * ny + y) * nx;
-    const T a = u[row + wrapi(x - 1, nx)] + u[row + wrapi(x + 1, nx)];
-    const T b = u[(z * ny + wrapi(y - 1, ny)) * nx + x] + u[(z * ny + wrapi(y + 1, ny)) * nx + x];
-    const T c = u[(wrapi(z - 1, nz) * ny + y) * nx + x] + u[(wrapi(z + 1, nz) * ny + y) * nx + x];
-    return (a + b) + c;
-}
-
-// One half-sweep of colour `color` (red: x + y + z even) in LDS.
-template <typename T>
-__device__ __forceinline__ void tail_gs(T* u, const T* f, int nx, int ny, int nz, int color, T s, T inv_diag) {
-    const int hx = nx >> 1, nh = hx * ny * nz;
-    const TailDec dec(hx, ny);
-    for (int j = threadIdx.x; j < nh; j += blockDim.x) {
-        int i, y, z;
-        dec(j, i, y, z);
-        const int x = 2 * i + ((y + z + color) & 1);
-        const int k = (z * ny + y) * nx + x;
-        u[k] = (f[k] + s * tail_nb(u, x, y, z, nx, ny, nz)) * inv_diag;
-    }
-    __syncthreads();
-}
-
-// Coarse tail: the whole V-cycle below level t in one work-group with every
-// level in LDS (natural layout [z][y][x]). It performs exactly the operations
-// of the per-level kernels, in the same order and with the same summation
-// order, so it is interchangeable with them: zero initial guess, R B R B
-// pre-smoothing, residual, full weighting, coarse dense solve, trilinear
-// correction, B R B R post-smoothing.
-template <typename T>
-__device__ __forceinline__ void tail_body(const T* __restrict__ f0g, const T* __restrict__ f1g, T* __restrict__ u0g,
-                                          T* __restrict__ u1g, const TailDesc& d, const double* __restrict__ cinv) {
-    extern __shared__ __align__(16) unsigned char smem[];
-#define TAIL_U(l) reinterpret_cast<T*>(smem + d.off_u[l])
-#define TAIL_F(l) reinterpret_cast<T*>(smem + d.off_f[l])
-#define TAIL_R(l) reinterpret_cast<T*>(smem + d.off_r[l])
-    const int L = d.nlev - 1;  // coarsest, natural, m cells
-    {
-        // split (red, black) global arrays -> natural LDS level 0
-        const int nx = d.nx[0], ny = d.ny[0], hx = nx >> 1, nh = hx * ny * d.nz[0];
-        const TailDec dec(hx, ny);
-        T* F0 = TAIL_F(0);
-        for (int j = threadIdx.x; j < nh; j += blockDim.x) {
-            int i, y, z;
-            dec(j, i, y, z);
-            const int row = (z * ny + y) * nx, par = (y + z) & 1;
-            F0[row + 2 * i + par] = f0g[j];
-            F0[row + 2 * i + (par ^ 1)] = f1g[j];
-        }
-    }
-    __syncthreads();
-    for (int l = 0; l < L; ++l) {
-        const int nx = d.nx[l], ny = d.ny[l], nz = d.nz[l], n = nx * ny * nz;
-        T* U = TAIL_U(l);
-        T* F = TAIL_F(l);
-        T* R = TAIL_R(l);
-        const T s = (T)d.s[l], idg = (T)d.inv_diag[l], dg = (T)d.diag[l];
-        for (int j = threadIdx.x; j < n; j += blockDim.x) U[j] = (T)0;
-        __syncthreads();
-        tail_gs(U, F, nx, ny, nz, 0, s, idg);
-        tail_gs(U, F, nx, ny, nz, 1, s, idg);
-        tail_gs(U, F, nx, ny, nz, 0, s, idg);
-        tail_gs(U, F, nx, ny, nz, 1, s, idg);
-        {
-            const TailDec dec(nx, ny);
-            for (int j = threadIdx.x; j < n; j += blockDim.x) {
-                int x, y, z;
-                dec(j, x, y, z);
-                R[j] = ((x + y + z) & 1) ? (T)0 : F[j] - (dg * U[j] - s * tail_nb(U, x, y, z, nx, ny, nz));
-            }
-        }
-        __syncthreads();
-        const int cx = nx >> 1, cy = ny >> 1, nc = cx * cy * (nz >> 1);
-        T* Fc = TAIL_F(l + 1);
-        const T w0 = (T)0.125, w1 = (T)0.375;
-        const TailDec cdec(cx, cy);
-        for (int j = threadIdx.x; j < nc; j += blockDim.x) {
-            int X, Y, Z;
-            cdec(j, X, Y, Z);
-            const int x0 = wrapi(2 * X - 1, nx), x1 = 2 * X, x2 = 2 * X + 1, x3 = wrapi(2 * X + 2, nx);
-            T acc = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const int z = wrapi(2 * Z - 1 + c, nz);
-                T accb = 0;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const T* rr = R + (z * ny + wrapi(2 * Y - 1 + b, ny)) * nx;
-                    const T acca = ((w0 * rr[x0] + w1 * rr[x1]) + w1 * rr[x2]) + w0 * rr[x3];
-                    accb += (b == 0 || b == 3 ? w0 : w1) * acca;
-                }
-                acc += (c == 0 || c == 3 ? w0 : w1) * accb;
-            }
-            Fc[j] = acc;
-        }
-        __syncthreads();
-    }
-    {
-        // one wave per row of the dense inverse: coalesced loads, wave reduction
-        const T* Fl = TAIL_F(L);
-        T* Ul = TAIL_U(L);
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-        for (int i = wv; i < d.m; i += nw) {
-            const double* row = cinv + (size_t)i * d.m;
-            double acc = 0.0;
-            for (int j = lane; j < d.m; j += 64) acc += row[j] * (double)Fl[j];
-            acc = wave_sum(acc);
-            if (lane == 0) Ul[i] = (T)acc;
-        }
-    }
-    __syncthreads();
-    for (int l = L - 1; l >= 0; --l) {
-        const int nx = d.nx[l], ny = d.ny[l], nz = d.nz[l], n = nx * ny * nz;
-        const int cx = nx >> 1, cy = ny >> 1, cz = nz >> 1;
-        const T* C = TAIL_U(l + 1);
-        T* U = TAIL_U(l);
-        const T* F = TAIL_F(l);
-        const TailDec dec(nx, ny);
-        for (int j = threadIdx.x; j < n; j += blockDim.x) {
-            int x, y, z;
-            dec(j, x, y, z);
-            const int I0 = x >> 1, I1 = wrapi((x & 1) ? I0 + 1 : I0 - 1, cx);
-            const int J0 = y >> 1, J1 = wrapi((y & 1) ? J0 + 1 : J0 - 1, cy);
-            const int K0 = z >> 1, K1 = wrapi((z & 1) ? K0 + 1 : K0 - 1, cz);
-            const T* c00 = C + (K0 * cy + J0) * cx;
-            const T* c10 = C + (K0 * cy + J1) * cx;
-            const T* c01 = C + (K1 * cy + J0) * cx;
-            const T* c11 = C + (K1 * cy + J1) * cx;
-            U[j] = tri_add(U[j], c00[I0], c00[I1], c10[I0], c10[I1], c01[I0], c01[I1], c11[I0], c11[I1]);
-        }
-        __syncthreads();
-        const T s = (T)d.s[l], idg = (T)d.inv_diag[l];
-        tail_gs(U, F, nx, ny, nz, 1, s, idg);
-        tail_gs(U, F, nx, ny, nz, 0, s, idg);
-        tail_gs(U, F, nx, ny, nz, 1, s, idg);
-        tail_gs(U, F, nx, ny, nz, 0, s, idg);
-    }
-    {
-        const int nx = d.nx[0], ny = d.ny[0], hx = nx >> 1, nh = hx * ny * d.nz[0];
-        const TailDec dec(hx, ny);
-        const T* U0 = TAIL_U(0);
-        for (int j = threadIdx.x; j < nh; j += blockDim.x) {
-            int i, y, z;
-            dec(j, i, y, z);
-            const int row = (z * ny + y) * nx, par = (y + z) & 1;
-            u0g[j] = U0[row + 2 * i + par];
-            u1g[j] = U0[row + 2 * i + (par ^ 1)];
-        }
-    }
-#undef TAIL_U
-#undef TAIL_F
-#undef TAIL_R
-}
-
-template <typename T>
-__global__ void __launch_bounds__(kFinBlock) k_tail(const T* __restrict__ f0g, const T* __restrict__ f1g,
-                                                    T* __restrict__ u0g, T* __restrict__ u1g, TailDesc d,
-                                                    const double* __restrict__ cinv, const Scalars* sc) {
-    if (sc && sc->done) return;
-    tail_body<T>(f0g, f1g, u0g, u1g, d, cinv);
-}
-
-template <typename T>
-void launch_tail(hipStream_t st, const T* f0, const T* f1, T* u0, T* u1, const TailDesc& d, const double* cinv,
-                 const Scalars* sc) {
-    hipLaunchKernelGGL(k_tail<T>, dim3(1), dim3(kFinBlock), d.lds_bytes, st, f0, f1, u0, u1, d, cinv, sc);
-}
-
-template <typename T>
-hipError_t tail_set_lds(size_t bytes) {
-    return hipFuncSetAttribute((const void*)k_tail<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-
-// ---------------------------------------------------------------------------
 // Batched forms: one launch covers one level of every instance in the table
 // (the same bodies as the solo kernels, so results are bitwise the same).
 template <typename T>
@@ -1258,17 +1003,6 @@ __global__ void __launch_bounds__(kBlock) kb_prolong(const InstDev* inst, const 
     }
 }
 
-// One work-group per instance: the coarse tail from the instance's level t.
-template <typename T>
-__global__ void __launch_bounds__(kFinBlock) kb_tail(const InstDev* inst, const int* gate, int ninst) {
-    const int i = blockIdx.x;
-    if (i >= ninst || !gate[i]) return;
-    const InstDev* I = inst + i;
-    if (I->sc->done) return;
-    T* const* a = reinterpret_cast<T* const*>(I->lv[I->t]);
-    tail_body<T>(a[2], a[3], a[0], a[1], I->tail, I->cinv);
-}
-
 template <typename T>
 void launchb_mg(hipStream_t st, int what, const InstDev* inst, const int* gate, const BatchTab* tab, unsigned grid,
                 int l, int color, unsigned lds) {
@@ -1279,13 +1013,8 @@ void launchb_mg(hipStream_t st, int what, const InstDev* inst, const int* gate, 
         case BMG_RESID: hipLaunchKernelGGL(kb_resid<T>, g, b, 0, st, inst, gate, tab, l); break;
         case BMG_RESTRICT: hipLaunchKernelGGL(kb_restrict<T>, g, b, 0, st, inst, gate, tab, l); break;
         case BMG_PROLONG: hipLaunchKernelGGL(kb_prolong<T>, g, b, 0, st, inst, gate, tab, l); break;
-        default: hipLaunchKernelGGL(kb_tail<T>, dim3(grid), dim3(kFinBlock), lds, st, inst, gate, (int)grid);
+        default: launchb_tail<T>(st, inst, gate, (int)grid, lds);
     }
-}
-
-template <typename T>
-hipError_t tail_set_lds_batched(size_t bytes) {
-    return hipFuncSetAttribute((const void*)kb_tail<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 #define BRD_INST(T)                                                                                                \
@@ -1304,18 +1033,13 @@ hipError_t tail_set_lds_batched(size_t bytes) {
                                     int);                                                                           \
     template unsigned launch_gs_dots<T>(hipStream_t, T*, const T*, const T*, int, int, int, double, double,         \
                                         const double*, const double*, double*, const Scalars*, int);                \
-    template void launch_coarse<T>(hipStream_t, const T*, T*, const double*, int, const Scalars*);             \
-    template void launch_tail<T>(hipStream_t, const T*, const T*, T*, T*, const TailDesc&, const double*,         \
-                                 const Scalars*);                                                                   \
-    template hipError_t tail_set_lds<T>(size_t);                                                                   \
     template void launch_down<T>(hipStream_t, const T*, const T*, const T*, T*, int, int, int, double, double, T*, T*, \
                                  T*, double, const Scalars*);                                                      \
     template void launch_up<T>(hipStream_t, const T*, const T*, const T*, const T*, const T*, T*, T*, int, int, int,  \
                                double, double, const Scalars*);                                                    \
     template hipError_t blocked_set_lds<T>();                                                                      \
     template void launchb_mg<T>(hipStream_t, int, const InstDev*, const int*, const BatchTab*, unsigned, int, int,   \
-                                unsigned);                                                                         \
-    template hipError_t tail_set_lds_batched<T>(size_t);
+                                unsigned);                                                                         
 
 BRD_INST(float)
 BRD_INST(double)

@@ -126,8 +126,9 @@ void launch_restrict(hipStream_t st, const T* r0, int nx, int ny, int nz, T* cf0
 template <typename T>
 void launch_prolong(hipStream_t st, const T* cu0, const T* cu1, int coarse_natural, T* u0, T* u1, int nx, int ny,
                     int nz, const Scalars* sc, int bs = kBlock);
+// a grid that is itself the coarsest level (natural, spec: the coarsest solve's spectral tables)
 template <typename T>
-void launch_coarse(hipStream_t st, const T* f, T* u, const double* cinv, int m, const Scalars* sc);
+void launch_coarse(hipStream_t st, const T* f, T* u, const double* spec, int nx, int ny, int nz, const Scalars* sc);
 
 // ---- multigrid of a box with homogeneous faces (split layout, one cell per thread) ----
 // The same V-cycle steps as above with the box operator: per-cell diagonals from
@@ -148,16 +149,13 @@ void launch_restrict_box(hipStream_t st, const T* r0, int nx, int ny, int nz, T*
 template <typename T>
 void launch_prolong_red_box(hipStream_t st, const T* cu0, const T* cu1, int coarse_natural, T* u0, int nx, int ny,
                             int nz, const Scalars* sc);
-// the box V-cycle below level t in one work-group (levels in LDS), as launch_tail
-template <typename T>
-void launch_tail_box(hipStream_t st, const T* f0, const T* f1, T* u0, T* u1, const TailDesc& d, const double* cinv,
-                     const Scalars* sc);
-template <typename T>
-hipError_t tail_box_set_lds(size_t bytes);
 
+// the V-cycle below level t in one work-group (levels in LDS; box: the box operator)
 template <typename T>
-void launch_tail(hipStream_t st, const T* f0, const T* f1, T* u0, T* u1, const TailDesc& d, const double* cinv,
-                 const Scalars* sc);
+void launch_tail(hipStream_t st, const T* f0, const T* f1, T* u0, T* u1, const TailDesc& d, const double* spec,
+                 bool box, const Scalars* sc);
+template <typename T>
+void launchb_tail(hipStream_t st, const InstDev* inst, const int* gate, int ninst, unsigned lds);
 template <typename T>
 hipError_t tail_set_lds(size_t bytes);
 // temporally blocked level (nx, ny, nz divisible by 8): pre-smoothing + red residual +
@@ -183,8 +181,6 @@ void launchb_cg(hipStream_t st, int what, const InstDev* inst, const int* gate, 
 template <typename T>
 void launchb_mg(hipStream_t st, int what, const InstDev* inst, const int* gate, const BatchTab* tab, unsigned grid,
                 int l, int color, unsigned lds);
-template <typename T>
-hipError_t tail_set_lds_batched(size_t bytes);
 // measurement probe: out = a + b over `bytes` bytes of 16-byte vectors
 void launch_stream_add(hipStream_t st, const void* a, const void* b, void* out, size_t bytes);
 // blob term: interp (spread = 0) or spread (1)
