@@ -191,6 +191,46 @@ struct LevelDims {
 // ---- helpers -------------------------------------------------------------
 __device__ __forceinline__ int wrapi(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
+// The smoother's update, the red residual and one row of the restriction, with their
+// roundings fixed (no contraction beyond the explicit FMAs), so that every form of a level
+// (per step, two launches a level, LDS tail) gives the same bits.
+template <typename T>
+__device__ __forceinline__ T relax(T f, T s, T nb, T inv_diag) {
+#pragma clang fp contract(off)
+    return fma(s, nb, f) * inv_diag;
+}
+template <typename T>
+__device__ __forceinline__ T relax_zero(T f, T inv_diag) {  // from a zero guess
+#pragma clang fp contract(off)
+    return f * inv_diag;
+}
+template <typename T>
+__device__ __forceinline__ T red_resid(T f, T diag, T u, T s, T nb) {
+#pragma clang fp contract(off)
+    return f - fma(diag, u, -(s * nb));
+}
+// p = 1: (a, b) = r0[X-1], r0[X]; p = 0: (b, c) = r0[X], r0[X+1]
+template <typename T>
+__device__ __forceinline__ T restrict_row(T w0, T w1, int p, T a, T b, T c) {
+#pragma clang fp contract(off)
+    return fma(w1, b, w0 * (p ? a : c));
+}
+
+// Tile of a two-launch level: lanes vectors of vw cells to a row, ty rows and tz planes to a
+// work-group, nty x ntz tiles, and the multipliers that divide by lanes and by the windows'
+// rows a plane. lanes = 0: not applicable.
+struct LevelTile {
+    int lanes, vw, ty, tz, nty, ntz;
+    unsigned mlanes, mdown, mup;
+};
+
+// Coefficients of a level in its precision: s = D / h^2 and, by the box faces a cell touches
+// (all alike in the periodic cell), the diagonals, their inverses and the next level's.
+template <typename T>
+struct LevelCoef {
+    T s, diag[4], inv[4], invc[4];
+};
+
 // u plus the trilinear correction of one fine cell from its four coarse rows (J0, K0),
 // (J1, K0), (J0, K1), (J1, K1): m is a row's value at the cell's own coarse x, n the one at
 // the neighbour on the cell's side. Evaluated as written, with no contraction beyond the
@@ -286,6 +326,14 @@ __device__ __forceinline__ double wg_sum(double s) {
     for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += sh[w];
     __syncthreads();
     return t;
+}
+
+// Work-group barrier that orders LDS accesses only: unlike __syncthreads() it does not wait
+// for global loads and stores in flight. For kernels whose threads exchange data in LDS alone.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 inline unsigned nblocks(size_t n, int bs = kBlock) { return (unsigned)((n + bs - 1) / bs); }

@@ -386,7 +386,8 @@ struct blob_rd {
     hipStream_t cap_stream = nullptr;
     bool use_graphs = true;
     bool relax = true;  // relaxed inner tolerances in the Schur GMRES
-    bool blocked = true;  // temporally blocked launches on the coarser per-level levels
+    bool blocked = true;  // two launches a level (kernels_level.hip) where they apply
+    LevelTile tile[kMaxLevels] = {};  // per level: its tile (lanes = 0: per-step launches)
     bool reorth_always = false;  // the block FGMRES re-orthogonalises every new basis vector
     // block FGMRES steps issued ahead of the host's reads: 0 never, 1 when the contraction says
     // the step in flight will not converge, 2 always (every converging step has one behind it)
@@ -590,10 +591,10 @@ TailDesc make_tail(const blob_rd* H, int t, double alpha) {
 // half-sweep, which does not read them) and four half-sweeps on the way up.
 constexpr double kPreRestrictBytes = 3 * 1.5 + 2.0 + 0.5 + 0.1875;
 constexpr double kProlongPostBytes = 1.125 + 4 * 1.5;
-// temporally blocked levels: red u and f in, pre-smoothed red and coarse f, u out;
-// coarse u, pre-smoothed red and f in, both colours out
-constexpr double kBlockedDownBytes = 0.5 + 1.0 + 0.5 + 0.1875;
-constexpr double kBlockedUpBytes = 0.125 + 0.5 + 1.0 + 1.0;
+// two-launch levels: f in, pre-smoothed red and coarse f out; coarse u, pre-smoothed red and f
+// in, both colours out
+constexpr double kFusedDownBytes = 1.0 + 0.5 + 0.125;
+constexpr double kFusedUpBytes = 0.125 + 0.5 + 1.0 + 1.0;
 
 // alpha I - D L has a null space (the constant) only on the periodic grid with alpha = 0
 bool singular(const blob_rd* H, double alpha) { return alpha == 0.0 && !H->box; }
@@ -608,6 +609,39 @@ void box_coefs(const blob_rd* H, int l, double alpha, BoxCoef* diag, BoxCoef* in
         if (diag) diag->v[f] = v;
         if (inv) inv->v[f] = 1.0 / v;
     }
+}
+
+// Level l in two launches (above the LDS tail only, so the next level is split): its zero-guess red sweep is stored where per-step launches follow.
+template <typename T>
+bool fused(const blob_rd* H, int l) {
+    const int t = H->tail_level[sizeof(T) == 4 ? 0 : 1];
+    return H->blocked && sizeof(T) == H->P.esz && l < t && t < H->P.nlev - 1 && H->tile[l].lanes > 0;
+}
+template <typename T>
+bool level_down(blob_rd* H, int l, int t, double alpha, const Scalars* sc) {
+    if (!fused<T>(H, l)) return false;
+    const Plan& P = H->P;
+    const LevelDims &d = P.lev[l], &c = P.lev[l + 1];
+    auto lv = [&](int k, int a) { return H->at<T>(P.off_lvl[k][a]); };
+    const double D = H->prm.D;
+    launch_level_down<T>(H->st, H->tile[l], H->box, lv(l, 2), lv(l, 3), lv(l, 4), d.nx, d.ny, d.nz,
+                         level_coef<T>(D / (d.h * d.h), alpha, D / (c.h * c.h), H->box), lv(l + 1, 2), lv(l + 1, 3),
+                         l + 1 == t || fused<T>(H, l + 1) ? nullptr : lv(l + 1, 0), sc);
+    H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kFusedDownBytes;
+    return true;
+}
+template <typename T>
+bool level_up(blob_rd* H, int l, double alpha, int sweeps, const Scalars* sc) {
+    if (!fused<T>(H, l)) return false;
+    const Plan& P = H->P;
+    const LevelDims &d = P.lev[l], &c = P.lev[l + 1];
+    auto lv = [&](int k, int a) { return H->at<T>(P.off_lvl[k][a]); };
+    const double D = H->prm.D;
+    launch_level_up<T>(H->st, H->tile[l], H->box, sweeps, lv(l + 1, 0), lv(l + 1, 1), lv(l, 4), lv(l, 2), lv(l, 3),
+                       lv(l, 0), lv(l, 1), d.nx, d.ny, d.nz,
+                       level_coef<T>(D / (d.h * d.h), alpha, D / (c.h * c.h), H->box), sc);
+    H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * (sweeps == 4 ? kFusedUpBytes : kFusedUpBytes - 0.5);
+    return true;
 }
 
 // The V-cycle of vcycle() below for the box operator alpha I - D L_0: the same
@@ -625,12 +659,14 @@ void vcycle_box(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
     for (int l = 0; l <= L; ++l) box_coefs(H, l, alpha, &dg[l], &inv[l]);
     if (!entered) {
         const LevelDims& d = P.lev[0];
-        launch_enter_box<T>(st, r, lv(0, 2), lv(0, 3), lv(0, 0), d.nx, d.ny, d.nz, inv[0], sc);
-        H->alg_bytes += (double)P.ncell * (8 + P.esz * 1.5);
+        launch_enter_box<T>(st, r, lv(0, 2), lv(0, 3), fused<T>(H, 0) ? nullptr : lv(0, 0), d.nx, d.ny, d.nz,
+                            inv[0], sc);
+        H->alg_bytes += (double)P.ncell * (8 + P.esz * (fused<T>(H, 0) ? 1.0 : 1.5));
     }
     for (int l = 0; l < t; ++l) {
         const LevelDims& d = P.lev[l];
         const double s = H->prm.D / (d.h * d.h);
+        if (level_down<T>(H, l, t, alpha, sc)) continue;
         launch_gs_box<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.nx, d.ny, d.nz, 1, s, inv[l], sc);
         launch_gs_box<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.nx, d.ny, d.nz, 0, s, inv[l], sc);
         launch_gs_box<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.nx, d.ny, d.nz, 1, s, inv[l], sc);
@@ -647,6 +683,7 @@ void vcycle_box(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
     for (int l = t - 1; l >= 0; --l) {
         const LevelDims& d = P.lev[l];
         const double s = H->prm.D / (d.h * d.h);
+        if (level_up<T>(H, l, alpha, 4, sc)) continue;
         const int cnat = (l + 1 == L);
         launch_prolong_red_box<T>(st, lv(l + 1, 0), cnat ? nullptr : lv(l + 1, 1), cnat, lv(l, 0), d.nx, d.ny, d.nz,
                                   sc);
@@ -702,29 +739,16 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
         // with from_f the first red sweep is not stored: the opening black sweep forms it
         const LevelDims& d = P.lev[0];
         const double s = D / (d.h * d.h);
-        launch_enter<T>(st, r, lv(0, 2), lv(0, 3), from_f ? nullptr : lv(0, 0), d.nx, d.ny, d.nz,
+        const bool no_u = from_f || fused<T>(H, 0);
+        launch_enter<T>(st, r, lv(0, 2), lv(0, 3), no_u ? nullptr : lv(0, 0), d.nx, d.ny, d.nz,
                         1.0 / (alpha + 6.0 * s), sc);
-        H->alg_bytes += (double)P.ncell * (8 + P.esz * (from_f ? 1.0 : 1.5));
+        H->alg_bytes += (double)P.ncell * (8 + P.esz * (no_u ? 1.0 : 1.5));
     }
-    // levels below the finest whose pre- and post-smoothing run temporally blocked:
-    // those of at most 64^3 cells, where a launch costs more than the level's bytes
-    // (on larger levels the recomputed halos cost more than the launches they save)
-    auto blocked = [&](int l) {
-        const LevelDims& d = P.lev[l];
-        return H->blocked && l >= 1 && d.nx % 8 == 0 && d.ny % 8 == 0 && d.nz % 8 == 0 &&
-               (size_t)d.nx * d.ny * d.nz <= (size_t)64 * 64 * 64;
-    };
     if (t < L) {
         for (int l = 0; l < t; ++l) {
             const LevelDims& d = P.lev[l];
             const double s = D / (d.h * d.h), diag = alpha + 6.0 * s;
-            if (blocked(l)) {
-                const LevelDims& c = P.lev[l + 1];
-                launch_down<T>(st, lv(l, 0), lv(l, 2), lv(l, 3), lv(l, 4), d.nx, d.ny, d.nz, s, diag, lv(l + 1, 2),
-                               lv(l + 1, 3), lv(l + 1, 0), 1.0 / (alpha + 6.0 * (D / (c.h * c.h))), sc);
-                H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kBlockedDownBytes;
-                continue;
-            }
+            if (level_down<T>(H, l, t, alpha, sc)) continue;
             const int* b = H->bs[l];
             first_black(l, s, diag, b);
             launch_gs<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.hx, d.ny, d.nz, 0, s, 1.0 / diag, sc, b[0]);
@@ -741,10 +765,14 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
         for (int l = t - 1; l >= 0; --l) {
             const LevelDims& d = P.lev[l];
             const double s = D / (d.h * d.h), diag = alpha + 6.0 * s;
-            if (blocked(l)) {
-                launch_up<T>(st, lv(l + 1, 0), lv(l + 1, 1), lv(l, 4), lv(l, 2), lv(l, 3), lv(l, 0), lv(l, 1), d.nx,
-                             d.ny, d.nz, s, diag, sc);
-                H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kBlockedUpBytes;
+            if (fused<T>(H, l)) {
+                // with the CG dots the closing red sweep keeps its own launch, which forms them
+                const bool dots = l == 0 && dot_q && sc && d.hx % (16 / (int)sizeof(T)) == 0;
+                level_up<T>(H, l, alpha, dots ? 3 : 4, sc);
+                if (dots) {
+                    last_red(l, s, diag, H->bs[l]);
+                    H->alg_bytes += (double)P.ncell * P.esz * 1.5;
+                }
                 continue;
             }
             const int* b = H->bs[l];
@@ -914,8 +942,8 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
             launch_fin(s_, FIN_ALPHA, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
         }
         launch_update2_enter<T>(s_, x, r, p, q, H->at<T>(P.off_lvl[0][2]), H->at<T>(P.off_lvl[0][3]),
-                                H->at<T>(P.off_lvl[0][0]), d.nx, d.ny, d.nz, 1.0 / (alpha + 6.0 * s), H->part(),
-                                H->sc(), &np, H->box ? &binv : nullptr);
+                                fused<T>(H, 0) ? nullptr : H->at<T>(P.off_lvl[0][0]), d.nx, d.ny, d.nz,
+                                1.0 / (alpha + 6.0 * s), H->part(), H->sc(), &np, H->box ? &binv : nullptr);
         launch_fin(s_, FIN_UPDATE, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
         precond_zdots<T>(H, alpha, r, q, spec, true);
         // direction (z, p r/w), stencil (p, q), update (x, r r/w, p, q) with the V-cycle entry (f, red u)
@@ -1575,7 +1603,8 @@ bool cycle_opens_from_f(const blob_rd* H) {
     const Plan& P = H->P;
     const int t0 = std::min(H->tail_level[sizeof(T) == 4 ? 0 : 1], P.nlev - 1);
     const int vw = 16 / (int)sizeof(T);
-    return !H->box && !(H->batch && H->batch_v) && (t0 == 0 || (P.lev[0].hx % vw == 0 && P.lev[0].hx >= vw));
+    if (H->batch && H->batch_v) return false;
+    return fused<T>(H, 0) || (!H->box && (t0 == 0 || (P.lev[0].hx % vw == 0 && P.lev[0].hx >= vw)));
 }
 
 void batch_run_vcycle(blob_rd* H);
@@ -1627,7 +1656,7 @@ void fg_cycles(blob_rd* H, double alpha, const double* base, const SpreadMult* M
             if (H->box) {
                 BoxCoef binv;
                 box_coefs(H, 0, alpha, nullptr, &binv);
-                launch_enter_box<T>(H->st, base, f0, f1, z0, d.nx, d.ny, d.nz, binv, nullptr);
+                launch_enter_box<T>(H->st, base, f0, f1, from_f ? nullptr : z0, d.nx, d.ny, d.nz, binv, nullptr);
             } else {
                 launch_enter<T>(H->st, base, f0, f1, from_f ? nullptr : z0, d.nx, d.ny, d.nz, inv_diag, nullptr);
             }
@@ -2308,8 +2337,10 @@ int blob_rd_create(const blob_rd_params* p, blob_rd_t* out) {
         if (H->tail_level[0] < Lc) HIPCHK(tail_set_lds<float>(budget));
         if (H->tail_level[1] < Lc) HIPCHK(tail_set_lds<double>(budget));
         if (H->blocked) {
-            HIPCHK(blocked_set_lds<float>());
-            HIPCHK(blocked_set_lds<double>());
+            HIPCHK(level_set_lds<float>());
+            HIPCHK(level_set_lds<double>());
+            for (int l = 0; l + 1 < P.nlev; ++l)
+                if (P.lev[l].nx % 2 == 0) H->tile[l] = level_tile(P.lev[l].nx, P.lev[l].ny, P.lev[l].nz, P.esz);
         }
         H->noalloc = &scratch_slot();
         if (P.off_net) {

@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(kBlock) k_enter_box(const double* __restrict__
     const double fb = r[rowN + 2 * i + (s0 ^ 1)];
     f0[idx] = (T)fr;
     f1[idx] = (T)fb;
-    u0[idx] = (T)((T)fr * (T)inv.v[box_faces(2 * i + s0, y, z, nx, ny, nz)]);
+    if (u0) u0[idx] = (T)((T)fr * (T)inv.v[box_faces(2 * i + s0, y, z, nx, ny, nz)]);  // null: the cycle opens from f
 }
 
 template <typename T>

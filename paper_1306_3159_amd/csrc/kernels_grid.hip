@@ -261,6 +261,7 @@ __device__ __forceinline__ void update2_enter_body(double* __restrict__ x, doubl
         const double fr = par ? fb : fa, fk = par ? fa : fb;
         f0[k] = (T)fr;
         f1[k] = (T)fk;
+        if (!u0) continue;  // the cycle opens from f
         if (BOX) {
             const int xr = 2 * (int)(k % hx) + par;  // the red cell of the pair
             u0[k] = (T)((T)fr * (T)binv.v[box_faces(xr, (int)(t % ny), (int)(t / ny), nx, ny, nz)]);

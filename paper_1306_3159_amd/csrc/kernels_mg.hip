@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(kMaxTuneBlock) k_gs(T* __restrict__ uc, const 
     const int y = t % ny, z = t / ny;
     const int so = ((y + z) & 1) ^ color;
     const T nb = nb_sum(uo, i, y, z, hx, ny, nz, so);
-    uc[idx] = (fc[idx] + s * nb) * inv_diag;
+    uc[idx] = relax(fc[idx], s, nb, inv_diag);
 }
 
 // Vector form: each thread updates VW = 16 / sizeof(T) consecutive cells of a
@@ -180,12 +180,12 @@ __device__ __forceinline__ void gs_vec_body(T* __restrict__ uc, const T* __restr
                 c = zm[k] * inv_diag;
                 e = zp[k] * inv_diag;
             }
-            out[k] = (f[k] + s * (((l + r) + (a + b)) + (c + e))) * inv_diag;
+            out[k] = relax(f[k], s, ((l + r) + (a + b)) + (c + e), inv_diag);
         }
     } else {
 #pragma unroll
         for (int k = 0; k < VW; ++k)
-            out[k] = (f[k] + s * (((left[k] + right[k]) + (ym[k] + yp[k])) + (zm[k] + zp[k]))) * inv_diag;
+            out[k] = relax(f[k], s, ((left[k] + right[k]) + (ym[k] + yp[k])) + (zm[k] + zp[k]), inv_diag);
     }
     *reinterpret_cast<V*>(uc + row + i0) = out;
 }
@@ -238,7 +238,7 @@ __device__ __forceinline__ void gs_vec_dots_body(T* __restrict__ uc, const T* __
         V out;
 #pragma unroll
         for (int k = 0; k < VW; ++k)
-            out[k] = (f[k] + s * (((left[k] + right[k]) + (ym[k] + yp[k])) + (zm[k] + zp[k]))) * inv_diag;
+            out[k] = relax(f[k], s, ((left[k] + right[k]) + (ym[k] + yp[k])) + (zm[k] + zp[k]), inv_diag);
         *reinterpret_cast<V*>(uc + row + i0) = out;
 #pragma unroll
         for (int k = 0; k < VW; ++k) {
@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(kMaxTuneBlock) k_resid(const T* __restrict__ u
     const unsigned t = idx / hx;
     const int y = t % ny, z = t / ny;
     const T nr = nb_sum(u1, i, y, z, hx, ny, nz, (y + z) & 1);  // neighbours of a red cell are black
-    r0[idx] = f0[idx] - (diag * u0[idx] - s * nr);
+    r0[idx] = red_resid(f0[idx], diag, u0[idx], s, nr);
 }
 
 template <typename T>
@@ -348,7 +348,7 @@ __device__ __forceinline__ void resid_vec_body(const T* __restrict__ u0, const T
     V out;
 #pragma unroll
     for (int k = 0; k < VW; ++k)
-        out[k] = f[k] - (diag * u[k] - s * (((left[k] + right[k]) + (ym[k] + yp[k])) + (zm[k] + zp[k])));
+        out[k] = red_resid(f[k], diag, u[k], s, ((left[k] + right[k]) + (ym[k] + yp[k])) + (zm[k] + zp[k]));
     *reinterpret_cast<V*>(r0 + row + i0) = out;
 }
 
@@ -384,12 +384,6 @@ void launch_resid_red(hipStream_t st, const T* u0, const T* u1, const T* f0, T* 
 // In a fine row of parity p = (y + z) & 1 the red cells are x = 2i + p, so
 // of the four fine cells of coarse X the red ones are 2X-1 (weight 1/8) and
 // 2X+1 (3/8) when p = 1, 2X (3/8) and 2X+2 (1/8) when p = 0.
-template <typename T>
-__device__ __forceinline__ T restrict_row(T w0, T w1, int p, T a, T b, T c) {
-    // p = 1: (a, b) = r0[X-1], r0[X]; p = 0: (b, c) = r0[X], r0[X+1]
-    return p ? w0 * a + w1 * b : w1 * b + w0 * c;
-}
-
 template <typename T>
 __global__ void __launch_bounds__(kMaxTuneBlock) k_restrict(const T* __restrict__ r0, int nx, int ny, int nz,
                                                      T* __restrict__ cf0, T* __restrict__ cf1, T* __restrict__ cu0,
@@ -724,215 +718,6 @@ void launch_prolong(hipStream_t st, const T* cu0, const T* cu1, int coarse_natur
 }
 
 // ---------------------------------------------------------------------------
-// Temporally blocked forms for the small per-level levels, where a launch costs
-// more than its bytes: one launch does the whole pre-smoothing, residual and
-// restriction of a tile, one the whole correction and post-smoothing. A tile is
-// 4 x 4 x 4 coarse cells (8^3 fine cells); it is computed in LDS from a halo that
-// shrinks by one cell per half-sweep, so neighbouring tiles recompute their
-// shared halo instead of synchronising. The arithmetic per cell is that of the
-// per-step kernels, in the same order, so the results are bitwise identical.
-constexpr int kTile = 8;             // fine tile edge
-constexpr int kDownW = kTile + 10;   // pre-smoothing window: 5-cell halo
-constexpr int kUpW = kTile + 8;      // post-smoothing window: 4-cell halo
-constexpr int kUpCW = kTile / 2 + 6; // coarse window of the correction
-constexpr int kResW = kTile + 2;     // residual window: 1-cell halo
-
-inline size_t down_lds_bytes(size_t esz) { return esz * (2 * kDownW * kDownW * kDownW + kResW * kResW * kResW); }
-inline size_t up_lds_bytes(size_t esz) { return esz * (2 * kUpW * kUpW * kUpW + kUpCW * kUpCW * kUpCW); }
-
-// One half-sweep of the cells of colour `col` in the window cube [lo, hi)^3 of a
-// W^3 LDS window; a cell's colour is (a + b + c + par) & 1 in window coordinates.
-template <typename T, int W>
-__device__ __forceinline__ void win_sweep(T* U, const T* F, int lo, int hi, int col, int par, T s, T inv_diag) {
-    const int w = hi - lo, half = w >> 1, count = half * w * w;
-    for (int j = threadIdx.x; j < count; j += blockDim.x) {
-        const int i = j % half, t = j / half;
-        const int b = lo + t % w, c = lo + t / w;
-        const int a = lo + 2 * i + ((col + b + c + par - lo) & 1);
-        const int k = (c * W + b) * W + a;
-        U[k] = (F[k] + s * (((U[k - 1] + U[k + 1]) + (U[k - W] + U[k + W])) + (U[k - W * W] + U[k + W * W]))) *
-               inv_diag;
-    }
-    __syncthreads();
-}
-
-// Pre-smoothing (black, red, black from the zero-guess red u0), red residual and
-// restriction of the tile; writes the pre-smoothed red to `ured` (a separate
-// array: neighbouring tiles still read u0 in their halos) and the coarse f and
-// zero-guess red u of level l + 1 (split).
-template <typename T>
-__global__ void __launch_bounds__(kFinBlock) k_down(const T* __restrict__ u0, const T* __restrict__ f0,
-                                                 const T* __restrict__ f1, T* __restrict__ ured, int nx, int ny, int nz,
-                                                 T s, T inv_diag, T diag, T* __restrict__ cf0, T* __restrict__ cf1,
-                                                 T* __restrict__ cu0, T inv_diag_c, const Scalars* sc) {
-    if (sc && sc->done) return;
-    constexpr int W = kDownW;
-    extern __shared__ __align__(16) unsigned char smem[];
-    T* U = reinterpret_cast<T*>(smem);
-    T* F = U + W * W * W;
-    T* R = F + W * W * W;
-    const int hx = nx >> 1, cx = nx >> 1, cy = ny >> 1, cz = nz >> 1;
-    const int tx = cx / 4, ty = cy / 4;
-    const unsigned tile = xcd_block(blockIdx.x, gridDim.x);
-    const int X0 = 4 * (int)(tile % tx), Y0 = 4 * (int)((tile / tx) % ty), Z0 = 4 * (int)(tile / (tx * ty));
-    const int ox = 2 * X0 - 5, oy = 2 * Y0 - 5, oz = 2 * Z0 - 5;  // window origin (fine)
-    for (int j = threadIdx.x; j < W * W * W; j += blockDim.x) {
-        const int a = j % W, b = (j / W) % W, c = j / (W * W);
-        const int x = wrapi(ox + a, nx), y = wrapi(oy + b, ny), z = wrapi(oz + c, nz);
-        const size_t k = ((size_t)z * ny + y) * hx + (x >> 1);
-        const int col = (x + y + z) & 1;
-        F[j] = col ? f1[k] : f0[k];
-        U[j] = col ? (T)0 : u0[k];
-    }
-    __syncthreads();
-    // window colour parity: the origin offsets are odd on all three axes
-    win_sweep<T, W>(U, F, 1, W - 1, 1, 1, s, inv_diag);
-    win_sweep<T, W>(U, F, 2, W - 2, 0, 1, s, inv_diag);
-    win_sweep<T, W>(U, F, 3, W - 3, 1, 1, s, inv_diag);
-    constexpr int RW = kResW;
-    for (int j = threadIdx.x; j < RW * RW * RW; j += blockDim.x) {
-        const int a = 4 + j % RW, b = 4 + (j / RW) % RW, c = 4 + j / (RW * RW);
-        const int k = (c * W + b) * W + a;
-        R[j] = ((a + b + c + 1) & 1)
-                   ? (T)0
-                   : F[k] - (diag * U[k] -
-                             s * (((U[k - 1] + U[k + 1]) + (U[k - W] + U[k + W])) + (U[k - W * W] + U[k + W * W])));
-    }
-    __syncthreads();
-    // pre-smoothed red of the tile interior
-    for (int j = threadIdx.x; j < kTile * kTile * kTile / 2; j += blockDim.x) {
-        const int i = j % (kTile / 2), t = j / (kTile / 2);
-        const int b = 5 + t % kTile, c = 5 + t / kTile;
-        const int a = 5 + 2 * i + ((b + c) & 1);  // red: (a + b + c + 1) even
-        const int x = ox + a, y = oy + b, z = oz + c;  // interior cells need no wrap
-        ured[((size_t)z * ny + y) * hx + (x >> 1)] = U[(c * W + b) * W + a];
-    }
-    // restriction of the tile's 64 coarse cells (black residual zero): the four
-    // z-planes of each coarse cell in parallel, then their weighted sum in order
-    T* P = U;  // the sweep window is free now
-    for (int j = threadIdx.x; j < 256; j += blockDim.x) {
-        const int cell = j & 63, c = j >> 6;
-        const int Xl = cell & 3, Yl = (cell >> 2) & 3, Zl = cell >> 4;
-        const T w0 = (T)0.125, w1 = (T)0.375;
-        T accb = 0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const T* row = R + ((2 * Zl + c) * RW + (2 * Yl + b)) * RW;  // fine y = 2Yl - 1 + b, +1 window shift
-            const int p = (b + c) & 1;  // parity of the fine row: red cells at x = 2X - 1, 2X + 1 when 1
-            const T ra = row[2 * Xl], rb = row[2 * Xl + 1], rc = row[2 * Xl + 2], rd = row[2 * Xl + 3];
-            accb += (b == 0 || b == 3 ? w0 : w1) * restrict_row(w0, w1, p, p ? ra : (T)0, p ? rc : rb, p ? (T)0 : rd);
-        }
-        P[j] = accb;
-    }
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        const int cell = threadIdx.x;
-        const int Xl = cell & 3, Yl = (cell >> 2) & 3, Zl = cell >> 4;
-        const T w0 = (T)0.125, w1 = (T)0.375;
-        T acc = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc += (c == 0 || c == 3 ? w0 : w1) * P[c * 64 + cell];
-        const int X = X0 + Xl, Y = Y0 + Yl, Z = Z0 + Zl;
-        const size_t j = ((size_t)Z * cy + Y) * (cx >> 1) + (X >> 1);
-        if ((X + Y + Z) & 1) {
-            cf1[j] = acc;
-        } else {
-            cf0[j] = acc;
-            cu0[j] = acc * inv_diag_c;
-        }
-    }
-    (void)cz;
-}
-
-// Correction of the red cells from the coarse level (split), then
-// post-smoothing (black, red, black, red); writes the tile's final u0 and u1.
-template <typename T>
-__global__ void __launch_bounds__(kFinBlock) k_up(const T* __restrict__ cu0, const T* __restrict__ cu1,
-                                               const T* __restrict__ ured, const T* __restrict__ f0,
-                                               const T* __restrict__ f1, T* __restrict__ u0, T* __restrict__ u1,
-                                               int nx, int ny, int nz, T s, T inv_diag, const Scalars* sc) {
-    if (sc && sc->done) return;
-    constexpr int W = kUpW, CW = kUpCW;
-    extern __shared__ __align__(16) unsigned char smem[];
-    T* U = reinterpret_cast<T*>(smem);
-    T* F = U + W * W * W;
-    T* C = F + W * W * W;
-    const int hx = nx >> 1, cx = nx >> 1, cy = ny >> 1, cz = nz >> 1;
-    const int tx = cx / 4, ty = cy / 4;
-    const unsigned tile = xcd_block(blockIdx.x, gridDim.x);
-    const int X0 = 4 * (int)(tile % tx), Y0 = 4 * (int)((tile / tx) % ty), Z0 = 4 * (int)(tile / (tx * ty));
-    const int ox = 2 * X0 - 4, oy = 2 * Y0 - 4, oz = 2 * Z0 - 4;  // window origin (fine)
-    const int cox = X0 - 3, coy = Y0 - 3, coz = Z0 - 3;          // coarse window origin
-    for (int j = threadIdx.x; j < CW * CW * CW; j += blockDim.x) {
-        const int a = j % CW, b = (j / CW) % CW, c = j / (CW * CW);
-        C[j] = coarse_at(cu0, cu1, 0, wrapi(cox + a, cx), wrapi(coy + b, cy), wrapi(coz + c, cz), cx, cy);
-    }
-    __syncthreads();
-    for (int j = threadIdx.x; j < W * W * W; j += blockDim.x) {
-        const int a = j % W, b = (j / W) % W, c = j / (W * W);
-        const int xu = ox + a, yu = oy + b, zu = oz + c;  // unwrapped fine coordinates
-        const int x = wrapi(xu, nx), y = wrapi(yu, ny), z = wrapi(zu, nz);
-        const size_t k = ((size_t)z * ny + y) * hx + (x >> 1);
-        const int col = (x + y + z) & 1;
-        F[j] = col ? f1[k] : f0[k];
-        if (col) {
-            U[j] = (T)0;
-        } else {
-            // trilinear weights 3/4 (own coarse cell) and 1/4 (the neighbour on the cell's side)
-            const int I0 = (xu >> 1) - cox, I1 = (xu & 1) ? I0 + 1 : I0 - 1;
-            const int J0 = (yu >> 1) - coy, J1 = (yu & 1) ? J0 + 1 : J0 - 1;
-            const int K0 = (zu >> 1) - coz, K1 = (zu & 1) ? K0 + 1 : K0 - 1;
-            const T* c00 = C + (K0 * CW + J0) * CW;
-            const T* c10 = C + (K0 * CW + J1) * CW;
-            const T* c01 = C + (K1 * CW + J0) * CW;
-            const T* c11 = C + (K1 * CW + J1) * CW;
-            U[j] = tri_add(ured[k], c00[I0], c00[I1], c10[I0], c10[I1], c01[I0], c01[I1], c11[I0], c11[I1]);
-        }
-    }
-    __syncthreads();
-    // window colour parity: the origin offsets are even
-    win_sweep<T, W>(U, F, 1, W - 1, 1, 0, s, inv_diag);
-    win_sweep<T, W>(U, F, 2, W - 2, 0, 0, s, inv_diag);
-    win_sweep<T, W>(U, F, 3, W - 3, 1, 0, s, inv_diag);
-    win_sweep<T, W>(U, F, 4, W - 4, 0, 0, s, inv_diag);
-    for (int j = threadIdx.x; j < kTile * kTile * kTile; j += blockDim.x) {
-        const int a = 4 + j % kTile, b = 4 + (j / kTile) % kTile, c = 4 + j / (kTile * kTile);
-        const int x = ox + a, y = oy + b, z = oz + c;
-        const size_t k = ((size_t)z * ny + y) * hx + (x >> 1);
-        const T v = U[(c * W + b) * W + a];
-        if ((x + y + z) & 1) u1[k] = v;
-        else u0[k] = v;
-    }
-}
-
-template <typename T>
-void launch_down(hipStream_t st, const T* u0, const T* f0, const T* f1, T* ured, int nx, int ny, int nz, double s,
-                 double diag, T* cf0, T* cf1, T* cu0, double inv_diag_c, const Scalars* sc) {
-    const unsigned nt = (unsigned)(nx / 8) * (ny / 8) * (nz / 8);
-    const unsigned bs = nt <= 512 ? kFinBlock : kBlock;  // few tiles: more threads per tile
-    hipLaunchKernelGGL(k_down<T>, dim3(nt), dim3(bs), down_lds_bytes(sizeof(T)), st, u0, f0, f1, ured, nx, ny, nz,
-                       (T)s, (T)(1.0 / diag), (T)diag, cf0, cf1, cu0, (T)inv_diag_c, sc);
-}
-
-template <typename T>
-void launch_up(hipStream_t st, const T* cu0, const T* cu1, const T* ured, const T* f0, const T* f1, T* u0, T* u1,
-               int nx, int ny, int nz, double s, double diag, const Scalars* sc) {
-    const unsigned nt = (unsigned)(nx / 8) * (ny / 8) * (nz / 8);
-    const unsigned bs = nt <= 512 ? kFinBlock : kBlock;  // few tiles: more threads per tile
-    hipLaunchKernelGGL(k_up<T>, dim3(nt), dim3(bs), up_lds_bytes(sizeof(T)), st, cu0, cu1, ured, f0, f1, u0, u1,
-                       nx, ny, nz, (T)s, (T)(1.0 / diag), sc);
-}
-
-template <typename T>
-hipError_t blocked_set_lds() {
-    hipError_t e = hipFuncSetAttribute((const void*)k_down<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)down_lds_bytes(sizeof(T)));
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute((const void*)k_up<T>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)up_lds_bytes(sizeof(T)));
-}
-
-// ---------------------------------------------------------------------------
 // Batched forms: one launch covers one level of every instance in the table
 // (the same bodies as the solo kernels, so results are bitwise the same).
 template <typename T>
@@ -1033,11 +818,6 @@ void launchb_mg(hipStream_t st, int what, const InstDev* inst, const int* gate, 
                                     int);                                                                           \
     template unsigned launch_gs_dots<T>(hipStream_t, T*, const T*, const T*, int, int, int, double, double,         \
                                         const double*, const double*, double*, const Scalars*, int);                \
-    template void launch_down<T>(hipStream_t, const T*, const T*, const T*, T*, int, int, int, double, double, T*, T*, \
-                                 T*, double, const Scalars*);                                                      \
-    template void launch_up<T>(hipStream_t, const T*, const T*, const T*, const T*, const T*, T*, T*, int, int, int,  \
-                               double, double, const Scalars*);                                                    \
-    template hipError_t blocked_set_lds<T>();                                                                      \
     template void launchb_mg<T>(hipStream_t, int, const InstDev*, const int*, const BatchTab*, unsigned, int, int,   \
                                 unsigned);                                                                         
 

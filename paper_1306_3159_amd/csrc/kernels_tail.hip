@@ -187,9 +187,9 @@ __device__ __forceinline__ T tail_restrict(const T* R, int X, int Y, int Z, int 
                 if (p ? X == 0 : X + 1 == hx) e = (T)0;
                 if (p ? X + 1 == hx : X == 0) wm = (T)0.25;  // the boundary fine cell of a boundary coarse cell
             }
-            accb += wy * (p ? w0 * e + wm * m : wm * m + w0 * e);
+            accb = fma(wy, restrict_row(w0, wm, p, e, m, e), accb);
         }
-        acc += wz * accb;
+        acc = fma(wz, accb, acc);
     }
     return acc;
 }
@@ -264,7 +264,7 @@ __device__ __forceinline__ void tail_run(const T* __restrict__ f0g, const T* __r
         for (int k = 0; k < K; ++k) {
             const int j = tid + k * kTailThreads;
             if (j < nh0) {
-                u0[k] = (f0[k] + c0.s * tail_sum(A1, u1[k], cell[k].xr(), cell[k])) * c0.inv(cell[k].fr());
+                u0[k] = relax(f0[k], c0.s, tail_sum(A1, u1[k], cell[k].xr(), cell[k]), c0.inv(cell[k].fr()));
                 A0[j] = u0[k];
             }
         }
@@ -275,7 +275,7 @@ __device__ __forceinline__ void tail_run(const T* __restrict__ f0g, const T* __r
         for (int k = 0; k < K; ++k) {
             const int j = tid + k * kTailThreads;
             if (j < nh0) {
-                u1[k] = (f1[k] + c0.s * tail_sum(A0, u0[k], cell[k].xb(), cell[k])) * c0.inv(cell[k].fb());
+                u1[k] = relax(f1[k], c0.s, tail_sum(A0, u0[k], cell[k].xb(), cell[k]), c0.inv(cell[k].fb()));
                 A1[j] = u1[k];
             }
         }
@@ -285,7 +285,7 @@ __device__ __forceinline__ void tail_run(const T* __restrict__ f0g, const T* __r
     for (int k = 0; k < K; ++k) {
         const int j = tid + k * kTailThreads;
         if (j < nh0) {
-            u0[k] = f0[k] * c0.inv(cell[k].fr());  // red sweep from zero
+            u0[k] = relax_zero(f0[k], c0.inv(cell[k].fr()));  // red sweep from zero
             A0[j] = u0[k];
         }
     }
@@ -298,7 +298,7 @@ __device__ __forceinline__ void tail_run(const T* __restrict__ f0g, const T* __r
     for (int k = 0; k < K; ++k) {
         const int j = tid + k * kTailThreads;
         if (j < nh0)
-            A0[j] = f0[k] - (c0.dg(cell[k].fr()) * u0[k] - c0.s * tail_sum(A1, u1[k], cell[k].xr(), cell[k]));
+            A0[j] = red_resid(f0[k], c0.dg(cell[k].fr()), u0[k], c0.s, tail_sum(A1, u1[k], cell[k].xr(), cell[k]));
     }
     __syncthreads();
     // lower levels, down: u0 | 0 | u1 | 0 | f0 | f1 | r of the level, then its values in natural order
@@ -338,17 +338,17 @@ __device__ __forceinline__ void tail_run(const T* __restrict__ f0g, const T* __r
             ce = tail_cell<T, BOX>(i, t % ny, t / ny, hx, ny, nz, nh);
             fa = F0[tid];
             fb = F1[tid];
-            a = fa * c.inv(ce.fr());
+            a = relax_zero(fa, c.inv(ce.fr()));
             B0[tid] = a;
         }
         __syncthreads();
-        if (on) B1[tid] = b = (fb + c.s * tail_sum(B0, a, ce.xb(), ce)) * c.inv(ce.fb());
+        if (on) B1[tid] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
         __syncthreads();
-        if (on) B0[tid] = a = (fa + c.s * tail_sum(B1, b, ce.xr(), ce)) * c.inv(ce.fr());
+        if (on) B0[tid] = a = relax(fa, c.s, tail_sum(B1, b, ce.xr(), ce), c.inv(ce.fr()));
         __syncthreads();
-        if (on) B1[tid] = b = (fb + c.s * tail_sum(B0, a, ce.xb(), ce)) * c.inv(ce.fb());
+        if (on) B1[tid] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
         __syncthreads();
-        if (on) RR[tid] = fa - (c.dg(ce.fr()) * a - c.s * tail_sum(B1, b, ce.xr(), ce));
+        if (on) RR[tid] = red_resid(fa, c.dg(ce.fr()), a, c.s, tail_sum(B1, b, ce.xr(), ce));
         __syncthreads();
         R = RR;
         fhx = hx;
@@ -390,14 +390,14 @@ __device__ __forceinline__ void tail_run(const T* __restrict__ f0g, const T* __r
             B0[tid] = a;
         }
         __syncthreads();
-        if (on) B1[tid] = b = (fb + c.s * tail_sum(B0, a, ce.xb(), ce)) * c.inv(ce.fb());
+        if (on) B1[tid] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
         __syncthreads();
-        if (on) B0[tid] = a = (fa + c.s * tail_sum(B1, b, ce.xr(), ce)) * c.inv(ce.fr());
+        if (on) B0[tid] = a = relax(fa, c.s, tail_sum(B1, b, ce.xr(), ce), c.inv(ce.fr()));
         __syncthreads();
-        if (on) B1[tid] = b = (fb + c.s * tail_sum(B0, a, ce.xb(), ce)) * c.inv(ce.fb());
+        if (on) B1[tid] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
         __syncthreads();
         if (on) {
-            a = (fa + c.s * tail_sum(B1, b, ce.xr(), ce)) * c.inv(ce.fr());
+            a = relax(fa, c.s, tail_sum(B1, b, ce.xr(), ce), c.inv(ce.fr()));
             const int row = (z * ny + y) * nx, up = (y + z) & 1;
             N[row + 2 * i + up] = a;
             N[row + 2 * i + (up ^ 1)] = b;
@@ -422,7 +422,7 @@ __device__ __forceinline__ void tail_run(const T* __restrict__ f0g, const T* __r
     for (int k = 0; k < K; ++k) {
         const int j = tid + k * kTailThreads;
         if (j < nh0) {
-            u0g[j] = (f0[k] + c0.s * tail_sum(A1, u1[k], cell[k].xr(), cell[k])) * c0.inv(cell[k].fr());
+            u0g[j] = relax(f0[k], c0.s, tail_sum(A1, u1[k], cell[k].xr(), cell[k]), c0.inv(cell[k].fr()));
             u1g[j] = u1[k];
         }
     }

@@ -158,16 +158,22 @@ template <typename T>
 void launchb_tail(hipStream_t st, const InstDev* inst, const int* gate, int ninst, unsigned lds);
 template <typename T>
 hipError_t tail_set_lds(size_t bytes);
-// temporally blocked level (nx, ny, nz divisible by 8): pre-smoothing + red residual +
-// restriction (pre-smoothed red to ured); red correction + post-smoothing from ured
+// A level in two launches (kernels_level.hip): pre-smoothing from a zero guess, red
+// residual and restriction (pre-smoothed red to ured; cu0 may be null), and red correction and
+// post-smoothing from ured (sweeps = 3: without the closing red sweep, only black written;
+// periodic only)
+LevelTile level_tile(int nx, int ny, int nz, size_t esz);
 template <typename T>
-void launch_down(hipStream_t st, const T* u0, const T* f0, const T* f1, T* ured, int nx, int ny, int nz, double s,
-                 double diag, T* cf0, T* cf1, T* cu0, double inv_diag_c, const Scalars* sc);
+LevelCoef<T> level_coef(double s, double alpha, double s_coarse, bool box);
 template <typename T>
-void launch_up(hipStream_t st, const T* cu0, const T* cu1, const T* ured, const T* f0, const T* f1, T* u0, T* u1,
-               int nx, int ny, int nz, double s, double diag, const Scalars* sc);
+void launch_level_down(hipStream_t st, const LevelTile& g, bool box, const T* f0, const T* f1, T* ured, int nx, int ny,
+                       int nz, const LevelCoef<T>& c, T* cf0, T* cf1, T* cu0, const Scalars* sc);
 template <typename T>
-hipError_t blocked_set_lds();
+void launch_level_up(hipStream_t st, const LevelTile& g, bool box, int sweeps, const T* cu0, const T* cu1,
+                     const T* ured, const T* f0, const T* f1, T* u0, T* u1, int nx, int ny, int nz,
+                     const LevelCoef<T>& c, const Scalars* sc);
+template <typename T>
+hipError_t level_set_lds();
 
 // ---- batched launches (one launch per step for every instance of a batch) ----
 enum { BCG_DIR = 0, BCG_APPLY, BCG_UPDATE, BCG_FIN_ALPHA, BCG_FIN_UPDATE, BCG_FIN_BETA };
