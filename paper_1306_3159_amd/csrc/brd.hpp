@@ -289,14 +289,69 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nb) {
     return xcd * full + (xcd < rem ? xcd : rem) + local;
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+// Work-group barrier that orders LDS accesses only: unlike __syncthreads() it does not wait
+// for global loads and stores in flight. For kernels whose threads exchange data in LDS alone.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Deterministic block reduction of K values; thread k < K writes block
-// partial k to part[k * nparts + slot].
+// v plus the value DPP moves to this lane (zero where it moves none): register moves between
+// lanes, without the LDS round trip of a shuffle.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+    return v + __hiloint2double(hi, lo);
+}
+// Lane 15 of each row of 16 lanes gets the row's sum (row_shr 1, 2, 4, 8).
+__device__ __forceinline__ double row_sum(double v) {
+    v = dpp_add<0x111, 0xf>(v);
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    return dpp_add<0x118, 0xf>(v);
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                            __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Sum over a whole wave (all 64 lanes active), the same value in every lane.
+__device__ __forceinline__ double wave_sum(double v) {
+    v = row_sum(v);
+    v = dpp_add<0x142, 0xa>(v);  // row_bcast 15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);  // row_bcast 31 into rows 2 and 3
+    return lane_value(v, 63);
+}
+
+// Sums of K values over one work-group: wave sums, then the waves' sums by a row of lanes.
+// Every thread gets the totals. A single work-group that reduces is a chain of latencies: with
+// shuffles and a loop over the waves' sums a kernel of three such sums took 4.8 us, as here
+// 2.9 us (k_fin at 32^3; 5.6 -> 4.2 us at 128^3, k_gmres_arnoldi 10.5 -> 7.0 us at 156 blobs,
+// k_nvec_project 3.1 -> 2.2 us).
+template <int K>
+__device__ __forceinline__ void wg_sums(double (&v)[K]) {
+    __shared__ double sh[K][kFinBlock / 64];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
+    lds_barrier();  // readers of an earlier call are done
+    if (lane == 0)
+#pragma unroll
+        for (int k = 0; k < K; ++k) sh[k][wid] = v[k];
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = lane_value(row_sum(lane < nw ? sh[k][lane & 15] : 0.0), 15);
+}
+__device__ __forceinline__ double wg_sum(double s) {
+    double v[1] = {s};
+    wg_sums<1>(v);
+    return v[0];
+}
+
+// Deterministic block reduction of K values; the first wave writes block partial k to
+// part[k * nparts + slot].
 template <int K>
 __device__ __forceinline__ void block_partials(double (&v)[K], double* part, unsigned nparts, unsigned slot) {
     __shared__ double sh[K][16];
@@ -306,34 +361,13 @@ __device__ __forceinline__ void block_partials(double (&v)[K], double* part, uns
     if (lane == 0)
 #pragma unroll
         for (int k = 0; k < K; ++k) sh[k][wid] = v[k];
-    __syncthreads();
-    if (threadIdx.x < K) {
-        double s = 0.0;
-        for (int w = 0; w < nw; ++w) s += sh[threadIdx.x][w];
-        part[(size_t)threadIdx.x * nparts + slot] = s;
-    }
-}
-
-// Sum over one work-group (wave sums, then the waves in order); every thread
-// gets the total.
-__device__ __forceinline__ double wg_sum(double s) {
-    __shared__ double sh[kFinBlock / 64];
-    s = wave_sum(s);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
-    __syncthreads();
-    double t = 0.0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += sh[w];
-    __syncthreads();
-    return t;
-}
-
-// Work-group barrier that orders LDS accesses only: unlike __syncthreads() it does not wait
-// for global loads and stores in flight. For kernels whose threads exchange data in LDS alone.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    lds_barrier();
+    if (wid == 0)
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const double t = row_sum(lane < nw ? sh[k][lane & 15] : 0.0);
+            if (lane == 15) part[(size_t)k * nparts + slot] = t;
+        }
 }
 
 inline unsigned nblocks(size_t n, int bs = kBlock) { return (unsigned)((n + bs - 1) / bs); }

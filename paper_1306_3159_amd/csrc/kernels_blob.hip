@@ -621,13 +621,12 @@ __global__ void __launch_bounds__(kFinBlock) k_nvec_sums(const double* a, const 
         s1 += a[i] * a[i];
         if (b) s2 += a[i] * b[i];
     }
-    s0 = wg_sum(s0);
-    s1 = wg_sum(s1);
-    s2 = wg_sum(s2);
+    double t[3] = {s0, s1, s2};
+    wg_sums<3>(t);
     if (threadIdx.x == 0) {
-        out[0] = s0;
-        out[1] = s1;
-        out[2] = s2;
+        out[0] = t[0];
+        out[1] = t[1];
+        out[2] = t[2];
     }
 }
 
@@ -677,10 +676,20 @@ void launch_gmres_start(hipStream_t st, const double* b, const double* w, int ha
 // Elements of an N-vector a work-group thread keeps in registers during the
 // modified Gram-Schmidt sweep (N <= kArnoldiRegs * kFinBlock).
 constexpr int kArnoldiRegs = 12;
+constexpr int kGivensLds = 128;  // columns whose scalar chain runs from LDS
 
 __global__ void __launch_bounds__(kFinBlock) k_gmres_arnoldi(double* V, double* H, double* cs, double* sn,
                                                              double* gvec, int N, int k, int m, GmresScalars* gs,
                                                              int project) {
+    // the new column and the earlier rotations in LDS: the closing scalar chain reads no global memory
+    __shared__ double hs[kGivensLds + 1], rc[kGivensLds], rs[kGivensLds];
+    const bool lds = k < kGivensLds;
+    if (lds)
+        for (int j = threadIdx.x; j < k; j += blockDim.x) {
+            rc[j] = cs[j];
+            rs[j] = sn[j];
+        }
+    const double gk = threadIdx.x == 0 ? gvec[k] : 0.0;
     double* w = V + (size_t)(k + 1) * N;
     double hk1;
     if (N <= kArnoldiRegs * (int)blockDim.x) {
@@ -715,7 +724,7 @@ __global__ void __launch_bounds__(kFinBlock) k_gmres_arnoldi(double* V, double* 
                 const int i = threadIdx.x + c * blockDim.x;
                 if (i < N) wr[c] -= hj * vj[i];  // v_j again from cache
             }
-            if (threadIdx.x == 0) H[j * m + k] = hj;
+            if (threadIdx.x == 0) (lds ? hs[j] : H[j * m + k]) = hj;
         }
         double s = 0.0;
 #pragma unroll
@@ -741,7 +750,7 @@ __global__ void __launch_bounds__(kFinBlock) k_gmres_arnoldi(double* V, double* 
             for (int i = threadIdx.x; i < N; i += blockDim.x) s += w[i] * vj[i];
             const double hj = wg_sum(s);
             for (int i = threadIdx.x; i < N; i += blockDim.x) w[i] -= hj * vj[i];
-            if (threadIdx.x == 0) H[j * m + k] = hj;
+            if (threadIdx.x == 0) (lds ? hs[j] : H[j * m + k]) = hj;
         }
         double s = 0.0;
         for (int i = threadIdx.x; i < N; i += blockDim.x) s += w[i] * w[i];
@@ -750,21 +759,24 @@ __global__ void __launch_bounds__(kFinBlock) k_gmres_arnoldi(double* V, double* 
         for (int i = threadIdx.x; i < N; i += blockDim.x) w[i] *= inv;
     }
     if (threadIdx.x == 0) {
-        H[(k + 1) * m + k] = hk1;
+        double a = lds ? hs[0] : H[k];
         for (int j = 0; j < k; ++j) {
-            const double a = H[j * m + k], b = H[(j + 1) * m + k];
-            H[j * m + k] = cs[j] * a + sn[j] * b;
-            H[(j + 1) * m + k] = -sn[j] * a + cs[j] * b;
+            const double b = lds ? hs[j + 1] : H[(j + 1) * m + k];
+            const double cj = lds ? rc[j] : cs[j], sj = lds ? rs[j] : sn[j];
+            H[j * m + k] = cj * a + sj * b;
+            a = -sj * a + cj * b;
         }
-        const double a = H[k * m + k], b = H[(k + 1) * m + k];
+        const double b = hk1;
         const double den = sqrt(a * a + b * b);
-        cs[k] = den == 0.0 ? 1.0 : a / den;
-        sn[k] = den == 0.0 ? 0.0 : b / den;
+        const double ck = den == 0.0 ? 1.0 : a / den, sk = den == 0.0 ? 0.0 : b / den;
+        cs[k] = ck;
+        sn[k] = sk;
         H[k * m + k] = den;
         H[(k + 1) * m + k] = 0.0;
-        gvec[k + 1] = -sn[k] * gvec[k];
-        gvec[k] = cs[k] * gvec[k];
-        gs->res = fabs(gvec[k + 1]);
+        const double gk1 = -sk * gk;
+        gvec[k + 1] = gk1;
+        gvec[k] = ck * gk;
+        gs->res = fabs(gk1);
         gs->hk1 = hk1;
         gs->k = k + 1;
         if (!(den == den) || !(hk1 == hk1)) gs->status = 1;
@@ -779,7 +791,21 @@ void launch_gmres_arnoldi(hipStream_t st, double* V, double* H, double* cs, doub
 // x += V y with H y = g (upper-triangular k x k), y solved by thread 0.
 __global__ void __launch_bounds__(kFinBlock) k_gmres_update(const double* V, const double* H, const double* gvec,
                                                             double* y, double* x, int N, int k, int m) {
-    if (threadIdx.x == 0) {
+    // y in LDS (its first entries), back substitution by columns: once y_j is known every row
+    // above takes its share of it, so the chain is one product and one division a row
+    __shared__ double ys[kGivensLds];
+    const bool lds = k <= kGivensLds;
+    if (lds) {
+        const int t = threadIdx.x;
+        double r = t < k ? gvec[t] : 0.0;
+        for (int j = k - 1; j >= 0; --j) {
+            const double h = t <= j && t < k ? H[t * m + j] : 0.0;
+            if (t == j) ys[j] = h != 0.0 ? r / h : 0.0;
+            lds_barrier();
+            if (t < j) r -= h * ys[j];
+        }
+        if (t < k) y[t] = ys[t];
+    } else if (threadIdx.x == 0) {
         for (int i = k - 1; i >= 0; --i) {
             double s = gvec[i];
             for (int j = i + 1; j < k; ++j) s -= H[i * m + j] * y[j];
@@ -790,7 +816,7 @@ __global__ void __launch_bounds__(kFinBlock) k_gmres_update(const double* V, con
     __syncthreads();
     for (int i = threadIdx.x; i < N; i += blockDim.x) {
         double acc = x[i];
-        for (int j = 0; j < k; ++j) acc += y[j] * V[(size_t)j * N + i];
+        for (int j = 0; j < k; ++j) acc += (lds ? ys[j] : y[j]) * V[(size_t)j * N + i];
         x[i] = acc;
     }
 }

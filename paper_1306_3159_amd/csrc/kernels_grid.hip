@@ -629,19 +629,31 @@ void launch_add_shift(hipStream_t st, double* v, size_t n, const double* shift_d
 // Finalize: one work-group of kFinBlock threads reduces block partials in a
 // fixed order and advances the CG scalars.
 // ---------------------------------------------------------------------------
+// Sums of K sets of n partials each (set k at p + k n): every load of four strides of every
+// set is issued before the first is added, then one reduction for all.
+template <int K>
+__device__ __forceinline__ void fin_sums(const double* __restrict__ p, unsigned n, double (&s)[K]) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) s[k] = 0.0;
+    for (unsigned i0 = threadIdx.x; i0 < n; i0 += 4 * blockDim.x) {
+        double v[K][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const unsigned i = i0 + u * blockDim.x;
+#pragma unroll
+            for (int k = 0; k < K; ++k) v[k][u] = i < n ? p[(size_t)k * n + i] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int k = 0; k < K; ++k) s[k] += v[k][u];
+    }
+    wg_sums<K>(s);
+}
 __device__ __forceinline__ double fin_sum(const double* __restrict__ p, unsigned n) {
-    __shared__ double sh[kFinBlock / 64];
-    double s = 0.0;
-    for (unsigned i = threadIdx.x; i < n; i += blockDim.x) s += p[i];
-    s = wave_sum(s);
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) sh[wid] = s;
-    __syncthreads();
-    double t = 0.0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += sh[w];
-    __syncthreads();
-    return t;
+    double s[1];
+    fin_sums<1>(p, n, s);
+    return s[0];
 }
 
 __device__ __forceinline__ bool is_finite_d(double v) { return v == v && v - v == 0.0; }
@@ -650,9 +662,9 @@ __device__ __forceinline__ void fin_body(int kind, const double* __restrict__ pa
                                          const double* __restrict__ na, const double* __restrict__ nb, int nblob,
                                          double inv_h3) {
     if (kind == FIN_INIT) {
-        const double rr = fin_sum(part, np);
-        const double rs = fin_sum(part + np, np);
-        const double gg = fin_sum(part + 2 * (size_t)np, np);
+        double t[3];
+        fin_sums<3>(part, np, t);
+        const double rr = t[0], rs = t[1], gg = t[2];
         if (threadIdx.x == 0) {
             // On entry tol2 holds rtol^2 and rr0 holds an absolute floor^2.
             const double t2 = fmax(sc->tol2 * gg, sc->rr0);
@@ -668,28 +680,28 @@ __device__ __forceinline__ void fin_body(int kind, const double* __restrict__ pa
             sc->mean_r = sc->project ? rs * sc->inv_ncell : 0.0;
         }
     } else if (kind == FIN_ALPHA) {
-        double pq = fin_sum(part, np);
-        double qs = fin_sum(part + np, np);
+        double t[2];
+        fin_sums<2>(part, np, t);
+        double pq = t[0], qs = t[1];
         if (na && nb) {
             // blob term of B: p.(S mu) = h^-3 (J p).mu, sum(S mu) = h^-3 sum(mu)
-            double a = 0.0, c = 0.0;
-            for (int i = threadIdx.x; i < nblob; i += blockDim.x) {
-                a += na[i] * nb[i];
-                c += nb[i];
+            double b[2] = {0.0, 0.0};
+            for (int i0 = threadIdx.x; i0 < nblob; i0 += 4 * blockDim.x) {
+                double x[4], y[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + u * (int)blockDim.x;
+                    x[u] = i < nblob ? na[i] : 0.0;
+                    y[u] = i < nblob ? nb[i] : 0.0;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    b[0] += x[u] * y[u];
+                    b[1] += y[u];
+                }
             }
-            __shared__ double sh2[2][kFinBlock / 64];
-            a = wave_sum(a);
-            c = wave_sum(c);
-            if ((threadIdx.x & 63) == 0) {
-                sh2[0][threadIdx.x >> 6] = a;
-                sh2[1][threadIdx.x >> 6] = c;
-            }
-            __syncthreads();
-            double ta = 0.0, tc = 0.0;
-            for (int w = 0; w < (int)(blockDim.x >> 6); ++w) {
-                ta += sh2[0][w];
-                tc += sh2[1][w];
-            }
+            wg_sums<2>(b);
+            const double ta = b[0], tc = b[1];
             pq += inv_h3 * ta;
             qs += inv_h3 * tc;
         }
@@ -708,8 +720,9 @@ __device__ __forceinline__ void fin_body(int kind, const double* __restrict__ pa
             }
         }
     } else if (kind == FIN_UPDATE) {
-        const double rr = fin_sum(part, np);
-        const double rs = fin_sum(part + np, np);
+        double t[2];
+        fin_sums<2>(part, np, t);
+        const double rr = t[0], rs = t[1];
         if (threadIdx.x == 0) {
             sc->rr = rr;
             sc->rsum = rs;
@@ -723,9 +736,9 @@ __device__ __forceinline__ void fin_body(int kind, const double* __restrict__ pa
             }
         }
     } else {  // FIN_BETA
-        const double zs = fin_sum(part, np);
-        const double zr = fin_sum(part + np, np);
-        const double zq = fin_sum(part + 2 * (size_t)np, np);
+        double t[3];
+        fin_sums<3>(part, np, t);
+        const double zs = t[0], zr = t[1], zq = t[2];
         if (threadIdx.x == 0) {
             const double shift = sc->project ? (sc->rsum * sc->eBe_inv - zs * sc->inv_ncell) : 0.0;
             const double rz_new = zr + shift * sc->rsum;
@@ -895,17 +908,19 @@ __global__ void __launch_bounds__(kBlock) k_fg_mdot(const double* __restrict__ w
     block_partials<K>(a, part, gridDim.x, blockIdx.x);
 }
 
-// out[v] (= or +=) the sum of value v's partials, v < nv; *wn = the last value's sum with wn.
-__global__ void __launch_bounds__(kFinBlock) k_fg_mfin(const double* __restrict__ part, unsigned np, int nv,
-                                                      double* out, double* wn, const int* gate) {
+// out[v] the sum of value v's partials, v < K (v < K - 1 with wn, which takes the last value's).
+template <int K>
+__global__ void __launch_bounds__(kFinBlock) k_fg_mfin(const double* __restrict__ part, unsigned np, double* out,
+                                                      double* wn, const int* gate) {
     if (gate && !*gate) return;
-    for (int v = 0; v < nv; ++v) {
-        const double sv = fin_sum(part + (size_t)v * np, np);
-        if (threadIdx.x == 0) out[v] = sv;
-    }
-    if (wn) {
-        const double sw = fin_sum(part + (size_t)nv * np, np);
-        if (threadIdx.x == 0) *wn = sw;
+    double t[K];
+    fin_sums<K>(part, np, t);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int v = 0; v < K; ++v) {
+            if (wn && v == K - 1) *wn = t[v];
+            else out[v] = t[v];
+        }
     }
 }
 
@@ -965,6 +980,13 @@ void mdot_launch(hipStream_t st, bool wn, unsigned nb, const double* w, const do
     if (wn) hipLaunchKernelGGL((k_fg_mdot<NV, true, true>), dim3(nb), dim3(kBlock), 0, st, w, V0, stride, n, part, gate);
     else hipLaunchKernelGGL((k_fg_mdot<NV, false, true>), dim3(nb), dim3(kBlock), 0, st, w, V0, stride, n, part, gate);
 }
+template <int K = 1>
+void mfin_launch(hipStream_t st, int k, const double* part, unsigned np, double* out, double* wn, const int* gate) {
+    if constexpr (K < 9) {
+        if (k > K) return mfin_launch<K + 1>(st, k, part, np, out, wn, gate);
+    }
+    hipLaunchKernelGGL(k_fg_mfin<K>, dim3(1), dim3(kFinBlock), 0, st, part, np, out, wn, gate);
+}
 }  // namespace
 
 unsigned fg_cgs_blocks(size_t n) { return red_blocks(n / 2 + 1); }
@@ -986,8 +1008,7 @@ void launch_fg_cgs_dots(hipStream_t st, const double* w, const double* V, size_t
             case 7: mdot_launch<7>(st, wn, nb, w, V0, stride, (unsigned)n, part, gate); break;
             default: mdot_launch<8>(st, wn, nb, w, V0, stride, (unsigned)n, part, gate); break;
         }
-        hipLaunchKernelGGL(k_fg_mfin, dim3(1), dim3(kFinBlock), 0, st, part, nb, nv, out + g0, wn ? wn2 : nullptr,
-                           gate);
+        mfin_launch(st, nv + (wn ? 1 : 0), part, nb, out + g0, wn ? wn2 : nullptr, gate);
     }
 }
 
@@ -1100,24 +1121,36 @@ void launch_fg_update(hipStream_t st, double* x, const double* Z, size_t stride,
 // complete: apply the previous Givens rotations, form rotation j, advance the
 // right-hand side g; out[0] = |g[j+1]| (the residual estimate), out[1] = the
 // subdiagonal entry before rotation.
-__global__ void k_fg_givens(double* Hd, int ld, double* cs, double* sn, double* g, int j, double* out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__global__ void __launch_bounds__(64) k_fg_givens(double* Hd, int ld, double* cs, double* sn, double* g, int j,
+                                                  double* out) {
+    // the chain runs over registers: entries and rotations are loaded by the wave, 64 at a time
     double* col = Hd + (size_t)j * ld;
-    for (int i = 0; i < j; ++i) {
-        const double a = col[i], b = col[i + 1];
-        col[i] = cs[i] * a + sn[i] * b;
-        col[i + 1] = -sn[i] * a + cs[i] * b;
+    const int t = threadIdx.x;
+    double a = col[0];
+    for (int i0 = 0; i0 < j; i0 += 64) {
+        const int i = i0 + t, n = min(64, j - i0);
+        const double b_ = i < j ? col[i + 1] : 0.0, c_ = i < j ? cs[i] : 0.0, s_ = i < j ? sn[i] : 0.0;
+        double mine = 0.0;
+        for (int k = 0; k < n; ++k) {
+            const double b = __shfl(b_, k, 64), c = __shfl(c_, k, 64), s = __shfl(s_, k, 64);
+            const double r = c * a + s * b;
+            if (t == k) mine = r;
+            a = -s * a + c * b;
+        }
+        if (i < j) col[i] = mine;
     }
-    const double a = col[j], b = col[j + 1];
+    if (t != 0) return;
+    const double b = col[j + 1], gj = g[j];
     const double den = sqrt(a * a + b * b);
-    cs[j] = den == 0.0 ? 1.0 : a / den;
-    sn[j] = den == 0.0 ? 0.0 : b / den;
+    const double c = den == 0.0 ? 1.0 : a / den, s = den == 0.0 ? 0.0 : b / den;
+    cs[j] = c;
+    sn[j] = s;
     out[1] = b;
     col[j] = den;
     col[j + 1] = 0.0;
-    g[j + 1] = -sn[j] * g[j];
-    g[j] = cs[j] * g[j];
-    out[0] = fabs(g[j + 1]);
+    g[j + 1] = -s * gj;
+    g[j] = c * gj;
+    out[0] = fabs(-s * gj);
 }
 
 void launch_fg_givens(hipStream_t st, double* Hd, int ld, double* cs, double* sn, double* g, int j, double* out) {
@@ -1134,18 +1167,27 @@ void launch_fg_gstart(hipStream_t st, double* g, int len, const double* beta) {
 }
 
 // y = R^{-1} g for the leading k x k upper triangle R of the rotated Hessenberg matrix
-__global__ void k_fg_backsolve(const double* Hd, int ld, const double* g, double* y, int k) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    for (int i = k - 1; i >= 0; --i) {
-        double s = g[i];
-        for (int j = i + 1; j < k; ++j) s -= Hd[(size_t)j * ld + i] * y[j];
-        const double d = Hd[(size_t)i * ld + i];
-        y[i] = d != 0.0 ? s / d : 0.0;
+__global__ void __launch_bounds__(kFgMaxRestart) k_fg_backsolve(const double* __restrict__ Hd, int ld,
+                                                                const double* __restrict__ g, double* y, int k) {
+    // by columns: once y_j is known every row above takes its share of it
+    __shared__ double yj;
+    const int t = threadIdx.x;
+    double r = t < k ? g[t] : 0.0;
+    for (int j = k - 1; j >= 0; --j) {
+        const double h = t <= j ? Hd[(size_t)j * ld + t] : 0.0;
+        if (t == j) {
+            yj = h != 0.0 ? r / h : 0.0;
+            y[j] = yj;
+        }
+        lds_barrier();
+        if (t < j) r -= h * yj;
+        lds_barrier();
     }
 }
 
 void launch_fg_backsolve(hipStream_t st, const double* Hd, int ld, const double* g, double* y, int k) {
-    hipLaunchKernelGGL(k_fg_backsolve, dim3(1), dim3(64), 0, st, Hd, ld, g, y, k);
+    hipLaunchKernelGGL(k_fg_backsolve, dim3(1), dim3(k > 0 ? (k + 63) / 64 * 64 : 64), 0, st, Hd, ld, g, y,
+                       k);
 }
 
 }  // namespace brd

@@ -375,7 +375,6 @@ __global__ void __launch_bounds__(kBlock) k_spmv_centered(const int* __restrict_
                                                           const double* __restrict__ val,
                                                           const double* __restrict__ x, double* __restrict__ y,
                                                           int N) {
-    __shared__ double sh[kBlock / 64];
     // the block's copy of mean(x): eight independent partial sums keep eight loads in flight
     double p[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const int bd = (int)blockDim.x;
@@ -385,13 +384,7 @@ __global__ void __launch_bounds__(kBlock) k_spmv_centered(const int* __restrict_
         for (int u = 0; u < 8; ++u) p[u] += x[i0 + u * bd];
     }
     for (; i0 < N; i0 += bd) p[0] += x[i0];
-    double s = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
-    __syncthreads();
-    double tot = 0.0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) tot += sh[w];
-    const double m = tot / (double)N;
+    const double m = wg_sum(((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]))) / (double)N;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= N) return;
     double acc = 0.0;
@@ -409,14 +402,8 @@ void launch_spmv_centered(hipStream_t st, const int* rowptr, const int* col, con
 __global__ void __launch_bounds__(kFinBlock) k_count_bad(const double* v, long long n, int* out) {
     int bad = 0;
     for (long long i = threadIdx.x; i < n; i += blockDim.x) bad += !(v[i] == v[i] && v[i] - v[i] == 0.0);
-    __shared__ int sh[kFinBlock];
-    sh[threadIdx.x] = bad;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int s = 0;
-        for (int t = 0; t < (int)blockDim.x; ++t) s += sh[t];
-        out[0] = s;
-    }
+    const double s = wg_sum((double)bad);  // exact: whole numbers below 2^53
+    if (threadIdx.x == 0) out[0] = (int)s;
 }
 void launch_count_bad(hipStream_t st, const double* v, long long n, int* out) {
     hipLaunchKernelGGL(k_count_bad, dim3(1), dim3(kFinBlock), 0, st, v, n, out);
