@@ -350,6 +350,33 @@ __device__ __forceinline__ double wg_sum(double s) {
     return v[0];
 }
 
+// Inclusive scan of one value a lane over the wave (T a 32- or 64-bit integer).
+template <typename T>
+__device__ __forceinline__ T wave_scan(T v) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const T u = __shfl_up(v, o, 64);
+        if (lane >= o) v += u;
+    }
+    return v;
+}
+// Exclusive scan of one value a thread over the work-group (blockDim a multiple of 64), *total
+// its sum.
+template <typename T>
+__device__ __forceinline__ T wg_scan(T v, T* total) {
+    __shared__ T sh[kFinBlock / 64];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = (int)blockDim.x >> 6;
+    const T inc = wave_scan(v);
+    lds_barrier();  // readers of an earlier call are done
+    if (lane == 63) sh[wid] = inc;
+    lds_barrier();
+    const T w = wave_scan(lane < nw ? sh[lane & 15] : (T)0);
+    *total = __shfl(w, nw - 1, 64);
+    const T before = __shfl(w, wid > 0 ? wid - 1 : 0, 64);
+    return (wid > 0 ? before : (T)0) + inc - v;
+}
+
 // Deterministic block reduction of K values; the first wave writes block partial k to
 // part[k * nparts + slot].
 template <int K>

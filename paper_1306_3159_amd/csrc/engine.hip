@@ -311,6 +311,7 @@ static __device__ __align__(256) unsigned char scratch[BLOB_RD_NOALLOC_BYTES];
 namespace {
 
 struct ScratchSlot {
+    bool lds_set = false;  // the multigrid kernels' LDS limits are raised on this GPU
     char* ptr = nullptr;
     std::mutex use;  // one no-alloc solve at a time on this GPU in this process
 };
@@ -330,6 +331,19 @@ ScratchSlot& scratch_slot() {
         s.ptr = static_cast<char*>(p);
     }
     return s;
+}
+
+// Raises the LDS limit of the multigrid kernels to the budget the levels are laid out for, once
+// per GPU (the limit is a property of the kernel, the same for every handle).
+void set_lds_limits(size_t budget) {
+    ScratchSlot& s = scratch_slot();
+    std::lock_guard<std::mutex> lk(g_scratch_m);
+    if (s.lds_set) return;
+    HIPCHK(tail_set_lds<float>(budget));
+    HIPCHK(tail_set_lds<double>(budget));
+    HIPCHK(level_set_lds<float>());
+    HIPCHK(level_set_lds<double>());
+    s.lds_set = true;
 }
 
 }  // namespace
@@ -2248,9 +2262,11 @@ int blob_rd_create(const blob_rd_params* p, blob_rd_t* out) {
     uintptr_t base = (uintptr_t)p->workspace;
     H->ws = (char*)((base + 255) & ~(uintptr_t)255);
     try {
-        HIPCHK(hipHostMalloc((void**)&H->hsc, sizeof(Scalars), hipHostMallocDefault));
-        HIPCHK(hipHostMalloc((void**)&H->hgs, sizeof(GmresScalars), hipHostMallocDefault));
-        HIPCHK(hipHostMalloc((void**)&H->hbuf, 64 * sizeof(double), hipHostMallocDefault));
+        // the host mirrors share one pinned allocation
+        HIPCHK(hipHostMalloc((void**)&H->hbuf, 64 * sizeof(double) + sizeof(Scalars) + sizeof(GmresScalars),
+                             hipHostMallocDefault));
+        H->hsc = reinterpret_cast<Scalars*>(H->hbuf + 64);
+        H->hgs = reinterpret_cast<GmresScalars*>(H->hsc + 1);
         const Plan& P = H->P;
         const int N = P.N;
         hipStream_t st = H->st;
@@ -2333,12 +2349,8 @@ int blob_rd_create(const blob_rd_params* p, blob_rd_t* out) {
         const size_t budget = std::min<size_t>((size_t)lds, 160 * 1024);
         H->tail_level[0] = tail_start(P, 4, budget);
         H->tail_level[1] = tail_start(P, 8, budget);
-        const int Lc = P.nlev - 1;
-        if (H->tail_level[0] < Lc) HIPCHK(tail_set_lds<float>(budget));
-        if (H->tail_level[1] < Lc) HIPCHK(tail_set_lds<double>(budget));
+        set_lds_limits(budget);
         if (H->blocked) {
-            HIPCHK(level_set_lds<float>());
-            HIPCHK(level_set_lds<double>());
             for (int l = 0; l + 1 < P.nlev; ++l)
                 if (P.lev[l].nx % 2 == 0) H->tile[l] = level_tile(P.lev[l].nx, P.lev[l].ny, P.lev[l].nz, P.esz);
         }
@@ -2370,8 +2382,6 @@ int blob_rd_destroy(blob_rd_t H) {
     for (auto& g : H->graphs) (void)hipGraphExecDestroy(g.exec);
     H->graphs.clear();
     if (H->cap_stream) (void)hipStreamDestroy(H->cap_stream);
-    if (H->hsc) (void)hipHostFree(H->hsc);
-    if (H->hgs) (void)hipHostFree(H->hgs);
     if (H->hbuf) (void)hipHostFree(H->hbuf);
     delete H;
     return BLOB_RD_OK;
@@ -3380,7 +3390,6 @@ int precond_build_into(blob_rd* H, blob_rd_net* Nt, void* buf, size_t bytes, siz
     const double* q = H->at<double>(H->P.off_q);
     HIPCHK(hipMemcpyAsync(L.rowptr, rowptr_s, (size_t)(N + 1) * 4, hipMemcpyDeviceToDevice, H->st));
     launch_pair_fill(H->st, q, N, pg, cell, offs, prm, L.rowptr, L.col, L.rowidx);
-    launch_rowidx(H->st, L.rowptr, N, L.rowidx);
     launch_pair_nu(H->st, q, L.pg, L.rowptr, L.col, N, L.nu);
     // the network's stream ordering: make sure its weights are current
     HIPCHK(hipStreamSynchronize(Nt->st));
@@ -3505,23 +3514,16 @@ int blob_rd_precond_loss_grad(blob_rd_t H, blob_rd_net_t Nt, const double* X, co
         double* YP = RP + (size_t)S * N;
         double* coef = YP + (size_t)S * N;
         double lsum = 0.0;
-        std::vector<double> cf(S);
+        std::vector<double> cf(S), sums(2 * (size_t)S);
+        // res = P W P y - x of every sample, its |res|^2 and |x|^2 in the partial-sum buffer
+        launch_loss_rows(st, L.rowptr, L.col, L.val, X, Y, S, N, RP, YP, H->part());
+        HIPCHK(hipMemcpyAsync(sums.data(), H->part(), 2 * (size_t)S * 8, hipMemcpyDeviceToHost, st));
+        HIPCHK(hipStreamSynchronize(st));
         for (int s = 0; s < S; ++s) {
-            double* yp = YP + (size_t)s * N;
-            double* rp = RP + (size_t)s * N;
-            launch_nvec_copy_scale(st, Y + (size_t)s * N, yp, N, 1.0, 0.0);
-            launch_nvec_project(st, yp, N);
-            launch_spmv(st, L.rowptr, L.col, L.val, yp, rp, N);
-            launch_nvec_project(st, rp, N);
-            launch_axpby(st, rp, X + (size_t)s * N, N, 1.0, -1.0);   // res = P W P y - x
-            launch_nvec_sums(st, rp, nullptr, N, H->dsc());
-            launch_nvec_sums(st, X + (size_t)s * N, nullptr, N, H->dsc() + 3);
-            sync_read(H, H->hbuf, H->dsc(), 6 * 8);
-            const double rr = H->hbuf[1], xx = H->hbuf[4];
+            const double rr = sums[2 * s], xx = sums[2 * s + 1];
             if (!(xx > 0.0)) throw Err(BLOB_RD_EINVAL, "zero sample x");
             lsum += rr / xx / S;
             cf[s] = 2.0 / (S * xx);
-            launch_nvec_project(st, rp, N);
         }
         HIPCHK(hipMemcpyAsync(coef, cf.data(), (size_t)S * 8, hipMemcpyHostToDevice, st));
         launch_entry_grad(st, L.rowidx, L.col, L.nnz, RP, YP, coef, S, N, 0.5 * H->prm.D * H->prm.h, L.dg);

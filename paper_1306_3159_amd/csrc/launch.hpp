@@ -263,7 +263,6 @@ void launch_pair_count(hipStream_t st, const double* q, int N, PairGeom pg, cons
                        const int* perm, int* cnt);
 void launch_pair_fill(hipStream_t st, const double* q, int N, PairGeom pg, const int* cell_of, const int* offsets,
                       const int* perm, const int* rowptr, int* col, int* rowidx);
-void launch_rowidx(hipStream_t st, const int* rowptr, int N, int* rowidx);
 void launch_pair_nu(hipStream_t st, const double* q, PairGeom pg, const int* rowptr, const int* col, int N, float* nu);
 void launch_net_assemble(hipStream_t st, const double* q, PairGeom pg, NetDev net, const int* col, const int* rowidx,
                          long long nnz, double Dh, double diag, double* val);
@@ -272,6 +271,10 @@ void launch_spmv(hipStream_t st, const int* rowptr, const int* col, const double
 // y = W (x - mean(x))
 void launch_spmv_centered(hipStream_t st, const int* rowptr, const int* col, const double* val, const double* x,
                           double* y, int N);
+// the S samples of the loss: rp = P W P y - x with its mean removed after sums[2 s] = |rp|^2, yp = P y,
+// sums[2 s + 1] = |x|^2
+void launch_loss_rows(hipStream_t st, const int* rowptr, const int* col, const double* val, const double* X,
+                      const double* Y, int S, int N, double* RP, double* YP, double* sums);
 void launch_count_bad(hipStream_t st, const double* v, long long n, int* out);
 void launch_entry_grad(hipStream_t st, const int* rowidx, const int* col, long long nnz, const double* RP,
                        const double* YP, const double* coef, int S, int N, double half_Dh, float* dg);
