@@ -25,6 +25,8 @@ constexpr int kMaxTuneBlock = 512;  // largest work-group the autotuner may pick
 constexpr int kFinBlock = 1024;
 constexpr int kMaxLevels = 16;
 constexpr int kMaxCoarse = 512;
+constexpr int kTailPad = 8;          // values between the planes of the tail's split levels in LDS
+constexpr int kTailDense = 64;       // coarsest cells up to which its inverse is applied as a dense matrix
 constexpr int kMaxCoarseCols = 256;  // columns of the Schur preconditioner's Fourier coarse level
 constexpr int kCoarseChunk = 2048;   // rows per work-group in the coarse level's dot products
 constexpr int kStageBlobs = 128;   // candidate blobs staged in LDS per pass of the spread planner
@@ -69,8 +71,8 @@ constexpr int kFgMaxRestart = 1024;
 
 // Levels handled by the single-work-group coarse tail (index 0 = first tail
 // level, last = coarsest). LDS byte offsets: each level's work arrays, its result in
-// natural order (levels 1 ..), the coarsest solve's two FP64 vectors and its spectral
-// tables (nspec doubles).
+// natural order (levels 1 ..), the coarsest solve's FP64 vectors and its spectral tables (nspec
+// doubles, followed in device memory by the dense inverse where there is one).
 struct TailDesc {
     int nlev;
     int nspec;

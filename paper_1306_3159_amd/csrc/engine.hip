@@ -120,6 +120,7 @@ size_t fg_bytes(const Plan& P, int restart) {
 size_t net_bytes();
 size_t learned_bytes(int N, long long nnz);
 size_t spec_doubles(const LevelDims& C);
+size_t dense_doubles(const LevelDims& C);
 
 int make_plan(const blob_rd_params* p, Plan* P, std::string* why) {
     if (!p) {
@@ -204,7 +205,8 @@ int make_plan(const blob_rd_params* p, Plan* P, std::string* why) {
     }
     P->off_lvl[P->nlev - 1][0] = take((size_t)P->m * P->esz);  // coarsest u (natural)
     P->off_lvl[P->nlev - 1][2] = take((size_t)P->m * P->esz);  // coarsest f (natural)
-    for (int k = 0; k < 4; ++k) P->off_spec[k] = take(spec_doubles(P->lev[P->nlev - 1]) * 8);
+    const LevelDims& lc = P->lev[P->nlev - 1];
+    for (int k = 0; k < 4; ++k) P->off_spec[k] = take((spec_doubles(lc) + dense_doubles(lc)) * 8);
     P->part_cap = nblocks(ncell) + 64;
     P->off_part = take(P->part_cap * 3 * 8);
     P->off_sc = take(sizeof(Scalars));
@@ -279,23 +281,63 @@ void axis_modes(int n, bool box, double* v, double* lam) {
 // the axes' eigenvectors (x, y, z) and the inverse eigenvalue of every mode in natural order.
 // Periodic with alpha = 0 the constant mode's is zero: the pseudo-inverse on mean-zero vectors.
 size_t spec_doubles(const LevelDims& C) {
-    return (size_t)C.nx * C.nx + (size_t)C.ny * C.ny + (size_t)C.nz * C.nz + (size_t)C.nx * C.ny * C.nz;
+    const size_t n = (size_t)C.nx * C.nx + (size_t)C.ny * C.ny + (size_t)C.nz * C.nz + (size_t)C.nx * C.ny * C.nz;
+    return n + (n & 1);
+}
+// the dense inverse behind them, rows and columns padded to kTailDense, for coarsest grids that
+// the tail solves with it (an even count of doubles before it keeps it 16-byte aligned)
+size_t dense_doubles(const LevelDims& C) {
+    return (size_t)C.nx * C.ny * C.nz <= kTailDense ? (size_t)kTailDense * kTailDense : 0;
 }
 std::vector<double> coarse_spectrum(const LevelDims& C, double D, double alpha, bool box) {
     const double s = D / (C.h * C.h);
-    std::vector<double> out(spec_doubles(C)), lx(C.nx), ly(C.ny), lz(C.nz);
-    double* v = out.data();
-    axis_modes(C.nx, box, v, lx.data());
-    axis_modes(C.ny, box, v + (size_t)C.nx * C.nx, ly.data());
-    axis_modes(C.nz, box, v + (size_t)C.nx * C.nx + (size_t)C.ny * C.ny, lz.data());
-    double* w = v + (size_t)C.nx * C.nx + (size_t)C.ny * C.ny + (size_t)C.nz * C.nz;
-    for (int z = 0; z < C.nz; ++z)
-        for (int y = 0; y < C.ny; ++y)
-            for (int x = 0; x < C.nx; ++x) {
+    const int nx = C.nx, ny = C.ny, nz = C.nz;
+    std::vector<double> out(spec_doubles(C) + dense_doubles(C)), lx(nx), ly(ny), lz(nz);
+    double* vx = out.data();
+    double* vy = vx + (size_t)nx * nx;
+    double* vz = vy + (size_t)ny * ny;
+    double* w = vz + (size_t)nz * nz;
+    axis_modes(nx, box, vx, lx.data());
+    axis_modes(ny, box, vy, ly.data());
+    axis_modes(nz, box, vz, lz.data());
+    for (int z = 0; z < nz; ++z)
+        for (int y = 0; y < ny; ++y)
+            for (int x = 0; x < nx; ++x) {
                 const bool null_mode = !box && alpha == 0.0 && x == 0 && y == 0 && z == 0;
-                w[((size_t)z * C.ny + y) * C.nx + x] =
-                    null_mode ? 0.0 : 1.0 / (alpha + s * (lx[x] + ly[y] + lz[z]));
+                w[((size_t)z * ny + y) * nx + x] = null_mode ? 0.0 : 1.0 / (alpha + s * (lx[x] + ly[y] + lz[z]));
             }
+    if (!dense_doubles(C)) return out;
+    // the dense inverse, an axis at a time: modes (c, b, a) -> (c, b, x x'), (c, y y', x x'), all cells
+    double* M = out.data() + spec_doubles(C);
+    const int x2 = nx * nx, y2 = ny * ny;
+    std::vector<double> t1((size_t)nz * ny * x2), t2((size_t)nz * y2 * x2);
+    for (int c = 0; c < nz; ++c)
+        for (int b = 0; b < ny; ++b)
+            for (int x = 0; x < nx; ++x)
+                for (int xx = 0; xx < nx; ++xx) {
+                    double v = 0.0;
+                    for (int a = 0; a < nx; ++a) v += w[((size_t)c * ny + b) * nx + a] * vx[a * nx + x] * vx[a * nx + xx];
+                    t1[((size_t)c * ny + b) * x2 + x * nx + xx] = v;
+                }
+    for (int c = 0; c < nz; ++c)
+        for (int y = 0; y < ny; ++y)
+            for (int yy = 0; yy < ny; ++yy)
+                for (int k = 0; k < x2; ++k) {
+                    double v = 0.0;
+                    for (int b = 0; b < ny; ++b) v += vy[b * ny + y] * vy[b * ny + yy] * t1[((size_t)c * ny + b) * x2 + k];
+                    t2[((size_t)c * y2 + y * ny + yy) * x2 + k] = v;
+                }
+    for (int z = 0; z < nz; ++z)
+        for (int zz = 0; zz < nz; ++zz)
+            for (int y = 0; y < ny; ++y)
+                for (int yy = 0; yy < ny; ++yy)
+                    for (int x = 0; x < nx; ++x)
+                        for (int xx = 0; xx < nx; ++xx) {
+                            double v = 0.0;
+                            for (int c = 0; c < nz; ++c)
+                                v += vz[c * nz + z] * vz[c * nz + zz] * t2[((size_t)c * y2 + y * ny + yy) * x2 + x * nx + xx];
+                            M[(size_t)((z * ny + y) * nx + x) * kTailDense + (zz * ny + yy) * nx + xx] = v;
+                        }
     return out;
 }
 
@@ -575,7 +617,8 @@ TailDesc make_tail(const blob_rd* H, int t, double alpha) {
         o += (unsigned)((bytes + 15) & ~(size_t)15);
         return r;
     };
-    d.off_ab = take(2 * (size_t)P.m * 8);
+    take(sizeof(TailDesc));  // the descriptor itself
+    d.off_ab = take(std::max<size_t>(2 * (size_t)P.m, kTailDense) * 8);
     d.off_spec = take((size_t)d.nspec * 8);
     for (int k = 0; k < d.nlev; ++k) {
         const LevelDims& ld = P.lev[t + k];
@@ -589,9 +632,10 @@ TailDesc make_tail(const blob_rd* H, int t, double alpha) {
         if (H->box)
             for (int f = 0; f < 4; ++f) d.inv_diag[k][f] = (T)1 / ((T)d.diag[k] + (T)f * (T)s);
         const size_t n = (size_t)ld.nx * ld.ny * ld.nz;
-        // red and black values, each with a stored zero; below the first level also both
-        // right-hand sides and the red residual
-        if (k + 1 < d.nlev) d.off_u[k] = take((n + 2 + (k > 0 ? n + n / 2 : 0)) * sizeof(T));
+        // red and black values (padded planes), each with a stored zero; below the first level
+        // also the red residual and both right-hand sides
+        const size_t pad = (size_t)ld.nz * (ld.nx / 2 * ld.ny + kTailPad);
+        if (k + 1 < d.nlev) d.off_u[k] = take((2 * (pad + 1) + (k > 0 ? pad + n : 0)) * sizeof(T));
         if (k > 0) d.off_nat[k] = take(n * sizeof(T));
     }
     d.lds_bytes = o;

@@ -13,12 +13,18 @@
 //    neighbours' LDS offsets in registers: a half-sweep reads five values and writes one.
 //    The first level's indices (up to eight per thread) stay in registers across the whole
 //    kernel; the lower levels have at most one index per thread and keep theirs in LDS.
-//  * The coarsest operator is a sum of three one-dimensional ones, so its (pseudo-)inverse
-//    is applied in their eigenvector bases: 2 (nx + ny + nz) products per cell in FP64 from
-//    LDS instead of the dense inverse's nx ny nz from L2.
-// Measured, one application (kernel trace): 16^3 -> 8^3 -> 4^3 in FP32 29.9 -> 12.8 us, in
-// FP64 31.8 -> 14.1 us, in a box (FP32) 35.6 -> 19.5 us; 18 x 14 x 10 -> 9 x 7 x 5 36.4 -> 9.3
-// us. Before: all arrays in LDS, cell coordinates divided out at every step, dense inverse.
+//  * The coarsest (pseudo-)inverse is applied in FP64: up to 64 cells as a dense matrix that
+//    is loaded into registers at the start, behind the first level's loads; beyond, in the
+//    eigenvector bases of the axes (the operator is a sum of three one-dimensional ones),
+//    2 (nx + ny + nz) products per cell from LDS instead of nx ny nz from L2.
+//  * Transfers: four threads to a coarse cell of the restriction, a plane each; coordinates
+//    by reciprocals and 24-bit products (a 32-bit product takes four issue slots).
+//  * The descriptor is copied to LDS at once and planes are padded against bank conflicts.
+// Measured, one application (kernel trace): FP64 from 16^3 11.4 us (12.4 with a thread to a
+// coarse cell, spectral coarsest solve and the descriptor in kernel arguments), FP32 box from
+// 16^3 16.6 us (19.5), FP32 from 18 x 14 x 10 9.4 us (9.3; its 315 coarsest cells stay
+// spectral). The first kernel, all arrays in LDS, coordinates divided out at every step and
+// the dense inverse read from L2: 28 to 36 us.
 #include "launch.hpp"
 
 namespace brd {
@@ -27,55 +33,86 @@ namespace {
 
 constexpr int kTailThreads = kFinBlock;
 
-// The coarsest solve: in and out are m doubles in LDS (natural order), tmp another m.
-// spec (LDS): row-major eigenvector matrices (row = mode) of the x, y and z axes, then the
+// Quotients by a fixed divisor of whole numbers below 2^13: (i + 1/2) / n is at least
+// 1 / (2 n) from every whole number, and the rounding of the product far smaller.
+struct Div {
+    float r;
+    int n;
+    __device__ __forceinline__ explicit Div(int d) : r(1.0f / (float)d), n(d) {}
+    __device__ __forceinline__ int operator()(int i) const { return (int)(((float)i + 0.5f) * r); }
+};
+// i -> (a, b, c) of row-major dims (na, nb, *)
+struct Dec {
+    Div a, b;
+    __device__ __forceinline__ Dec(int na, int nb) : a(na), b(nb) {}
+    __device__ __forceinline__ void operator()(int i, int& x, int& y, int& z) const {
+        const int t = a(i);
+        x = i - __mul24(t, a.n);
+        z = b(t);
+        y = t - __mul24(z, b.n);
+    }
+};
+
+// The coarsest solve by eigenvectors: in and out are m doubles in LDS (natural order), b another
+// m. spec (LDS): row-major eigenvector matrices (row = mode) of the x, y and z axes, then the
 // inverse eigenvalue of every mode (natural order; zero for the constant mode when it is
 // the null space). The result is left in `a`.
+__device__ __forceinline__ double spec_dot(const double* v, int vs, const double* a, int as, int n) {
+    double s = 0.0;
+    for (int k0 = 0; k0 < n; k0 += 4) {  // four products' operands in flight
+        double x[4], y[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = min(k0 + u, n - 1);
+            x[u] = v[__mul24(k, vs)];
+            y[u] = k0 + u < n ? a[__mul24(k, as)] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += x[u] * y[u];
+    }
+    return s;
+}
 __device__ __forceinline__ void spectral_solve(double* a, double* b, const double* spec, int nx, int ny, int nz) {
-    const int m = nx * ny * nz, j = threadIdx.x;
+    const int m = nx * ny * nz, j = threadIdx.x, pl = nx * ny;
     const double* vx = spec;
     const double* vy = vx + nx * nx;
     const double* vz = vy + ny * ny;
     const double* w = vz + nz * nz;
     const bool on = j < m;
-    const int x = on ? j % nx : 0, t = on ? j / nx : 0, y = t % ny, z = t / ny;
-    const int row = j - x, col = j - y * nx, pil = j - z * nx * ny;
-    if (on) {
-        double s = 0.0;
-        for (int k = 0; k < nx; ++k) s += vx[x * nx + k] * a[row + k];
-        b[j] = s;
-    }
-    __syncthreads();
-    if (on) {
-        double s = 0.0;
-        for (int k = 0; k < ny; ++k) s += vy[y * ny + k] * b[col + k * nx];
-        a[j] = s;
-    }
-    __syncthreads();
-    if (on) {
-        double s = 0.0;
-        for (int k = 0; k < nz; ++k) s += vz[z * nz + k] * a[pil + k * nx * ny];
-        b[j] = s * w[j];
-    }
-    __syncthreads();
-    if (on) {
-        double s = 0.0;
-        for (int k = 0; k < nz; ++k) s += vz[k * nz + z] * b[pil + k * nx * ny];
-        a[j] = s;
-    }
-    __syncthreads();
-    if (on) {
-        double s = 0.0;
-        for (int k = 0; k < ny; ++k) s += vy[k * ny + y] * a[col + k * nx];
-        b[j] = s;
-    }
-    __syncthreads();
-    if (on) {
-        double s = 0.0;
-        for (int k = 0; k < nx; ++k) s += vx[k * nx + x] * b[row + k];
-        a[j] = s;
-    }
-    __syncthreads();
+    int x = 0, y = 0, z = 0;
+    if (on) Dec(nx, ny)(j, x, y, z);
+    const int row = j - x, col = j - y * nx, pil = j - z * pl;
+    if (on) b[j] = spec_dot(vx + x * nx, 1, a + row, 1, nx);
+    lds_barrier();
+    if (on) a[j] = spec_dot(vy + y * ny, 1, b + col, nx, ny);
+    lds_barrier();
+    if (on) b[j] = spec_dot(vz + z * nz, 1, a + pil, pl, nz) * w[j];
+    lds_barrier();
+    if (on) a[j] = spec_dot(vz + z, nz, b + pil, pl, nz);
+    lds_barrier();
+    if (on) b[j] = spec_dot(vy + y, ny, a + col, nx, ny);
+    lds_barrier();
+    if (on) a[j] = spec_dot(vx + x, nx, b + row, 1, nx);
+    lds_barrier();
+}
+
+// The coarsest solve as a dense matrix (rows and columns padded to kDenseCells): 16 threads to a
+// row, four columns each, loaded by dense_load into c; the result is left in a.
+constexpr int kDenseCells = 64;
+static_assert(kDenseCells * 16 == kTailThreads && kDenseCells == kTailDense, "a row of lanes to a row");
+__device__ __forceinline__ void dense_load(double (&c)[4], const double* __restrict__ dense) {
+    typedef double D2 __attribute__((ext_vector_type(2)));
+    const D2* p = reinterpret_cast<const D2*>(dense + 4 * threadIdx.x);
+    const D2 u = p[0], v = p[1];
+    c[0] = u[0], c[1] = u[1], c[2] = v[0], c[3] = v[1];
+}
+__device__ __forceinline__ void dense_solve(double* a, const double (&c)[4]) {
+    const double* f = a + 4 * (threadIdx.x & 15);
+    double s = (c[0] * f[0] + c[1] * f[1]) + (c[2] * f[2] + c[3] * f[3]);
+    s = row_sum(s);
+    lds_barrier();  // every thread has read a
+    if ((threadIdx.x & 15) == 15) a[threadIdx.x >> 4] = s;
+    lds_barrier();
 }
 
 // One index of a split level: byte offsets within a colour array of the other colour's values
@@ -84,7 +121,7 @@ __device__ __forceinline__ void spectral_solve(double* a, double* b, const doubl
 // 64 KiB); beyond a box face the offset is that of a stored zero (`zero`). pos holds the
 // index's (i, y, z) and the faces its red and black cells touch in a box.
 struct TailCell {
-    unsigned x, y, z, pos;
+    unsigned x, y, z, pos, own;  // own: the index's offset in elements
     __device__ __forceinline__ unsigned xr() const { return x & 0xffffu; }
     __device__ __forceinline__ unsigned xb() const { return x >> 16; }
     __device__ __forceinline__ int pi() const { return pos & 255; }
@@ -95,8 +132,8 @@ struct TailCell {
 };
 
 template <typename T, bool BOX>
-__device__ __forceinline__ TailCell tail_cell(int i, int y, int z, int hx, int ny, int nz, int zero) {
-    const int row = (z * ny + y) * hx, plane = ny * hx, own = row + i;
+__device__ __forceinline__ TailCell tail_cell(int i, int y, int z, int hx, int ny, int nz, int plane, int zero) {
+    const int row = __mul24(z, plane) + __mul24(y, hx), own = row + i, wrap = __mul24(ny - 1, hx);
     const int up = (y + z) & 1;  // red cell x = 2i + up, black cell x = 2i + (1 - up)
     const int r = i + 1, l = i - 1;
     int right, left, ym, yp, zm, zp, fr = 0, fb = 0;
@@ -113,16 +150,17 @@ __device__ __forceinline__ TailCell tail_cell(int i, int y, int z, int hx, int n
     } else {
         right = row + (r < hx ? r : 0);
         left = row + (l >= 0 ? l : hx - 1);
-        ym = y > 0 ? own - hx : own + plane - hx;
-        yp = y + 1 < ny ? own + hx : own - (plane - hx);
-        zm = z > 0 ? own - plane : own + (nz - 1) * plane;
-        zp = z + 1 < nz ? own + plane : own - (nz - 1) * plane;
+        ym = y > 0 ? own - hx : own + wrap;
+        yp = y + 1 < ny ? own + hx : own - wrap;
+        zm = z > 0 ? own - plane : own + __mul24(nz - 1, plane);
+        zp = z + 1 < nz ? own + plane : own - __mul24(nz - 1, plane);
     }
     constexpr unsigned S = sizeof(T);
     TailCell c;
     c.x = (unsigned)(up ? right : left) * S | ((unsigned)(up ? left : right) * S << 16);
     c.y = (unsigned)ym * S | ((unsigned)yp * S << 16);
     c.z = (unsigned)zm * S | ((unsigned)zp * S << 16);
+    c.own = (unsigned)own;
     c.pos = (unsigned)i | ((unsigned)y << 8) | ((unsigned)z << 17) | ((unsigned)fr << 26) | ((unsigned)fb << 28);
     return c;
 }
@@ -151,45 +189,63 @@ __device__ __forceinline__ T tail_sum(const T* o, T own, unsigned xo, const Tail
     return ((own + at(xo)) + (at(c.y & 0xffffu) + at(c.y >> 16))) + (at(c.z & 0xffffu) + at(c.z >> 16));
 }
 
-// Restriction of the split red residual R (black zero) to coarse cell (X, Y, Z): the red
-// cells of a fine row of parity p among 2X-1 .. 2X+2 are those at index X-1 and X (p = 1)
-// or X and X+1 (p = 0).
+// Plane c (fine z = 2Z - 1 + c) of the restriction of the split red residual R (black zero) to
+// coarse cell (X, Y, Z): the red cells of a fine row of parity p among 2X-1 .. 2X+2 are those at
+// index X-1 and X (p = 1) or X and X+1 (p = 0).
 template <typename T, bool BOX>
-__device__ __forceinline__ T tail_restrict(const T* R, int X, int Y, int Z, int hx, int ny, int nz) {
+__device__ __forceinline__ T tail_restrict_plane(const T* R, int X, int Y, int Z, int c, int hx, int ny, int nz,
+                                                 int pstr) {
     const T w0 = (T)0.125, w1 = (T)0.375;
     const int xl = X == 0 ? hx - 1 : X - 1, xr = X + 1 == hx ? 0 : X + 1;
+    const T* plane = R + __mul24(wrapi(2 * Z - 1 + c, nz), pstr);
+    T accb = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        int y = 2 * Y - 1 + b;
+        T wy = (b == 0 || b == 3) ? w0 : w1;
+        if (BOX) {
+            if (y < 0 || y >= ny) wy = (T)0;
+            else if ((b == 1 && y == 0) || (b == 2 && y == ny - 1)) wy = (T)0.25;
+        }
+        const T* row = plane + __mul24(wrapi(y, ny), hx);
+        const int p = (b + c) & 1;  // parity of the row (dims are even)
+        const T m = row[X];
+        T e = row[p ? xl : xr];
+        T wm = w1;
+        if (BOX) {
+            if (p ? X == 0 : X + 1 == hx) e = (T)0;
+            if (p ? X + 1 == hx : X == 0) wm = (T)0.25;  // the boundary fine cell of a boundary coarse cell
+        }
+        accb = fma(wy, restrict_row(w0, wm, p, e, m, e), accb);
+    }
+    return accb;
+}
+
+// The value of lane c of every quad of lanes (DPP quad_perm).
+template <int C>
+__device__ __forceinline__ float quad_value(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x55 * C, 0xf, 0xf, false));
+}
+template <int C>
+__device__ __forceinline__ double quad_value(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x55 * C, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x55 * C, 0xf, 0xf, false));
+}
+
+// The weighted sum of the four planes' values held by the lanes of a quad, in every lane of it.
+template <typename T, bool BOX>
+__device__ __forceinline__ T tail_restrict_sum(T v, int Z, int nz) {
+    const T p[4] = {quad_value<0>(v), quad_value<1>(v), quad_value<2>(v), quad_value<3>(v)};
     T acc = 0;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        int z = 2 * Z - 1 + c;
-        T wz = (c == 0 || c == 3) ? w0 : w1;
+        T w = (c == 0 || c == 3) ? (T)0.125 : (T)0.375;
         if (BOX) {
-            if (z < 0 || z >= nz) wz = (T)0;
-            else if ((c == 1 && z == 0) || (c == 2 && z == nz - 1)) wz = (T)0.25;
+            const int z = 2 * Z - 1 + c;
+            if (z < 0 || z >= nz) w = (T)0;
+            else if ((c == 1 && z == 0) || (c == 2 && z == nz - 1)) w = (T)0.25;
         }
-        z = wrapi(z, nz);
-        T accb = 0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            int y = 2 * Y - 1 + b;
-            T wy = (b == 0 || b == 3) ? w0 : w1;
-            if (BOX) {
-                if (y < 0 || y >= ny) wy = (T)0;
-                else if ((b == 1 && y == 0) || (b == 2 && y == ny - 1)) wy = (T)0.25;
-            }
-            y = wrapi(y, ny);
-            const T* row = R + (z * ny + y) * hx;
-            const int p = (y + z) & 1;
-            const T m = row[X];
-            T e = row[p ? xl : xr];
-            T wm = w1;
-            if (BOX) {
-                if (p ? X == 0 : X + 1 == hx) e = (T)0;
-                if (p ? X + 1 == hx : X == 0) wm = (T)0.25;  // the boundary fine cell of a boundary coarse cell
-            }
-            accb = fma(wy, restrict_row(w0, wm, p, e, m, e), accb);
-        }
-        acc = fma(wz, accb, acc);
+        acc = fma(w, p[c], acc);
     }
     return acc;
 }
@@ -207,10 +263,9 @@ __device__ __forceinline__ T tail_correct(T u, const T* C, int i, int y, int z, 
         if (I1 < 0 || I1 >= cx) I1 = I0, a0 = (T)0.5, a1 = (T)0;
         if (J1 < 0 || J1 >= cy) J1 = J0, b0 = (T)0.5, b1 = (T)0;
         if (K1 < 0 || K1 >= cz) K1 = K0, c0 = (T)0.5, c1 = (T)0;
-        const T* r00 = C + (K0 * cy + J0) * cx;
-        const T* r10 = C + (K0 * cy + J1) * cx;
-        const T* r01 = C + (K1 * cy + J0) * cx;
-        const T* r11 = C + (K1 * cy + J1) * cx;
+        const int pl = __mul24(cx, cy), j0 = __mul24(J0, cx), j1 = __mul24(J1, cx);
+        const T *p0 = C + __mul24(K0, pl), *p1 = C + __mul24(K1, pl);
+        const T *r00 = p0 + j0, *r10 = p0 + j1, *r01 = p1 + j0, *r11 = p1 + j1;
         const T v00 = a0 * r00[I0] + a1 * r00[I1], v10 = a0 * r10[I0] + a1 * r10[I1];
         const T v01 = a0 * r01[I0] + a1 * r01[I1], v11 = a0 * r11[I0] + a1 * r11[I1];
         return u + (c0 * (b0 * v00 + b1 * v10) + c1 * (b0 * v01 + b1 * v11));
@@ -218,24 +273,24 @@ __device__ __forceinline__ T tail_correct(T u, const T* C, int i, int y, int z, 
     I1 = wrapi(I1, cx);
     J1 = wrapi(J1, cy);
     K1 = wrapi(K1, cz);
-    const T* r00 = C + (K0 * cy + J0) * cx;
-    const T* r10 = C + (K0 * cy + J1) * cx;
-    const T* r01 = C + (K1 * cy + J0) * cx;
-    const T* r11 = C + (K1 * cy + J1) * cx;
+    const int pl = __mul24(cx, cy), j0 = __mul24(J0, cx), j1 = __mul24(J1, cx);
+    const T *p0 = C + __mul24(K0, pl), *p1 = C + __mul24(K1, pl);
+    const T *r00 = p0 + j0, *r10 = p0 + j1, *r01 = p1 + j0, *r11 = p1 + j1;
     return tri_add(u, r00[I0], r00[I1], r10[I0], r10[I1], r01[I0], r01[I1], r11[I0], r11[I1]);
 }
 
-// K indices of the first level per thread (index j = threadIdx.x + k * kTailThreads).
+// K indices of the first level per thread (index j = threadIdx.x + k * kTailThreads). dg: the
+// descriptor where the caller has it (kernel arguments or device memory); its words go to LDS
+// first, all at once: read where they are used, each of its cache lines would stall a step.
 template <typename T, int K, bool BOX>
 __device__ __forceinline__ void tail_run(const T* __restrict__ f0g, const T* __restrict__ f1g, T* __restrict__ u0g,
-                                         T* __restrict__ u1g, const TailDesc& d, const double* __restrict__ specg,
+                                         T* __restrict__ u1g, const TailDesc& dg, const double* __restrict__ specg,
                                          unsigned char* smem) {
-    const int tid = threadIdx.x, L = d.nlev - 1;
-    const int nx0 = d.nx[0], ny0 = d.ny[0], nz0 = d.nz[0], hx0 = nx0 >> 1, nh0 = hx0 * ny0 * nz0;
-    T* const A0 = reinterpret_cast<T*>(smem + d.off_u[0]);  // red values, then a zero
-    T* const A1 = A0 + nh0 + 1;                             // black values, then a zero
-    double* const spec = reinterpret_cast<double*>(smem + d.off_spec);
-    const TailCoef<T, BOX> c0(d, 0);
+    TailDesc& d = *reinterpret_cast<TailDesc*>(smem);
+    const int tid = threadIdx.x;
+    static_assert(sizeof(TailDesc) % 4 == 0 && sizeof(TailDesc) / 4 <= kTailThreads, "a word a thread");
+    if (tid < (int)(sizeof(TailDesc) / 4)) reinterpret_cast<int*>(&d)[tid] = reinterpret_cast<const int*>(&dg)[tid];
+    const int nx0 = dg.nx[0], ny0 = dg.ny[0], nz0 = dg.nz[0], hx0 = nx0 >> 1, nh0 = hx0 * ny0 * nz0;
     T f0[K], f1[K], u0[K], u1[K];
     TailCell cell[K];
 #pragma unroll
@@ -248,173 +303,194 @@ __device__ __forceinline__ void tail_run(const T* __restrict__ f0g, const T* __r
             f1[k] = f1g[j];
         }
     }
-    for (int j = tid; j < d.nspec; j += kTailThreads) spec[j] = specg[j];
+    const int L = dg.nlev - 1, nspec = dg.nspec;
+    const int mc = dg.nx[L] * dg.ny[L] * dg.nz[L];
+    const bool dense = mc <= kDenseCells;
+    double dc[4];
+    if (dense) dense_load(dc, specg + nspec);
+    // planes are padded by 8 values: rows of neighbouring planes fall into different banks
+    const int ps0 = __mul24(hx0, ny0) + kTailPad, zero0 = __mul24(nz0, ps0);
+    {
+        const Dec dec(hx0, ny0);
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int j = tid + k * kTailThreads;
-        if (j < nh0) {
-            const int i = j % hx0, t = j / hx0, y = t % ny0, z = t / ny0;
-            cell[k] = tail_cell<T, BOX>(i, y, z, hx0, ny0, nz0, nh0);
+        for (int k = 0; k < K; ++k) {
+            const int j = tid + k * kTailThreads;
+            if (j < nh0) {
+                int i, y, z;
+                dec(j, i, y, z);
+                cell[k] = tail_cell<T, BOX>(i, y, z, hx0, ny0, nz0, ps0, zero0);
+            }
         }
     }
-    if (BOX && tid == 0) A0[nh0] = A1[nh0] = (T)0;
+    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    auto at = [&](int off) { return smem + uni(off); };
+    lds_barrier();
+    T* const A0 = reinterpret_cast<T*>(at(d.off_u[0]));  // red values, then a zero
+    T* const A1 = A0 + zero0 + 1;                        // black values, then a zero
+    double* const spec = reinterpret_cast<double*>(at(d.off_spec));
+    double* const ab = reinterpret_cast<double*>(at(d.off_ab));
+    const TailCoef<T, BOX> c0(d, 0);
+    if (dense) {
+        if (tid < kDenseCells) ab[tid] = 0.0;  // padding of the solve
+    } else {
+        for (int j = tid; j < nspec; j += kTailThreads) spec[j] = specg[j];
+    }
+    if (BOX && tid == 0) A0[zero0] = A1[zero0] = (T)0;
     // half-sweeps of the first level; the barrier orders the written colour before its readers
     auto red = [&]() {
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int j = tid + k * kTailThreads;
-            if (j < nh0) {
+        for (int k = 0; k < K; ++k)
+            if (tid + k * kTailThreads < nh0) {
                 u0[k] = relax(f0[k], c0.s, tail_sum(A1, u1[k], cell[k].xr(), cell[k]), c0.inv(cell[k].fr()));
-                A0[j] = u0[k];
+                A0[cell[k].own] = u0[k];
             }
-        }
-        __syncthreads();
+        lds_barrier();
     };
     auto black = [&]() {
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int j = tid + k * kTailThreads;
-            if (j < nh0) {
+        for (int k = 0; k < K; ++k)
+            if (tid + k * kTailThreads < nh0) {
                 u1[k] = relax(f1[k], c0.s, tail_sum(A0, u0[k], cell[k].xb(), cell[k]), c0.inv(cell[k].fb()));
-                A1[j] = u1[k];
+                A1[cell[k].own] = u1[k];
             }
-        }
-        __syncthreads();
+        lds_barrier();
     };
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int j = tid + k * kTailThreads;
-        if (j < nh0) {
+    for (int k = 0; k < K; ++k)
+        if (tid + k * kTailThreads < nh0) {
             u0[k] = relax_zero(f0[k], c0.inv(cell[k].fr()));  // red sweep from zero
-            A0[j] = u0[k];
+            A0[cell[k].own] = u0[k];
         }
-    }
-    __syncthreads();
+    lds_barrier();
     black();
     red();
     black();
     // red residual, over the red values (every owner keeps its own)
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int j = tid + k * kTailThreads;
-        if (j < nh0)
-            A0[j] = red_resid(f0[k], c0.dg(cell[k].fr()), u0[k], c0.s, tail_sum(A1, u1[k], cell[k].xr(), cell[k]));
-    }
-    __syncthreads();
-    // lower levels, down: u0 | 0 | u1 | 0 | f0 | f1 | r of the level, then its values in natural order
+    for (int k = 0; k < K; ++k)
+        if (tid + k * kTailThreads < nh0)
+            A0[cell[k].own] =
+                red_resid(f0[k], c0.dg(cell[k].fr()), u0[k], c0.s, tail_sum(A1, u1[k], cell[k].xr(), cell[k]));
+    lds_barrier();
+    // lower levels, down: u0 | 0 | u1 | 0 | r (padded planes) | f0 | f1 of the level, then its
+    // values in natural order
     const T* R = A0;
-    int fhx = hx0, fny = ny0, fnz = nz0;
+    int fhx = hx0, fny = ny0, fnz = nz0, fps = ps0;
     for (int l = 1; l <= L; ++l) {
-        const int nx = d.nx[l], ny = d.ny[l], nz = d.nz[l], n = nx * ny * nz;
-        if (l == L) {
-            double* a = reinterpret_cast<double*>(smem + d.off_ab);
-            for (int j = tid; j < n; j += kTailThreads) {
-                const int X = j % nx, t = j / nx;
-                // the right-hand side is rounded to T, as the stored coarse level would be
-                a[j] = (double)tail_restrict<T, BOX>(R, X, t % ny, t / ny, fhx, fny, fnz);
+        const int nx = uni(d.nx[l]), ny = uni(d.ny[l]), nz = uni(d.nz[l]), n = nx * ny * nz;
+        const int hx = nx >> 1, nh = hx * ny * nz, ps = hx * ny + kTailPad, zero = nz * ps;
+        const bool last = l == L;
+        T* B0 = reinterpret_cast<T*>(at(d.off_u[last ? 0 : l]));
+        T* B1 = B0 + zero + 1;
+        T* RR = B1 + zero + 1;
+        T* F0 = RR + zero;
+        T* F1 = F0 + nh;
+        {
+            const Dec dec(nx, ny);
+            for (int q = tid; q < 4 * n; q += kTailThreads) {  // whole quads: 4 n and the stride are multiples of 4
+                int X, Y, Z;
+                dec(q >> 2, X, Y, Z);
+                T v = tail_restrict_plane<T, BOX>(R, X, Y, Z, q & 3, fhx, fny, fnz, fps);
+                v = tail_restrict_sum<T, BOX>(v, Z, fnz);
+                if ((q & 3) == 0) {
+                    // rounded to T on the coarsest grid too, as a stored level would be
+                    if (last) ab[q >> 2] = (double)v;
+                    else (((X + Y + Z) & 1) ? F1 : F0)[__mul24(__mul24(Z, ny) + Y, hx) + (X >> 1)] = v;
+                }
             }
-            __syncthreads();
+        }
+        if (last) {
+            lds_barrier();
             break;
         }
-        const int hx = nx >> 1, nh = hx * ny * nz;
-        T* B0 = reinterpret_cast<T*>(smem + d.off_u[l]);
-        T* B1 = B0 + nh + 1;
-        T* F0 = B1 + nh + 1;
-        T* F1 = F0 + nh;
-        T* RR = F1 + nh;
-        for (int j = tid; j < n; j += kTailThreads) {
-            const int X = j % nx, t = j / nx, Y = t % ny, Z = t / ny;
-            const T v = tail_restrict<T, BOX>(R, X, Y, Z, fhx, fny, fnz);
-            (((X + Y + Z) & 1) ? F1 : F0)[(Z * ny + Y) * hx + (X >> 1)] = v;
-        }
-        if (BOX && tid == 0) B0[nh] = B1[nh] = (T)0;
-        __syncthreads();
+        if (BOX && tid == 0) B0[zero] = B1[zero] = (T)0;
         const TailCoef<T, BOX> c(d, l);
         const bool on = tid < nh;
         T a = 0, b = 0, fa = 0, fb = 0;
         TailCell ce{};
         if (on) {
-            const int i = tid % hx, t = tid / hx;
-            ce = tail_cell<T, BOX>(i, t % ny, t / ny, hx, ny, nz, nh);
+            int i, y, z;
+            Dec(hx, ny)(tid, i, y, z);
+            ce = tail_cell<T, BOX>(i, y, z, hx, ny, nz, ps, zero);
+        }
+        lds_barrier();
+        if (on) {
             fa = F0[tid];
             fb = F1[tid];
             a = relax_zero(fa, c.inv(ce.fr()));
-            B0[tid] = a;
+            B0[ce.own] = a;
         }
-        __syncthreads();
-        if (on) B1[tid] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
-        __syncthreads();
-        if (on) B0[tid] = a = relax(fa, c.s, tail_sum(B1, b, ce.xr(), ce), c.inv(ce.fr()));
-        __syncthreads();
-        if (on) B1[tid] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
-        __syncthreads();
-        if (on) RR[tid] = red_resid(fa, c.dg(ce.fr()), a, c.s, tail_sum(B1, b, ce.xr(), ce));
-        __syncthreads();
+        lds_barrier();
+        if (on) B1[ce.own] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
+        lds_barrier();
+        if (on) B0[ce.own] = a = relax(fa, c.s, tail_sum(B1, b, ce.xr(), ce), c.inv(ce.fr()));
+        lds_barrier();
+        if (on) B1[ce.own] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
+        lds_barrier();
+        if (on) RR[ce.own] = red_resid(fa, c.dg(ce.fr()), a, c.s, tail_sum(B1, b, ce.xr(), ce));
+        lds_barrier();
         R = RR;
         fhx = hx;
         fny = ny;
         fnz = nz;
+        fps = ps;
     }
     // coarsest grid
     {
-        const int nx = d.nx[L], ny = d.ny[L], nz = d.nz[L], m = nx * ny * nz;
-        double* a = reinterpret_cast<double*>(smem + d.off_ab);
-        spectral_solve(a, a + m, spec, nx, ny, nz);
-        T* C = reinterpret_cast<T*>(smem + d.off_nat[L]);
-        for (int j = tid; j < m; j += kTailThreads) C[j] = (T)a[j];
-        __syncthreads();
+        const int nx = uni(d.nx[L]), ny = uni(d.ny[L]), nz = uni(d.nz[L]), m = nx * ny * nz;
+        if (dense) dense_solve(ab, dc);
+        else spectral_solve(ab, ab + m, spec, nx, ny, nz);
+        T* C = reinterpret_cast<T*>(at(d.off_nat[L]));
+        for (int j = tid; j < m; j += kTailThreads) C[j] = (T)ab[j];
+        lds_barrier();
     }
     // lower levels, up
     for (int l = L - 1; l >= 1; --l) {
-        const int nx = d.nx[l], ny = d.ny[l], nz = d.nz[l], hx = nx >> 1, nh = hx * ny * nz;
-        T* B0 = reinterpret_cast<T*>(smem + d.off_u[l]);
-        T* B1 = B0 + nh + 1;
-        const T* F0 = B1 + nh + 1;
+        const int nx = uni(d.nx[l]), ny = uni(d.ny[l]), nz = uni(d.nz[l]);
+        const int hx = nx >> 1, nh = hx * ny * nz, ps = hx * ny + kTailPad, zero = nz * ps;
+        T* B0 = reinterpret_cast<T*>(at(d.off_u[l]));
+        T* B1 = B0 + zero + 1;
+        const T* F0 = B1 + zero + 1 + zero;
         const T* F1 = F0 + nh;
-        T* N = reinterpret_cast<T*>(smem + d.off_nat[l]);
-        const T* C = reinterpret_cast<const T*>(smem + d.off_nat[l + 1]);
+        T* N = reinterpret_cast<T*>(at(d.off_nat[l]));
+        const T* C = reinterpret_cast<const T*>(at(d.off_nat[l + 1]));
         const TailCoef<T, BOX> c(d, l);
         const bool on = tid < nh;
         T a = 0, b = 0, fa = 0, fb = 0;
         TailCell ce{};
         int i = 0, y = 0, z = 0;
         if (on) {
-            i = tid % hx;
-            const int t = tid / hx;
-            y = t % ny;
-            z = t / ny;
-            ce = tail_cell<T, BOX>(i, y, z, hx, ny, nz, nh);
+            Dec(hx, ny)(tid, i, y, z);
+            ce = tail_cell<T, BOX>(i, y, z, hx, ny, nz, ps, zero);
             fa = F0[tid];
             fb = F1[tid];
-            a = tail_correct<T, BOX>(B0[tid], C, i, y, z, hx, ny >> 1, nz >> 1);
-            B0[tid] = a;
+            a = tail_correct<T, BOX>(B0[ce.own], C, i, y, z, hx, ny >> 1, nz >> 1);
+            B0[ce.own] = a;
         }
-        __syncthreads();
-        if (on) B1[tid] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
-        __syncthreads();
-        if (on) B0[tid] = a = relax(fa, c.s, tail_sum(B1, b, ce.xr(), ce), c.inv(ce.fr()));
-        __syncthreads();
-        if (on) B1[tid] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
-        __syncthreads();
+        lds_barrier();
+        if (on) B1[ce.own] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
+        lds_barrier();
+        if (on) B0[ce.own] = a = relax(fa, c.s, tail_sum(B1, b, ce.xr(), ce), c.inv(ce.fr()));
+        lds_barrier();
+        if (on) B1[ce.own] = b = relax(fb, c.s, tail_sum(B0, a, ce.xb(), ce), c.inv(ce.fb()));
+        lds_barrier();
         if (on) {
             a = relax(fa, c.s, tail_sum(B1, b, ce.xr(), ce), c.inv(ce.fr()));
-            const int row = (z * ny + y) * nx, up = (y + z) & 1;
+            const int row = __mul24(__mul24(z, ny) + y, nx), up = (y + z) & 1;
             N[row + 2 * i + up] = a;
             N[row + 2 * i + (up ^ 1)] = b;
         }
-        __syncthreads();
+        lds_barrier();
     }
     // first level, up
-    const T* C = reinterpret_cast<const T*>(smem + d.off_nat[1]);
+    const T* C = reinterpret_cast<const T*>(at(d.off_nat[1]));
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const int j = tid + k * kTailThreads;
-        if (j < nh0) {
+    for (int k = 0; k < K; ++k)
+        if (tid + k * kTailThreads < nh0) {
             u0[k] = tail_correct<T, BOX>(u0[k], C, cell[k].pi(), cell[k].py(), cell[k].pz(), hx0, ny0 >> 1, nz0 >> 1);
-            A0[j] = u0[k];
+            A0[cell[k].own] = u0[k];
         }
-    }
-    __syncthreads();
+    lds_barrier();
     black();
     red();
     black();
