@@ -54,7 +54,9 @@ struct Scalars {
     int32_t iters;    // completed CG iterations
     int32_t project;  // 1: alpha = 0 problem, work on mean-zero vectors
     int32_t status;   // 0 ok, 1 breakdown/non-finite
-    int32_t xzero;    // 1: x starts at zero and the first update writes it (no prior fill)
+    int32_t xzero;    // 1: x starts at zero and its first step writes it (no prior fill)
+    int32_t xsteps;   // iterations whose steps x holds
+    double step[2];   // CG steps of the last two iterations (iteration k: step[k & 1])
 };
 
 // Device-resident scalars of the Schur GMRES (single work-group kernels).
@@ -158,7 +160,7 @@ struct BatchEntry {
 struct InstDev {
     Scalars* sc;
     double* part;
-    double *x, *r, *p, *q;               // CG vectors of the current solve
+    double *x, *r, *q, *p[2];             // CG vectors of the current solve (direction of iteration k in p[k & 1])
     double alpha;                         // operator alpha I - D L (+ S kappa J)
     int nx, ny, nz, nlev, t;              // level 0 dims, levels, first tail level
     int np_apply, np_update, np_dots;     // partial slots of the three reductions

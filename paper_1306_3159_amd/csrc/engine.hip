@@ -881,9 +881,12 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
 }
 
 template <typename T>
+bool cycle_opens_from_f(const blob_rd* H);
+
+template <typename T>
 void precond_zdots(blob_rd* H, double alpha, const double* r, const double* q, const double* spec,
-                   bool entered = false) {
-    unsigned np = vcycle<T>(H, alpha, r, H->sc(), spec, entered, q);
+                   bool entered, bool from_f) {
+    unsigned np = vcycle<T>(H, alpha, r, H->sc(), spec, entered, q, from_f);
     if (np) {
         H->alg_bytes += (double)H->P.ncell * 16;  // r, q read by the fused sweep
     } else {
@@ -922,13 +925,18 @@ void blob_term(blob_rd* H, const double* p, double* q, const Scalars* sc) {
 // Batch executor hooks (defined with the executor below).
 void batch_run_cg(blob_rd* H, double* x, int maxit, bool blobs, double alpha);
 
+// Algorithmic bytes per cell of the vector passes of a CG iteration: direction with its product
+// (z, p r/w, q; every second iteration x r/w and the older p), update (r r/w, q) with the
+// V-cycle entry (f, red u unless the cycle opens from f).
+double cg_vector_bytes(size_t esz, bool from_f) { return esz + 24 + 12 + 24 + (from_f ? 1.0 : 1.5) * esz; }
+
 // Algorithmic bytes of one CG iteration inside the CG loop (update with the
 // V-cycle entry, V-cycle with the fused dots).
 double iteration_bytes(const blob_rd* H) {
     const Plan& P = H->P;
     const int L = P.nlev - 1;
     const int t = std::min(H->tail_level[P.esz == 4 ? 0 : 1], L);
-    double b = (double)P.ncell * (P.esz + 16 + 16 + 48 + 1.5 * P.esz) + (double)P.ncell * 16;
+    double b = (double)P.ncell * cg_vector_bytes(P.esz, false) + (double)P.ncell * 16;
     for (int l = 0; l < t; ++l) b += (double)P.ncell / (1 << (3 * l)) * P.esz * (kPreRestrictBytes + kProlongPostBytes);
     return b;
 }
@@ -949,7 +957,6 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
     hipStream_t st = H->st;
     double* r = H->grid(G_R);
     double* pbuf[2] = {H->grid(G_P), H->grid(G_P2)};
-    int parity = 0;
     double* q = H->grid(G_Q);
     const LevelDims& d = P.lev[0];
     const double s = H->prm.D / (d.h * d.h);
@@ -964,7 +971,7 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
                        rtol * rtol, abs_tol * abs_tol, x_zero ? 1 : 0);
     unsigned np = 0;
     if (x_zero) {
-        // x = 0 is written by the first update (or below when no iteration runs)
+        // x = 0 is written by its first step (or below when no iteration runs)
         if (g == r) {
             launch_self_partials(st, g, P.ncell, H->part(), &np);
             H->alg_bytes += (double)P.ncell * 8;
@@ -979,34 +986,42 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
         H->alg_bytes += (double)P.ncell * 40;
     }
     launch_fin(st, FIN_INIT, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
-    precond_zdots<T>(H, alpha, r, q, spec);
+    const bool from_f = cycle_opens_from_f<T>(H);
+    precond_zdots<T>(H, alpha, r, q, spec, false, from_f);
     int& hist = H->last_iters[(with_blobs ? 2 : 0) + project];
     int chunk = hist > 0 ? std::min(hist, maxit) : std::min(4, maxit);
     int done_iters = 0;
     PcgResult res;
-    // One CG iteration; all scalars come from device memory, so the sequence
-    // is identical from one iteration to the next apart from the p parity.
-    auto iteration = [&](hipStream_t s_) {
+    // One CG iteration; all scalars come from device memory, so the sequence is identical
+    // from one iteration to the next apart from the parity (iteration k: p in pbuf[k & 1]).
+    auto iteration = [&](hipStream_t s_, int parity) {
         hipStream_t keep = H->st;
         H->st = s_;
-        double* p = pbuf[0];
-        (void)parity;
-        launch_dir2<T>(s_, H->at<T>(P.off_lvl[0][0]), H->at<T>(P.off_lvl[0][1]), p, d.nx, d.ny, d.nz, H->sc());
-        launch_applyA2(s_, p, q, alpha, s, d.nx, d.ny, d.nz, H->part(), H->sc(), &np, H->box);
+        double* p = pbuf[parity];
+        launch_cg_dir<T>(s_, H->at<T>(P.off_lvl[0][0]), H->at<T>(P.off_lvl[0][1]), pbuf[parity ^ 1], p, q, x, alpha, s,
+                         d.nx, d.ny, d.nz, H->part(), H->sc(), &np, H->box);
         if (blobs) {
             blob_term(H, p, q, H->sc());
             launch_fin(s_, FIN_ALPHA, H->part(), np, H->sc(), H->nv(0), H->nv(1), P.N, H->inv_h3());
         } else {
             launch_fin(s_, FIN_ALPHA, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
         }
-        launch_update2_enter<T>(s_, x, r, p, q, H->at<T>(P.off_lvl[0][2]), H->at<T>(P.off_lvl[0][3]),
-                                fused<T>(H, 0) ? nullptr : H->at<T>(P.off_lvl[0][0]), d.nx, d.ny, d.nz,
+        launch_update2_enter<T>(s_, r, q, H->at<T>(P.off_lvl[0][2]), H->at<T>(P.off_lvl[0][3]),
+                                from_f ? nullptr : H->at<T>(P.off_lvl[0][0]), d.nx, d.ny, d.nz,
                                 1.0 / (alpha + 6.0 * s), H->part(), H->sc(), &np, H->box ? &binv : nullptr);
         launch_fin(s_, FIN_UPDATE, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
-        precond_zdots<T>(H, alpha, r, q, spec, true);
-        // direction (z, p r/w), stencil (p, q), update (x, r r/w, p, q) with the V-cycle entry (f, red u)
-        H->alg_bytes += (double)P.ncell * (P.esz + 16 + 16 + 48 + 1.5 * P.esz);
+        precond_zdots<T>(H, alpha, r, q, spec, true, from_f);
+        H->alg_bytes += (double)P.ncell * cg_vector_bytes(P.esz, from_f);
         H->st = keep;
+    };
+    // the last steps of x, which no further direction applies
+    auto finish_x = [&]() {
+        if (res.iters > 0) {
+            launch_cg_last(st, x, pbuf[0], pbuf[1], P.ncell, H->sc());
+            H->alg_bytes += (double)P.ncell * 32;
+        } else if (x_zero) {
+            launch_fill(st, x, P.ncell, 0.0);
+        }
     };
     if (H->batch) {
         // The lock-step batch executor runs this solve's iterations in its
@@ -1022,7 +1037,7 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
         res.rr = H->hsc->rr;
         res.gg = H->hsc->gg;
         res.converged = H->hsc->done && H->hsc->status == 0;
-        if (x_zero && res.iters == 0) launch_fill(st, x, P.ncell, 0.0);
+        finish_x();
         return res;
     }
     blob_rd::GraphEntry* ge = nullptr;
@@ -1034,8 +1049,8 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
             const double b0 = H->alg_bytes;
             const int v0 = H->vcycles;
             HIPCHK(hipStreamBeginCapture(H->cap_stream, hipStreamCaptureModeThreadLocal));
-            iteration(H->cap_stream);
-            iteration(H->cap_stream);
+            iteration(H->cap_stream, 0);
+            iteration(H->cap_stream, 1);
             hipGraph_t graph;
             HIPCHK(hipStreamEndCapture(H->cap_stream, &graph));
             hipGraphExec_t exec;
@@ -1053,7 +1068,7 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
         } else {
             // an even number of iterations keeps the p parity aligned with the graphs
             chunk += chunk & 1;
-            for (int k = 0; k < chunk; ++k) iteration(st);
+            for (int k = 0; k < chunk; ++k) iteration(st, k & 1);
         }
         sync_read(H, H->hsc, H->sc(), sizeof(Scalars));
         done_iters = H->hsc->iters;
@@ -1079,7 +1094,7 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
     res.rr = H->hsc->rr;
     res.gg = H->hsc->gg;
     res.converged = H->hsc->done && H->hsc->status == 0;
-    if (x_zero && res.iters == 0) launch_fill(st, x, P.ncell, 0.0);
+    finish_x();
     return res;
 }
 
@@ -2874,7 +2889,7 @@ namespace {
 
 size_t batch_align(size_t b) { return (b + 255) & ~(size_t)255; }
 
-enum { TAB_DIR = 0, TAB_APPLY, TAB_UPDATE, TAB_DOTS, TAB_INTERP, TAB_SPREAD, TAB_LEVELS };
+enum { TAB_DIR = 0, TAB_UPDATE, TAB_DOTS, TAB_INTERP, TAB_SPREAD, TAB_LEVELS };
 constexpr unsigned kPersistBlocks = 2048;  // grid of a batched launch (8 work-groups per CU)
 
 size_t batch_tab_bytes(int n) { return batch_align(sizeof(BatchTab) + (size_t)n * sizeof(BatchEntry)); }
@@ -2915,7 +2930,6 @@ void batch_round(BatchServer& B, hipStream_t s) {
     const int LV = TAB_LEVELS, RS = TAB_LEVELS + B.Lmax;
     for (int it = 0; it < kBatchRoundIters; ++it) {
         launchb_cg<T>(s, BCG_DIR, I, G, T_(TAB_DIR), grid(TAB_DIR), B.n);
-        launchb_cg<T>(s, BCG_APPLY, I, G, T_(TAB_APPLY), grid(TAB_APPLY), B.n);
         if (grid(TAB_INTERP)) {
             launchb_blob(s, 0, I, G, T_(TAB_INTERP), grid(TAB_INTERP));
             launchb_blob(s, 1, I, G, T_(TAB_SPREAD), grid(TAB_SPREAD));
@@ -3003,7 +3017,8 @@ void batch_describe(BatchServer& B, int i, blob_rd* H, bool blobs) {
     D.part = H->part();
     D.x = H->grid(G_U);
     D.r = H->grid(G_R);
-    D.p = H->grid(G_P);
+    D.p[0] = H->grid(G_P);
+    D.p[1] = H->grid(G_P2);
     D.q = H->grid(G_Q);
     D.alpha = B.alpha;
     D.nx = P.lev[0].nx;
@@ -3084,8 +3099,7 @@ void batch_setup(BatchServer& B, char* ws, size_t ws_bytes, const int32_t* kind)
     for (auto& t : B.tabs) t.nb.assign(n, 0u);
     for (int i = 0; i < n; ++i) {
         const InstDev& D = B.h_inst[i];
-        B.tabs[TAB_DIR].nb[i] = nblocks(npair(i));
-        B.tabs[TAB_APPLY].nb[i] = red_blocks(npair(i));
+        B.tabs[TAB_DIR].nb[i] = red_blocks(npair(i));
         B.tabs[TAB_UPDATE].nb[i] = red_blocks(npair(i));
         B.tabs[TAB_DOTS].nb[i] = nblocks(nv(i, 0));
         if (D.blobs) {

@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(kBlock) kb_interp(const InstDev* inst, const i
         Blk blk;
         const InstDev* I = batch_slot(inst, gate, ent, tab->n, g, blk);
         if (!I || !I->blobs) continue;
-        interp_body(I->p, I->N, I->geom, I->base, I->wts, I->perm, I->jx, I->kappa, I->mu, blk);
+        interp_body(I->p[I->sc->iters & 1], I->N, I->geom, I->base, I->wts, I->perm, I->jx, I->kappa, I->mu, blk);
     }
 }
 

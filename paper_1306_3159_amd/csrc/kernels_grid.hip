@@ -68,8 +68,18 @@ void launch_applyA(hipStream_t st, const double* p, double* q, double alpha, dou
 
 typedef double double2_t __attribute__((ext_vector_type(2)));
 
+// alpha p - D L p of the cells (x even, x + 1) whose row holds xl, c[0], c[1], xr, with its
+// roundings fixed: every kernel that applies the operator to a vector gives the same bits.
+__device__ __forceinline__ double2_t stencil_pair(double2_t c, double xl, double xr, double2_t ym, double2_t yp,
+                                                  double2_t zm, double2_t zp, double alpha, double s) {
+#pragma clang fp contract(off)
+    const double a = ((xl + c[1]) + (ym[0] + yp[0])) + (zm[0] + zp[0]);
+    const double b = ((c[0] + xr) + (ym[1] + yp[1])) + (zm[1] + zp[1]);
+    return double2_t{fma(-s, fma(-6.0, c[0], a), alpha * c[0]), fma(-s, fma(-6.0, c[1], b), alpha * c[1])};
+}
+
 // Two cells per thread (x even, x + 1) with 16-byte loads: q = alpha p - D L p,
-// partials (p.q, sum q). Same arithmetic and summation order as stencil_A.
+// partials (p.q, sum q).
 template <bool BOX>
 __device__ __forceinline__ void applyA2_body(const double* __restrict__ p, double* __restrict__ q, double alpha,
                                              double s, int nx, int ny, int nz, unsigned npair, double* part, Blk blk,
@@ -118,11 +128,7 @@ __device__ __forceinline__ void applyA2_body(const double* __restrict__ p, doubl
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             if (k0 + u * bd >= hi) continue;
-            double2_t y;
-            y[0] = alpha * c[u][0] - s * ((xl[u] + c[u][1]) + (ym[u][0] + yp[u][0]) + (zm[u][0] + zp[u][0]) -
-                                          6.0 * c[u][0]);
-            y[1] = alpha * c[u][1] - s * ((c[u][0] + xr[u]) + (ym[u][1] + yp[u][1]) + (zm[u][1] + zp[u][1]) -
-                                          6.0 * c[u][1]);
+            double2_t y = stencil_pair(c[u], xl[u], xr[u], ym[u], yp[u], zm[u], zp[u], alpha, s);
             if (base) {  // residual form q = base - A p
                 y[0] = b[u][0] - y[0];
                 y[1] = b[u][1] - y[1];
@@ -151,18 +157,6 @@ __global__ void __launch_bounds__(kBlock) k_residA2(const double* __restrict__ b
     applyA2_body<BOX>(p, q, alpha, s, nx, ny, nz, npair, nullptr, Blk{blockIdx.x, gridDim.x}, base);
 }
 
-__global__ void __launch_bounds__(kBlock) kb_applyA2(const InstDev* inst, const int* gate, const BatchTab* tab) {
-    const BatchEntry* ent = tab_entries(tab);
-    for (unsigned g = blockIdx.x; g < tab->total; g += gridDim.x) {
-        Blk blk;
-        const InstDev* I = batch_slot(inst, gate, ent, tab->n, g, blk);
-        if (!I) continue;
-        applyA2_body<false>(I->p, I->q, I->alpha, I->ls[0], I->nx, I->ny, I->nz, (unsigned)(I->nx / 2) * I->ny * I->nz,
-                     I->part, blk);
-        __syncthreads();  // partial-sum scratch is reused by the next virtual block
-    }
-}
-
 void launch_applyA2(hipStream_t st, const double* p, double* q, double alpha, double s, int nx, int ny, int nz,
                     double* part, const Scalars* sc, unsigned* np, bool box) {
     const unsigned npair = (unsigned)(nx / 2) * ny * nz;
@@ -172,86 +166,211 @@ void launch_applyA2(hipStream_t st, const double* p, double* q, double alpha, do
     *np = nb;
 }
 
-// p = z + shift + beta p, two cells per thread (z from the split level-0 arrays)
-template <typename T>
-__device__ __forceinline__ void dir2_body(const T* __restrict__ z0, const T* __restrict__ z1, double* __restrict__ p,
-                                          int nx, int ny, unsigned npair, double beta, double shift, Blk blk) {
-    const unsigned k = xcd_block(blk.b, blk.nb) * blockDim.x + threadIdx.x;
-    if (k >= npair) return;
-    const int hx = nx >> 1;
-    const unsigned t = k / hx;
-    const int Y = t % ny, Z = t / ny;
-    const int par = (Y + Z) & 1;  // colour of the even cell
-    const double za = (double)(par ? z1[k] : z0[k]) + shift;
-    const double zb = (double)(par ? z0[k] : z1[k]) + shift;
-    double2_t* pp = reinterpret_cast<double2_t*>(p) + k;
-    double2_t v;
-    if (beta == 0.0) {
-        v[0] = za;
-        v[1] = zb;
-    } else {
-        const double2_t o = *pp;
-        v[0] = za + beta * o[0];
-        v[1] = zb + beta * o[1];
+// Steps of x that iteration k = sc->iters applies before its direction: none at odd k (and
+// k = 0), those of the two iterations before at even k. 1: x starts at zero and is not read.
+__device__ __forceinline__ int cg_steps(const Scalars* sc) {
+    return (sc->iters & 1) || sc->iters == 0 ? 0 : (sc->xzero && sc->iters == 2 ? 1 : 2);
+}
+
+// One CG direction and its product in one pass, two cells per thread:
+//   pn = z + shift + beta po
+//   q  = alpha pn - D L pn, partials (pn.q, sum q)
+//   x += step[0] pn_old + step[1] po   (every second iteration: the steps of the last two, whose
+//                                       directions are in the two buffers)
+// Bound by bytes on large grids, by launches on small ones. Apart, the direction (reads z, po;
+// writes pn), the stencil (reads pn; writes q) and the step of x in the update (reads po, x;
+// writes x) move 8 words of 8 bytes and z per cell; here the neighbours' directions are formed
+// again from z and po, which the caches hold, and 4.5 words and z move. pn and po are two
+// buffers: a block reads neighbours of po that another block would have replaced.
+// Measured per iteration, FP32 z: at 256^3 164 us and 87 us for the update (direction 57,
+// stencil 58 and update 177 apart: 292 -> 251 us, 4.1 TB/s here, writes as many bytes as it
+// reads); at 128^3 13.6 + 9.8 us (6.4 + 9.4 + 14.0) and a launch less.
+template <typename T, bool BOX>
+__device__ __forceinline__ void cg_dir_body(const T* __restrict__ z0, const T* __restrict__ z1,
+                                            const double* __restrict__ po, double* __restrict__ pn,
+                                            double* __restrict__ q, double* __restrict__ x, double alpha, double s,
+                                            int nx, int ny, int nz, unsigned npair, double beta, double shift,
+                                            double step0, double step1, int steps, bool old, double* part,
+                                            Blk blk) {
+    unsigned lo, hi;
+    chunk_of(xcd_block(blk.b, blk.nb), blk.nb, npair, &lo, &hi);
+    double v[2] = {0.0, 0.0};
+    const int hx = nx >> 1, plane = hx * ny;
+    const double2_t* po2 = reinterpret_cast<const double2_t*>(po);
+    // kU pairs per pass: the loads of all are issued before any is computed
+    constexpr int kU = 2;
+    const unsigned bd = blockDim.x;
+    for (unsigned k0 = lo + threadIdx.x; k0 < hi; k0 += kU * bd) {
+        int X[kU], Y[kU], Z[kU];
+        double2_t c[kU], ym[kU], yp[kU], zm[kU], zp[kU], xv[kU], pv[kU];
+        T wc[kU][2], wl[kU], wr[kU], wy[kU][4], wz[kU][4];
+        double xl[kU], xr[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const unsigned k = k0 + u * bd;
+            if (k >= hi) continue;
+            X[u] = (int)(k % hx);
+            const unsigned t = k / hx;
+            Y[u] = t % ny;
+            Z[u] = t / ny;
+            const int par = (Y[u] + Z[u]) & 1;  // colour of the row's even cells
+            const T* ze = par ? z1 : z0;
+            const T* zo = par ? z0 : z1;
+            // neighbour pairs (out of the box: the pair itself, its value is not used)
+            const int kl = (int)k + (X[u] > 0 ? -1 : (BOX ? 0 : hx - 1));
+            const int kr = (int)k + (X[u] + 1 < hx ? 1 : (BOX ? 0 : 1 - hx));
+            const int kym = (int)k + (Y[u] > 0 ? -hx : (BOX ? 0 : plane - hx));
+            const int kyp = (int)k + (Y[u] + 1 < ny ? hx : (BOX ? 0 : hx - plane));
+            const int kzm = (int)k + (Z[u] > 0 ? -plane : (BOX ? 0 : (nz - 1) * plane));
+            const int kzp = (int)k + (Z[u] + 1 < nz ? plane : (BOX ? 0 : -(nz - 1) * plane));
+            wc[u][0] = ze[k];
+            wc[u][1] = zo[k];
+            wl[u] = zo[kl];
+            wr[u] = ze[kr];
+            wy[u][0] = zo[kym];  // rows of the other parity: even cells in zo
+            wy[u][1] = ze[kym];
+            wy[u][2] = zo[kyp];
+            wy[u][3] = ze[kyp];
+            wz[u][0] = zo[kzm];
+            wz[u][1] = ze[kzm];
+            wz[u][2] = zo[kzp];
+            wz[u][3] = ze[kzp];
+            c[u] = ym[u] = yp[u] = zm[u] = zp[u] = xv[u] = pv[u] = double2_t{0.0, 0.0};
+            xl[u] = xr[u] = 0.0;
+            if (old) {
+                c[u] = po2[k];
+                xl[u] = po[2 * (size_t)kl + 1];
+                xr[u] = po[2 * (size_t)kr];
+                ym[u] = po2[kym];
+                yp[u] = po2[kyp];
+                zm[u] = po2[kzm];
+                zp[u] = po2[kzp];
+            }
+            if (steps) pv[u] = reinterpret_cast<const double2_t*>(pn)[k];
+            if (steps == 2) xv[u] = reinterpret_cast<const double2_t*>(x)[k];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const unsigned k = k0 + u * bd;
+            if (k >= hi) continue;
+            if (steps)
+                reinterpret_cast<double2_t*>(x)[k] =
+                    double2_t{fma(step1, c[u][0], fma(step0, pv[u][0], xv[u][0])),
+                              fma(step1, c[u][1], fma(step0, pv[u][1], xv[u][1]))};
+            auto dir = [&](T w, double o) { return fma(beta, o, (double)w + shift); };
+            double2_t cn{dir(wc[u][0], c[u][0]), dir(wc[u][1], c[u][1])};
+            double l = dir(wl[u], xl[u]), r = dir(wr[u], xr[u]);
+            double2_t a{dir(wy[u][0], ym[u][0]), dir(wy[u][1], ym[u][1])};
+            double2_t b{dir(wy[u][2], yp[u][0]), dir(wy[u][3], yp[u][1])};
+            double2_t d{dir(wz[u][0], zm[u][0]), dir(wz[u][1], zm[u][1])};
+            double2_t e{dir(wz[u][2], zp[u][0]), dir(wz[u][3], zp[u][1])};
+            if (BOX) {
+                if (X[u] == 0) l = -cn[0];
+                if (X[u] + 1 == hx) r = -cn[1];
+                if (Y[u] == 0) a = -cn;
+                if (Y[u] + 1 == ny) b = -cn;
+                if (Z[u] == 0) d = -cn;
+                if (Z[u] + 1 == nz) e = -cn;
+            }
+            const double2_t y = stencil_pair(cn, l, r, a, b, d, e, alpha, s);
+            reinterpret_cast<double2_t*>(pn)[k] = cn;
+            reinterpret_cast<double2_t*>(q)[k] = y;
+            v[0] += cn[0] * y[0] + cn[1] * y[1];
+            v[1] += y[0] + y[1];
+        }
     }
-    *pp = v;
+    block_partials<2>(v, part, blk.nb, blk.b);
 }
 
-template <typename T>
-__global__ void __launch_bounds__(kBlock) k_dir2(const T* __restrict__ z0, const T* __restrict__ z1,
-                                                 double* __restrict__ p, int nx, int ny, unsigned npair,
-                                                 const Scalars* sc) {
+template <typename T, bool BOX>
+__global__ void __launch_bounds__(kBlock) k_cg_dir(const T* __restrict__ z0, const T* __restrict__ z1,
+                                                   const double* __restrict__ po, double* __restrict__ pn,
+                                                   double* __restrict__ q, double* __restrict__ x, double alpha,
+                                                   double s, int nx, int ny, int nz, unsigned npair, double* part,
+                                                   const Scalars* sc) {
     if (sc->done) return;
-    dir2_body<T>(z0, z1, p, nx, ny, npair, sc->beta, sc->shift, Blk{blockIdx.x, gridDim.x});
+    cg_dir_body<T, BOX>(z0, z1, po, pn, q, x, alpha, s, nx, ny, nz, npair, sc->beta, sc->shift, sc->step[0], sc->step[1],
+                        cg_steps(sc), sc->iters > 0, part, Blk{blockIdx.x, gridDim.x});
 }
 
 template <typename T>
-__global__ void __launch_bounds__(kBlock) kb_dir2(const InstDev* inst, const int* gate, const BatchTab* tab) {
+__global__ void __launch_bounds__(kBlock) kb_cg_dir(const InstDev* inst, const int* gate, const BatchTab* tab) {
     const BatchEntry* ent = tab_entries(tab);
     for (unsigned g = blockIdx.x; g < tab->total; g += gridDim.x) {
         Blk blk;
         const InstDev* I = batch_slot(inst, gate, ent, tab->n, g, blk);
         if (!I) continue;
-        dir2_body<T>(static_cast<const T*>(I->lv[0][0]), static_cast<const T*>(I->lv[0][1]), I->p, I->nx, I->ny,
-                     (unsigned)(I->nx / 2) * I->ny * I->nz, I->sc->beta, I->sc->shift, blk);
+        const Scalars* sc = I->sc;
+        const int cur = sc->iters & 1;
+        cg_dir_body<T, false>(static_cast<const T*>(I->lv[0][0]), static_cast<const T*>(I->lv[0][1]), I->p[cur ^ 1],
+                              I->p[cur], I->q, I->x, I->alpha, I->ls[0], I->nx, I->ny, I->nz,
+                              (unsigned)(I->nx / 2) * I->ny * I->nz, sc->beta, sc->shift, sc->step[0], sc->step[1],
+                              cg_steps(sc), sc->iters > 0, I->part, blk);
+        __syncthreads();  // partial-sum scratch is reused by the next virtual block
     }
 }
 
 template <typename T>
-void launch_dir2(hipStream_t st, const T* z0, const T* z1, double* p, int nx, int ny, int nz, const Scalars* sc) {
+void launch_cg_dir(hipStream_t st, const T* z0, const T* z1, const double* po, double* pn, double* q, double* x,
+                   double alpha, double s, int nx, int ny, int nz, double* part, const Scalars* sc, unsigned* np,
+                   bool box) {
     const unsigned npair = (unsigned)(nx / 2) * ny * nz;
-    hipLaunchKernelGGL(k_dir2<T>, dim3(nblocks(npair)), dim3(kBlock), 0, st, z0, z1, p, nx, ny, npair, sc);
+    const unsigned nb = red_blocks(npair);
+    if (box)
+        hipLaunchKernelGGL((k_cg_dir<T, true>), dim3(nb), dim3(kBlock), 0, st, z0, z1, po, pn, q, x, alpha, s, nx, ny,
+                           nz, npair, part, sc);
+    else
+        hipLaunchKernelGGL((k_cg_dir<T, false>), dim3(nb), dim3(kBlock), 0, st, z0, z1, po, pn, q, x, alpha, s, nx, ny,
+                           nz, npair, part, sc);
+    *np = nb;
 }
-template void launch_dir2<float>(hipStream_t, const float*, const float*, double*, int, int, int, const Scalars*);
-template void launch_dir2<double>(hipStream_t, const double*, const double*, double*, int, int, int, const Scalars*);
+template void launch_cg_dir<float>(hipStream_t, const float*, const float*, const double*, double*, double*, double*,
+                                   double, double, int, int, int, double*, const Scalars*, unsigned*, bool);
+template void launch_cg_dir<double>(hipStream_t, const double*, const double*, const double*, double*, double*,
+                                    double*, double, double, int, int, int, double*, const Scalars*, unsigned*, bool);
 
-// x += alpha p ; r -= alpha q with partials (r.r, sum r), and the V-cycle
+// The steps of x that no further direction applies: iterations sc->xsteps .. sc->iters - 1
+// (at most two).
+__global__ void __launch_bounds__(kBlock) k_cg_last(double* __restrict__ x, const double* __restrict__ p0,
+                                                    const double* __restrict__ p1, unsigned npair,
+                                                    const Scalars* sc) {
+    const int first = sc->xsteps, n = sc->iters - first;
+    const unsigned k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= npair || n <= 0) return;
+    const int a = first & 1;
+    const double2_t pv = reinterpret_cast<const double2_t*>(a ? p1 : p0)[k];
+    double2_t xv = sc->xzero && first == 0 ? double2_t{0.0, 0.0} : reinterpret_cast<const double2_t*>(x)[k];
+    xv = double2_t{fma(sc->step[a], pv[0], xv[0]), fma(sc->step[a], pv[1], xv[1])};
+    if (n > 1) {
+        const double2_t pw = reinterpret_cast<const double2_t*>(a ? p0 : p1)[k];
+        xv = double2_t{fma(sc->step[a ^ 1], pw[0], xv[0]), fma(sc->step[a ^ 1], pw[1], xv[1])};
+    }
+    reinterpret_cast<double2_t*>(x)[k] = xv;
+}
+void launch_cg_last(hipStream_t st, double* x, const double* p0, const double* p1, size_t ncell, const Scalars* sc) {
+    const unsigned npair = (unsigned)(ncell / 2);
+    hipLaunchKernelGGL(k_cg_last, dim3(nblocks(npair)), dim3(kBlock), 0, st, x, p0, p1, npair, sc);
+}
+
+// r -= alpha q with partials (r.r, sum r), and the V-cycle
 // entry for the new r in the same pass: f = r - mean (the mean predicted from
 // sum r and sum q) into the split level-0 arrays, and the first red
 // half-sweep from a zero guess, u_red = f_red / diag (as k_enter computes it).
 // BOX: the diagonal of a box with fixed faces, per red cell from its face count.
 template <typename T, bool BOX = false>
-__device__ __forceinline__ void update2_enter_body(double* __restrict__ x, double* __restrict__ r,
-                                                   const double* __restrict__ p, const double* __restrict__ q,
+__device__ __forceinline__ void update2_enter_body(double* __restrict__ r, const double* __restrict__ q,
                                                    T* __restrict__ f0, T* __restrict__ f1, T* __restrict__ u0, int nx,
                                                    int ny, unsigned npair, double inv_diag, double a, double m,
-                                                   bool fresh, double* part, Blk blk, int nz = 0,
-                                                   BoxCoef binv = BoxCoef{}) {
+                                                   double* part, Blk blk, int nz = 0, BoxCoef binv = BoxCoef{}) {
     unsigned lo, hi;
     chunk_of(xcd_block(blk.b, blk.nb), blk.nb, npair, &lo, &hi);
     double v[2] = {0.0, 0.0};
     const int hx = nx >> 1;
     for (unsigned k = lo + threadIdx.x; k < hi; k += blockDim.x) {
-        // fresh: x starts at zero and is not read (the first step of a zero-start run)
-        double2_t xv = fresh ? double2_t{0.0, 0.0} : reinterpret_cast<double2_t*>(x)[k];
         double2_t rv = reinterpret_cast<double2_t*>(r)[k];
-        const double2_t pv = reinterpret_cast<const double2_t*>(p)[k];
         const double2_t qv = reinterpret_cast<const double2_t*>(q)[k];
-        xv[0] += a * pv[0];
-        xv[1] += a * pv[1];
         rv[0] -= a * qv[0];
         rv[1] -= a * qv[1];
-        reinterpret_cast<double2_t*>(x)[k] = xv;
         reinterpret_cast<double2_t*>(r)[k] = rv;
         v[0] += rv[0] * rv[0] + rv[1] * rv[1];
         v[1] += rv[0] + rv[1];
@@ -273,26 +392,23 @@ __device__ __forceinline__ void update2_enter_body(double* __restrict__ x, doubl
 }
 
 template <typename T>
-__global__ void __launch_bounds__(kBlock) k_update2_enter(double* __restrict__ x, double* __restrict__ r,
-                                                          const double* __restrict__ p, const double* __restrict__ q,
+__global__ void __launch_bounds__(kBlock) k_update2_enter(double* __restrict__ r, const double* __restrict__ q,
                                                           T* __restrict__ f0, T* __restrict__ f1, T* __restrict__ u0,
                                                           int nx, int ny, unsigned npair, double inv_diag,
                                                           double* part, const Scalars* sc) {
     if (sc->done) return;
-    update2_enter_body<T>(x, r, p, q, f0, f1, u0, nx, ny, npair, inv_diag, sc->alpha, sc->mean_next,
-                          sc->xzero && sc->iters == 0, part, Blk{blockIdx.x, gridDim.x});
+    update2_enter_body<T>(r, q, f0, f1, u0, nx, ny, npair, inv_diag, sc->alpha, sc->mean_next, part, Blk{blockIdx.x, gridDim.x});
 }
 
 template <typename T>
-__global__ void __launch_bounds__(kBlock) k_update2_enter_box(double* __restrict__ x, double* __restrict__ r,
-                                                              const double* __restrict__ p,
-                                                              const double* __restrict__ q, T* __restrict__ f0,
+__global__ void __launch_bounds__(kBlock) k_update2_enter_box(double* __restrict__ r, const double* __restrict__ q,
+                                                              T* __restrict__ f0,
                                                               T* __restrict__ f1, T* __restrict__ u0, int nx, int ny,
                                                               int nz, unsigned npair, BoxCoef binv, double* part,
                                                               const Scalars* sc) {
     if (sc->done) return;
-    update2_enter_body<T, true>(x, r, p, q, f0, f1, u0, nx, ny, npair, 0.0, sc->alpha, sc->mean_next,
-                                sc->xzero && sc->iters == 0, part, Blk{blockIdx.x, gridDim.x}, nz, binv);
+    update2_enter_body<T, true>(r, q, f0, f1, u0, nx, ny, npair, 0.0, sc->alpha, sc->mean_next,
+                                part, Blk{blockIdx.x, gridDim.x}, nz, binv);
 }
 
 template <typename T>
@@ -302,32 +418,31 @@ __global__ void __launch_bounds__(kBlock) kb_update2_enter(const InstDev* inst, 
         Blk blk;
         const InstDev* I = batch_slot(inst, gate, ent, tab->n, g, blk);
         if (!I) continue;
-        update2_enter_body<T>(I->x, I->r, I->p, I->q, static_cast<T*>(I->lv[0][2]), static_cast<T*>(I->lv[0][3]),
+        update2_enter_body<T>(I->r, I->q, static_cast<T*>(I->lv[0][2]), static_cast<T*>(I->lv[0][3]),
                               static_cast<T*>(I->lv[0][0]), I->nx, I->ny, (unsigned)(I->nx / 2) * I->ny * I->nz,
-                              1.0 / I->ldiag[0], I->sc->alpha, I->sc->mean_next,
-                              I->sc->xzero && I->sc->iters == 0, I->part, blk);
+                              1.0 / I->ldiag[0], I->sc->alpha, I->sc->mean_next, I->part, blk);
         __syncthreads();  // partial-sum scratch is reused by the next virtual block
     }
 }
 
 template <typename T>
-void launch_update2_enter(hipStream_t st, double* x, double* r, const double* p, const double* q, T* f0, T* f1, T* u0,
+void launch_update2_enter(hipStream_t st, double* r, const double* q, T* f0, T* f1, T* u0,
                           int nx, int ny, int nz, double inv_diag, double* part, const Scalars* sc, unsigned* np,
                           const BoxCoef* box_inv) {
     const unsigned npair = (unsigned)(nx / 2) * ny * nz;
     const unsigned nb = red_blocks(npair);
     if (box_inv)
-        hipLaunchKernelGGL(k_update2_enter_box<T>, dim3(nb), dim3(kBlock), 0, st, x, r, p, q, f0, f1, u0, nx, ny, nz,
+        hipLaunchKernelGGL(k_update2_enter_box<T>, dim3(nb), dim3(kBlock), 0, st, r, q, f0, f1, u0, nx, ny, nz,
                            npair, *box_inv, part, sc);
     else
-        hipLaunchKernelGGL(k_update2_enter<T>, dim3(nb), dim3(kBlock), 0, st, x, r, p, q, f0, f1, u0, nx, ny, npair,
+        hipLaunchKernelGGL(k_update2_enter<T>, dim3(nb), dim3(kBlock), 0, st, r, q, f0, f1, u0, nx, ny, npair,
                            inv_diag, part, sc);
     *np = nb;
 }
-template void launch_update2_enter<float>(hipStream_t, double*, double*, const double*, const double*, float*, float*,
+template void launch_update2_enter<float>(hipStream_t, double*, const double*, float*, float*,
                                           float*, int, int, int, double, double*, const Scalars*, unsigned*,
                                           const BoxCoef*);
-template void launch_update2_enter<double>(hipStream_t, double*, double*, const double*, const double*, double*,
+template void launch_update2_enter<double>(hipStream_t, double*, const double*, double*,
                                            double*, double*, int, int, int, double, double*, const Scalars*,
                                            unsigned*, const BoxCoef*);
 
@@ -674,6 +789,7 @@ __device__ __forceinline__ void fin_body(int kind, const double* __restrict__ pa
             sc->gg = gg;
             sc->tol2 = t2;
             sc->iters = 0;
+            sc->xsteps = 0;
             sc->beta = 0.0;
             sc->status = is_finite_d(rr) ? 0 : 1;
             sc->done = (rr <= t2 || !is_finite_d(rr)) ? 1 : 0;
@@ -709,12 +825,14 @@ __device__ __forceinline__ void fin_body(int kind, const double* __restrict__ pa
             sc->pq = pq;
             sc->qsum = qs;
             sc->mean_next = 0.0;
+            sc->xsteps = sc->iters & ~1;  // the direction's launch has applied these
             if (!(pq > 0.0) || !is_finite_d(pq) || !is_finite_d(sc->rz)) {
                 sc->status = 1;
                 sc->done = 1;
                 sc->alpha = 0.0;
             } else {
                 sc->alpha = sc->rz / pq;
+                sc->step[sc->iters & 1] = sc->alpha;
                 // sum(r - alpha q) = sum r - alpha sum q: the mean the fused update removes
                 if (sc->project) sc->mean_next = (sc->rsum - sc->alpha * qs) * sc->inv_ncell;
             }
@@ -787,8 +905,7 @@ void launchb_cg(hipStream_t st, int what, const InstDev* inst, const int* gate, 
                 int ninst) {
     const dim3 g(grid), b(kBlock);
     switch (what) {
-        case BCG_DIR: hipLaunchKernelGGL(kb_dir2<T>, g, b, 0, st, inst, gate, tab); break;
-        case BCG_APPLY: hipLaunchKernelGGL(kb_applyA2, g, b, 0, st, inst, gate, tab); break;
+        case BCG_DIR: hipLaunchKernelGGL(kb_cg_dir<T>, g, b, 0, st, inst, gate, tab); break;
         case BCG_UPDATE: hipLaunchKernelGGL(kb_update2_enter<T>, g, b, 0, st, inst, gate, tab); break;
         default:
             hipLaunchKernelGGL(kb_fin, dim3(ninst), dim3(kFinBlock), 0, st,

@@ -20,19 +20,23 @@ void launch_self_partials(hipStream_t st, const double* g, size_t n, double* par
 // r = g - q0 (q0 may be null: r = g); partials (r.r, sum r, g.g)
 void launch_residual_from_q(hipStream_t st, const double* g, const double* q0, double* r, size_t n, double* part,
                             unsigned* nparts_out);
-// Two-cells-per-thread forms (nx even): stencil with partials, direction update,
-// CG update, z dots.
+// Two-cells-per-thread forms (nx even): stencil with partials, CG direction with its
+// product, CG update, z dots.
 void launch_applyA2(hipStream_t st, const double* p, double* q, double alpha, double s, int nx, int ny, int nz,
                     double* part, const Scalars* sc, unsigned* nparts_out, bool box = false);
-// p = z + shift + beta p (z split, level-0 layout of type T)
+// pn = z + shift + beta po (z split, level-0 layout of type T) ; q = A pn with partials
+// (pn.q, sum q) ; every second iteration the last two steps of x. The scalars are read from sc.
 template <typename T>
-void launch_dir2(hipStream_t st, const T* z0, const T* z1, double* p, int nx, int ny, int nz, const Scalars* sc);
-// x += alpha p ; r -= alpha q with partials (r.r, sum r), and the V-cycle entry of
+void launch_cg_dir(hipStream_t st, const T* z0, const T* z1, const double* po, double* pn, double* q, double* x,
+                   double alpha, double s, int nx, int ny, int nz, double* part, const Scalars* sc,
+                   unsigned* nparts_out, bool box);
+// the steps of x left when the iterations end (p0, p1: directions of even and odd iterations)
+void launch_cg_last(hipStream_t st, double* x, const double* p0, const double* p1, size_t ncell, const Scalars* sc);
+// r -= alpha q with partials (r.r, sum r), and the V-cycle entry of
 // the new r (f split, first red sweep u0); box_inv: per-face-count inverse
 // diagonals of a box with fixed faces (inv_diag unused)
 template <typename T>
-void launch_update2_enter(hipStream_t st, double* x, double* r, const double* p, const double* q, T* f0, T* f1, T* u0,
-                          int nx, int ny, int nz, double inv_diag, double* part, const Scalars* sc,
+void launch_update2_enter(hipStream_t st, double* r, const double* q, T* f0, T* f1, T* u0, int nx, int ny, int nz, double inv_diag, double* part, const Scalars* sc,
                           unsigned* nparts_out, const BoxCoef* box_inv = nullptr);
 // partials (sum z, z.r, z.q) with z split of type T
 template <typename T>
@@ -176,7 +180,7 @@ template <typename T>
 hipError_t level_set_lds();
 
 // ---- batched launches (one launch per step for every instance of a batch) ----
-enum { BCG_DIR = 0, BCG_APPLY, BCG_UPDATE, BCG_FIN_ALPHA, BCG_FIN_UPDATE, BCG_FIN_BETA };
+enum { BCG_DIR = 0, BCG_UPDATE, BCG_FIN_ALPHA, BCG_FIN_UPDATE, BCG_FIN_BETA };
 enum { BMG_GS = 0, BMG_GS_DOTS, BMG_RESID, BMG_RESTRICT, BMG_PROLONG, BMG_TAIL };
 // CG steps over the work list `tab` with a fixed grid of `grid` work-groups;
 // the fin kinds take one work-group per instance (ninst)
