@@ -12,7 +12,7 @@ ROOT = os.path.dirname(HERE)
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libblob_rd.so")
 
-SOURCES = ["kernels_grid.hip", "kernels_mg.hip", "kernels_level.hip", "kernels_tail.hip", "kernels_box.hip", "kernels_blob.hip", "kernels_learned.hip",
+SOURCES = ["kernels_grid.hip", "kernels_mg.hip", "kernels_level.hip", "kernels_slab.hip", "kernels_tail.hip", "kernels_box.hip", "kernels_blob.hip", "kernels_learned.hip",
            "kernels_coarse.hip", "engine.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

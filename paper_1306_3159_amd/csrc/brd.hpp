@@ -301,6 +301,17 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// The value of lane c of every quad of lanes (DPP quad_perm).
+template <int C>
+__device__ __forceinline__ float quad_value(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x55 * C, 0xf, 0xf, false));
+}
+template <int C>
+__device__ __forceinline__ double quad_value(double v) {
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x55 * C, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x55 * C, 0xf, 0xf, false));
+}
+
 // v plus the value DPP moves to this lane (zero where it moves none): register moves between
 // lanes, without the LDS round trip of a shuffle.
 template <int CTRL, int ROWS>

@@ -653,6 +653,10 @@ constexpr double kProlongPostBytes = 1.125 + 4 * 1.5;
 // in, both colours out
 constexpr double kFusedDownBytes = 1.0 + 0.5 + 0.125;
 constexpr double kFusedUpBytes = 0.125 + 0.5 + 1.0 + 1.0;
+// f in, red out; red and f in, coarse f out
+constexpr double kSlabDownBytes = 1.0 + 0.5 + 1.5 + 0.125;
+// three half-sweeps of 1.5 apart; together red and f in, black out
+constexpr double kSlabSavedBytes = 3 * 1.5 - 2.0;
 
 // alpha I - D L has a null space (the constant) only on the periodic grid with alpha = 0
 bool singular(const blob_rd* H, double alpha) { return alpha == 0.0 && !H->box; }
@@ -675,6 +679,46 @@ bool fused(const blob_rd* H, int l) {
     const int t = H->tail_level[sizeof(T) == 4 ? 0 : 1];
     return H->blocked && sizeof(T) == H->P.esz && l < t && t < H->P.nlev - 1 && H->tile[l].lanes > 0;
 }
+// Level l, too large for two launches, in tiles cut on all axes: pre-smoothing, residual and
+// restriction in two launches, three post-smoothing half-sweeps in one (above the LDS tail, so the next level is split).
+template <typename T>
+bool slab(const blob_rd* H, int l) {
+    const int t = H->tail_level[sizeof(T) == 4 ? 0 : 1];
+    const LevelDims& d = H->P.lev[l];
+    return H->blocked && sizeof(T) == H->P.esz && l < t && t < H->P.nlev - 1 && !fused<T>(H, l) &&
+           slab_fits(d.nx, d.ny, d.nz, sizeof(T));
+}
+// Whether level l opens from its right-hand side (its first red sweep need not be stored).
+template <typename T>
+bool opens_from_f(const blob_rd* H, int l) {
+    return fused<T>(H, l) || slab<T>(H, l);
+}
+template <typename T>
+bool slab_down(blob_rd* H, int l, int t, double alpha, const Scalars* sc) {
+    if (!slab<T>(H, l)) return false;
+    const Plan& P = H->P;
+    const LevelDims &d = P.lev[l], &c = P.lev[l + 1];
+    auto lv = [&](int k, int a) { return H->at<T>(P.off_lvl[k][a]); };
+    const double D = H->prm.D;
+    const LevelCoef<T> co = level_coef<T>(D / (d.h * d.h), alpha, D / (c.h * c.h), H->box);
+    launch_slab_down<T>(H->st, H->box, lv(l, 0), lv(l, 2), lv(l, 3), d.nx, d.ny, d.nz, co, lv(l + 1, 2), lv(l + 1, 3),
+                        l + 1 == t || opens_from_f<T>(H, l + 1) ? nullptr : lv(l + 1, 0), sc);
+    H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kSlabDownBytes;
+    return true;
+}
+// black, red and black half-sweeps of a level's corrected values
+template <typename T>
+bool slab_sweeps(blob_rd* H, int l, double alpha, const Scalars* sc) {
+    if (!slab<T>(H, l)) return false;
+    const Plan& P = H->P;
+    const LevelDims& d = P.lev[l];
+    auto lv = [&](int k, int a) { return H->at<T>(P.off_lvl[k][a]); };
+    const double s = H->prm.D / (d.h * d.h);
+    launch_slab_post<T>(H->st, H->box, lv(l, 0), lv(l, 1), lv(l, 2), lv(l, 3), d.nx, d.ny, d.nz,
+                        level_coef<T>(s, alpha, s, H->box), sc);
+    H->alg_bytes -= (double)P.ncell / (1 << (3 * l)) * P.esz * kSlabSavedBytes;
+    return true;
+}
 template <typename T>
 bool level_down(blob_rd* H, int l, int t, double alpha, const Scalars* sc) {
     if (!fused<T>(H, l)) return false;
@@ -684,7 +728,7 @@ bool level_down(blob_rd* H, int l, int t, double alpha, const Scalars* sc) {
     const double D = H->prm.D;
     launch_level_down<T>(H->st, H->tile[l], H->box, lv(l, 2), lv(l, 3), lv(l, 4), d.nx, d.ny, d.nz,
                          level_coef<T>(D / (d.h * d.h), alpha, D / (c.h * c.h), H->box), lv(l + 1, 2), lv(l + 1, 3),
-                         l + 1 == t || fused<T>(H, l + 1) ? nullptr : lv(l + 1, 0), sc);
+                         l + 1 == t || opens_from_f<T>(H, l + 1) ? nullptr : lv(l + 1, 0), sc);
     H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kFusedDownBytes;
     return true;
 }
@@ -717,14 +761,14 @@ void vcycle_box(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
     for (int l = 0; l <= L; ++l) box_coefs(H, l, alpha, &dg[l], &inv[l]);
     if (!entered) {
         const LevelDims& d = P.lev[0];
-        launch_enter_box<T>(st, r, lv(0, 2), lv(0, 3), fused<T>(H, 0) ? nullptr : lv(0, 0), d.nx, d.ny, d.nz,
+        launch_enter_box<T>(st, r, lv(0, 2), lv(0, 3), opens_from_f<T>(H, 0) ? nullptr : lv(0, 0), d.nx, d.ny, d.nz,
                             inv[0], sc);
-        H->alg_bytes += (double)P.ncell * (8 + P.esz * (fused<T>(H, 0) ? 1.0 : 1.5));
+        H->alg_bytes += (double)P.ncell * (8 + P.esz * (opens_from_f<T>(H, 0) ? 1.0 : 1.5));
     }
     for (int l = 0; l < t; ++l) {
         const LevelDims& d = P.lev[l];
         const double s = H->prm.D / (d.h * d.h);
-        if (level_down<T>(H, l, t, alpha, sc)) continue;
+        if (level_down<T>(H, l, t, alpha, sc) || slab_down<T>(H, l, t, alpha, sc)) continue;
         launch_gs_box<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.nx, d.ny, d.nz, 1, s, inv[l], sc);
         launch_gs_box<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.nx, d.ny, d.nz, 0, s, inv[l], sc);
         launch_gs_box<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.nx, d.ny, d.nz, 1, s, inv[l], sc);
@@ -745,9 +789,11 @@ void vcycle_box(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
         const int cnat = (l + 1 == L);
         launch_prolong_red_box<T>(st, lv(l + 1, 0), cnat ? nullptr : lv(l + 1, 1), cnat, lv(l, 0), d.nx, d.ny, d.nz,
                                   sc);
-        launch_gs_box<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.nx, d.ny, d.nz, 1, s, inv[l], sc);
-        launch_gs_box<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.nx, d.ny, d.nz, 0, s, inv[l], sc);
-        launch_gs_box<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.nx, d.ny, d.nz, 1, s, inv[l], sc);
+        if (!slab_sweeps<T>(H, l, alpha, sc)) {
+            launch_gs_box<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.nx, d.ny, d.nz, 1, s, inv[l], sc);
+            launch_gs_box<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.nx, d.ny, d.nz, 0, s, inv[l], sc);
+            launch_gs_box<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.nx, d.ny, d.nz, 1, s, inv[l], sc);
+        }
         launch_gs_box<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.nx, d.ny, d.nz, 0, s, inv[l], sc);
         H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kProlongPostBytes;
     }
@@ -797,7 +843,7 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
         // with from_f the first red sweep is not stored: the opening black sweep forms it
         const LevelDims& d = P.lev[0];
         const double s = D / (d.h * d.h);
-        const bool no_u = from_f || fused<T>(H, 0);
+        const bool no_u = from_f || opens_from_f<T>(H, 0);
         launch_enter<T>(st, r, lv(0, 2), lv(0, 3), no_u ? nullptr : lv(0, 0), d.nx, d.ny, d.nz,
                         1.0 / (alpha + 6.0 * s), sc);
         H->alg_bytes += (double)P.ncell * (8 + P.esz * (no_u ? 1.0 : 1.5));
@@ -806,7 +852,7 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
         for (int l = 0; l < t; ++l) {
             const LevelDims& d = P.lev[l];
             const double s = D / (d.h * d.h), diag = alpha + 6.0 * s;
-            if (level_down<T>(H, l, t, alpha, sc)) continue;
+            if (level_down<T>(H, l, t, alpha, sc) || slab_down<T>(H, l, t, alpha, sc)) continue;
             const int* b = H->bs[l];
             first_black(l, s, diag, b);
             launch_gs<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.hx, d.ny, d.nz, 0, s, 1.0 / diag, sc, b[0]);
@@ -835,9 +881,11 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
             }
             const int* b = H->bs[l];
             launch_prolong<T>(st, lv(l + 1, 0), lv(l + 1, 1), 0, lv(l, 0), lv(l, 1), d.nx, d.ny, d.nz, sc, b[3]);
-            launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
-            launch_gs<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.hx, d.ny, d.nz, 0, s, 1.0 / diag, sc, b[0]);
-            launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
+            if (!slab_sweeps<T>(H, l, alpha, sc)) {
+                launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
+                launch_gs<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.hx, d.ny, d.nz, 0, s, 1.0 / diag, sc, b[0]);
+                launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
+            }
             last_red(l, s, diag, b);
             H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kProlongPostBytes;
         }
@@ -1677,7 +1725,7 @@ bool cycle_opens_from_f(const blob_rd* H) {
     const int t0 = std::min(H->tail_level[sizeof(T) == 4 ? 0 : 1], P.nlev - 1);
     const int vw = 16 / (int)sizeof(T);
     if (H->batch && H->batch_v) return false;
-    return fused<T>(H, 0) || (!H->box && (t0 == 0 || (P.lev[0].hx % vw == 0 && P.lev[0].hx >= vw)));
+    return opens_from_f<T>(H, 0) || (!H->box && (t0 == 0 || (P.lev[0].hx % vw == 0 && P.lev[0].hx >= vw)));
 }
 
 void batch_run_vcycle(blob_rd* H);

@@ -17,7 +17,7 @@
 // Measured (kernel trace, FP32, down / up): 64^3 7.4 / 8.7 us where ten per-step launches took
 // about 45; 32^3 5.0 / 5.3 us (an earlier form with an 18^3 window per 8^3 cells and one cell
 // per thread and step: 8.7 / 7.8); 128^3 15.3 / 15.6 us.
-#include "launch.hpp"
+#include "level.hpp"
 
 namespace brd {
 
@@ -26,17 +26,6 @@ namespace {
 constexpr int kDownHalo = 5;  // rows around a tile that the pre-smoothing starts from
 constexpr int kUpHalo = 4;    // the same for the post-smoothing
 constexpr int kLevelThreads = kFinBlock;
-
-template <typename T, int VW>
-struct RowVec {
-    typedef T type __attribute__((ext_vector_type(VW)));
-};
-
-// i mod n for any i
-__device__ __forceinline__ int modi(int i, int n) {
-    i %= n;
-    return i < 0 ? i + n : i;
-}
 
 // A vector of a window row: LDS offset, offset in a grid array, and packed: the distance to
 // the rows the launch writes (bits 0-7), x parity of its red cells (8), first / last vector
@@ -139,43 +128,6 @@ __device__ __forceinline__ typename RowVec<T, VW>::type level_relax(typename Row
     return u;
 }
 
-// Weight of fine cell 2X - 1 + b for coarse cell X on an axis of n fine cells of a box.
-template <typename T>
-__device__ __forceinline__ T level_rweight(int b, int X, int n) {
-    const int f = 2 * X - 1 + b;
-    if (f < 0 || f >= n) return (T)0;
-    if (b == 0 || b == 3) return (T)0.125;
-    if ((b == 1 && f == 0) || (b == 2 && f == n - 1)) return (T)0.25;
-    return (T)0.375;
-}
-
-// Coarse cells X0 .. X0 + VW - 1 of row Y, plane Z: the values a to the split arrays, with
-// the next level's zero-guess red sweep where u0 is set.
-template <typename T, int VW, bool BOX>
-__device__ __forceinline__ void level_coarse_store(const T (&a)[VW], int X0, int Y, int Z, int cx, int cy, int cz,
-                                                   const LevelCoef<T>& c, T* __restrict__ f0, T* __restrict__ f1,
-                                                   T* __restrict__ u0) {
-    const size_t row = ((size_t)Z * cy + Y) * (cx >> 1);
-    const int pc = (Y + Z) & 1;
-    auto inv = [&](int X) {
-        if (!BOX) return c.invc[0];
-        const int f = (X == 0) + (X == cx - 1) + (Y == 0) + (Y == cy - 1) + (Z == 0) + (Z == cz - 1);
-        return f == 0 ? c.invc[0] : (f == 1 ? c.invc[1] : (f == 2 ? c.invc[2] : c.invc[3]));
-    };
-    typedef T H __attribute__((ext_vector_type(VW / 2)));
-    const size_t j = row + (X0 >> 1);
-    H red, blk, u;
-#pragma unroll
-    for (int k = 0; k < VW / 2; ++k) {
-        red[k] = pc ? a[2 * k + 1] : a[2 * k];
-        blk[k] = pc ? a[2 * k] : a[2 * k + 1];
-        u[k] = red[k] * inv(X0 + 2 * k + pc);
-    }
-    *reinterpret_cast<H*>(f0 + j) = red;
-    *reinterpret_cast<H*>(f1 + j) = blk;
-    if (u0) *reinterpret_cast<H*>(u0 + j) = u;
-}
-
 // ---------------------------------------------------------------------------
 template <typename T, int VW, int K, bool BOX>
 __device__ __forceinline__ void level_down(const T* __restrict__ f0, const T* __restrict__ f1, T* __restrict__ ured,
@@ -260,7 +212,6 @@ __device__ __forceinline__ void level_down(const T* __restrict__ f0, const T* __
         const int a = t / nc, q = t - a * nc;
         int i0, qy, qz;
         coarse_of(q, i0, qy, qz);
-        const T w0 = (T)0.125, w1 = (T)0.375;
         const int wz = 2 * qz - 1 + a + H, Y = (b.y0 >> 1) + qy;
         T accb[VW];
 #pragma unroll
@@ -271,18 +222,12 @@ __device__ __forceinline__ void level_down(const T* __restrict__ f0, const T* __
             const int pr = (a + e) & 1;  // red cells of the row (y, z): x = 2i + pr (y0 and z0 are even)
             const V m = *reinterpret_cast<const V*>(r + i0);
             T x = pr ? r[i0 ? i0 - 1 : hx - 1] : r[i0 + VW == hx ? 0 : i0 + VW];
-            T wgt = (e == 0 || e == 3) ? w0 : w1;
+            T wgt = (e == 0 || e == 3) ? (T)0.125 : (T)0.375;
             if (BOX) {
                 if (pr ? i0 == 0 : i0 + VW == hx) x = (T)0;
                 wgt = level_rweight<T>(e, Y, ny);
             }
-#pragma unroll
-            for (int k = 0; k < VW; ++k) {
-                const T l = k ? m[k - 1] : x, n = k + 1 < VW ? m[k + 1] : x;
-                T wm = w1;
-                if (BOX && (pr ? i0 + k == cx - 1 : i0 + k == 0)) wm = (T)0.25;
-                accb[k] = fma(wgt, restrict_row(w0, wm, pr, l, m[k], n), accb[k]);
-            }
+            level_restrict_row<T, VW, BOX>(accb, m, x, pr, wgt, i0 == 0, i0 + VW == hx);
         }
 #pragma unroll
         for (int k = 0; k < VW; ++k) P[t * VW + k] = accb[k];
@@ -488,14 +433,17 @@ unsigned magic(int d) { return (unsigned)(((1ull << 32) + d - 1) / d); }  // umu
 // 4 x 4 rows recomputes the most halo (12 window rows a tile row against 5 for 8 x 8) but
 // gives the most work-groups, so it is taken while they are few enough to run at once and
 // larger tiles beyond. With more than 512 work-groups the recomputed halo costs more than the
-// launches it saves, and the level keeps its per-step launches. One V-cycle in FP32 (us;
-// per-step, 4 x 4, 8 x 4, 8 x 8 on every level): 32^3 46, 25, 26, 28; 64^3 84, 40, 42, 47;
-// 72 x 56 x 40 81, 40, 44, 50; 96 x 112 x 80 119, 77, 73, 64; 128^3 (8 x 8 does not fit its
-// first level) 122, 107, 86, 91. FP64: 64^3 82, 50, 55, 63. Box, FP32: 64^3 86, 50, 52, 58.
+// launches it saves. One V-cycle in FP32 (us; per-step, 4 x 4, 8 x 4, 8 x 8 on every level):
+// 32^3 46, 25, 26, 28; 64^3 84, 40, 42, 47; 72 x 56 x 40 81, 40, 44, 50; 96 x 112 x 80 119,
+// 77, 73, 64; 128^3 (8 x 8 does not fit its first level) 122, 107, 86, 91. FP64: 64^3 82, 50,
+// 55, 63. Box, FP32: 64^3 86, 50, 52, 58. From 512 tiles of kernels_slab.hip on (two to a CU; 8 MB
+// a level) its four launches are faster: 128^3 in FP32 down and up 12.2 + 11.2 us against
+// 15.1 + 15.5 here; at 96 x 112 x 80 (336 such tiles) a solve takes the same time in both.
 LevelTile level_tile(int nx, int ny, int nz, size_t esz) {
     LevelTile g{};
     const int hx = nx / 2;
     if (hx % 2 || hx < 4) return g;  // a level above another split one has even half-rows
+    if (slab_fits(nx, ny, nz, esz) && slab_tiles(nx, ny, nz, esz) >= 512) return g;
     g.vw = esz == 4 && hx % 4 == 0 && hx > 4 ? 4 : 2;
     g.lanes = hx / g.vw;
     const int shapes[3][2] = {{4, 4}, {8, 8}, {8, 4}};

@@ -221,17 +221,6 @@ __device__ __forceinline__ T tail_restrict_plane(const T* R, int X, int Y, int Z
     return accb;
 }
 
-// The value of lane c of every quad of lanes (DPP quad_perm).
-template <int C>
-__device__ __forceinline__ float quad_value(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x55 * C, 0xf, 0xf, false));
-}
-template <int C>
-__device__ __forceinline__ double quad_value(double v) {
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x55 * C, 0xf, 0xf, false),
-                            __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x55 * C, 0xf, 0xf, false));
-}
-
 // The weighted sum of the four planes' values held by the lanes of a quad, in every lane of it.
 template <typename T, bool BOX>
 __device__ __forceinline__ T tail_restrict_sum(T v, int Z, int nz) {

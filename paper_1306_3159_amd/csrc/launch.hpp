@@ -289,4 +289,16 @@ void launch_adam(hipStream_t st, float* P, float* m, float* v, const float* grad
                  float eps, int t);
 void launch_net_pack(hipStream_t st, const float* P, __bf16* W1b, __bf16* W2b, __bf16* w3b);
 
+// Large levels (kernels_slab.hip). Down: pre-smoothing from a zero guess, red residual and
+// restriction in two launches, only u0 is written (cu0 null: the next level opens from its f).
+// Post: black, red and black half-sweeps of the corrected values, u1 is written.
+bool slab_fits(int nx, int ny, int nz, size_t esz);
+unsigned slab_tiles(int nx, int ny, int nz, size_t esz);
+template <typename T>
+void launch_slab_down(hipStream_t st, bool box, T* u0, const T* f0, const T* f1, int nx, int ny, int nz,
+                      const LevelCoef<T>& c, T* cf0, T* cf1, T* cu0, const Scalars* sc);
+template <typename T>
+void launch_slab_post(hipStream_t st, bool box, const T* u0, T* u1, const T* f0, const T* f1, int nx, int ny, int nz,
+                      const LevelCoef<T>& c, const Scalars* sc);
+
 }  // namespace brd
