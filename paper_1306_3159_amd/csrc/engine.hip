@@ -3083,7 +3083,7 @@ void batch_describe(BatchServer& B, int i, blob_rd* H, bool blobs) {
         D.ldiag[l] = B.alpha + 6.0 * D.ls[l];
     }
     const unsigned npair = (unsigned)(D.nx / 2) * D.ny * D.nz;
-    D.np_apply = D.np_update = (int)red_blocks(npair);
+    D.np_apply = D.np_update = (int)cg_blocks(npair);
     D.np_dots = (int)nblocks((size_t)(P.lev[0].hx / (16 / P.esz)) * D.ny * D.nz);
     D.blobs = blobs ? 1 : 0;
     D.N = P.N;
@@ -3147,8 +3147,8 @@ void batch_setup(BatchServer& B, char* ws, size_t ws_bytes, const int32_t* kind)
     for (auto& t : B.tabs) t.nb.assign(n, 0u);
     for (int i = 0; i < n; ++i) {
         const InstDev& D = B.h_inst[i];
-        B.tabs[TAB_DIR].nb[i] = red_blocks(npair(i));
-        B.tabs[TAB_UPDATE].nb[i] = red_blocks(npair(i));
+        B.tabs[TAB_DIR].nb[i] = cg_blocks(npair(i));
+        B.tabs[TAB_UPDATE].nb[i] = cg_blocks(npair(i));
         B.tabs[TAB_DOTS].nb[i] = nblocks(nv(i, 0));
         if (D.blobs) {
             B.tabs[TAB_INTERP].nb[i] = (unsigned)((D.N + kBlock / 64 - 1) / (kBlock / 64));

@@ -182,9 +182,9 @@ __device__ __forceinline__ int cg_steps(const Scalars* sc) {
 // writes x) move 8 words of 8 bytes and z per cell; here the neighbours' directions are formed
 // again from z and po, which the caches hold, and 4.5 words and z move. pn and po are two
 // buffers: a block reads neighbours of po that another block would have replaced.
-// Measured per iteration, FP32 z: at 256^3 164 us and 87 us for the update (direction 57,
-// stencil 58 and update 177 apart: 292 -> 251 us, 4.1 TB/s here, writes as many bytes as it
-// reads); at 128^3 13.6 + 9.8 us (6.4 + 9.4 + 14.0) and a launch less.
+// Measured per iteration, FP32 z: at 256^3 149 us and 75 us for the update (direction 57,
+// stencil 58 and update 177 apart, in 4096 blocks; 4.5 TB/s here, which writes as many bytes as
+// it reads); at 128^3 13.7 + 9.4 us (6.4 + 9.4 + 14.0) and a launch less.
 template <typename T, bool BOX>
 __device__ __forceinline__ void cg_dir_body(const T* __restrict__ z0, const T* __restrict__ z1,
                                             const double* __restrict__ po, double* __restrict__ pn,
@@ -315,7 +315,7 @@ void launch_cg_dir(hipStream_t st, const T* z0, const T* z1, const double* po, d
                    double alpha, double s, int nx, int ny, int nz, double* part, const Scalars* sc, unsigned* np,
                    bool box) {
     const unsigned npair = (unsigned)(nx / 2) * ny * nz;
-    const unsigned nb = red_blocks(npair);
+    const unsigned nb = cg_blocks(npair);
     if (box)
         hipLaunchKernelGGL((k_cg_dir<T, true>), dim3(nb), dim3(kBlock), 0, st, z0, z1, po, pn, q, x, alpha, s, nx, ny,
                            nz, npair, part, sc);
@@ -430,7 +430,7 @@ void launch_update2_enter(hipStream_t st, double* r, const double* q, T* f0, T* 
                           int nx, int ny, int nz, double inv_diag, double* part, const Scalars* sc, unsigned* np,
                           const BoxCoef* box_inv) {
     const unsigned npair = (unsigned)(nx / 2) * ny * nz;
-    const unsigned nb = red_blocks(npair);
+    const unsigned nb = cg_blocks(npair);
     if (box_inv)
         hipLaunchKernelGGL(k_update2_enter_box<T>, dim3(nb), dim3(kBlock), 0, st, r, q, f0, f1, u0, nx, ny, nz,
                            npair, *box_inv, part, sc);
