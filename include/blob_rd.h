@@ -124,7 +124,7 @@ size_t blob_rd_workspace_bytes(const blob_rd_params* p);
 
 /* Validate parameters, place blobs on the grid (wrap, kernel weights, tile
  * binning: one pass of kernels on the stream), build the multigrid hierarchy
- * and the dense coarsest-grid (pseudo-)inverse. q and kappa are copied into
+ * and the coarsest grid's eigenvector tables. q and kappa are copied into
  * the workspace, so the caller may free them afterwards. The workspace must
  * stay valid until blob_rd_destroy. Errors: EINVAL (dims < 8, a level that
  * cannot coarsen to <= 512 cells, kernel_w not 3/4, h or D not positive,

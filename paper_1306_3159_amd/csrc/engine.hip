@@ -673,14 +673,15 @@ void box_coefs(const blob_rd* H, int l, double alpha, BoxCoef* diag, BoxCoef* in
     }
 }
 
-// Level l in two launches (above the LDS tail only, so the next level is split): its zero-guess red sweep is stored where per-step launches follow.
+// Level l in two launches (above the LDS tail only, so the next level is split).
 template <typename T>
 bool fused(const blob_rd* H, int l) {
     const int t = H->tail_level[sizeof(T) == 4 ? 0 : 1];
     return H->blocked && sizeof(T) == H->P.esz && l < t && t < H->P.nlev - 1 && H->tile[l].lanes > 0;
 }
 // Level l, too large for two launches, in tiles cut on all axes: pre-smoothing, residual and
-// restriction in two launches, three post-smoothing half-sweeps in one (above the LDS tail, so the next level is split).
+// restriction in two launches, three post-smoothing half-sweeps in one (above the LDS tail
+// too).
 template <typename T>
 bool slab(const blob_rd* H, int l) {
     const int t = H->tail_level[sizeof(T) == 4 ? 0 : 1];
@@ -747,9 +748,8 @@ bool level_up(blob_rd* H, int l, double alpha, int sweeps, const Scalars* sc) {
 }
 
 // The V-cycle of vcycle() below for the box operator alpha I - D L_0: the same
-// steps and order with the box kernels, per-level launches down to the first
-// level of the LDS tail (then the box tail kernel) or to the coarsest level (the
-// dense box inverse); no temporally blocked levels.
+// steps and order with the box kernels, down to the first level of the LDS tail or
+// to the coarsest level.
 template <typename T>
 void vcycle_box(blob_rd* H, double alpha, const double* r, const Scalars* sc, const double* spec, bool entered) {
     const Plan& P = H->P;
@@ -2751,7 +2751,7 @@ void zero_levels(blob_rd* H) {
     HIPCHK(hipMemsetAsync(H->ws + P.off_lvl[L][2], 0, (size_t)P.m * P.esz, H->st));
 }
 
-// Levels launched one kernel at a time (above the LDS tail or the dense coarse solve).
+// Levels above the LDS tail or the coarse solve.
 int tuned_levels(const blob_rd* H) {
     const int L = H->P.nlev - 1;
     const int t = H->tail_level[H->P.esz == 4 ? 0 : 1];
