@@ -35,7 +35,6 @@ constexpr int kStageBlobs = 128;   // candidate blobs staged in LDS per pass of 
 // `done` first and returns if it is set, so the host can enqueue iterations
 // without waiting for convergence.
 struct Scalars {
-    double rz;        // z . r of the current iterate (with the constant shift)
     double pq;        // p . B p
     double alpha;     // CG step
     double beta;      // CG direction update (Polak-Ribiere form)
@@ -56,7 +55,18 @@ struct Scalars {
     int32_t status;   // 0 ok, 1 breakdown/non-finite
     int32_t xzero;    // 1: x starts at zero and its first step writes it (no prior fill)
     int32_t xsteps;   // iterations whose steps x holds
+    double rz[2];     // z . r (with the constant shift) of the last two iterates (iteration k: rz[k & 1])
     double step[2];   // CG steps of the last two iterations (iteration k: step[k & 1])
+};
+
+// A reduction of CG that a vector pass finishes itself (np = 0: done before it): np partials a
+// set at `in`; alpha's: the blob term's vectors Jp (na) and mu (nb) of length n.
+struct CgFold {
+    const double* in;
+    unsigned np;
+    const double *na, *nb;
+    int n;
+    double inv_h3;
 };
 
 // Device-resident scalars of the Schur GMRES (single work-group kernels).
@@ -421,11 +431,12 @@ inline unsigned red_blocks(size_t n) {
     const unsigned nb = nblocks(n);
     return nb < kRedBlocks ? nb : kRedBlocks;
 }
-// Blocks of CG's vector passes over n cell pairs: a pair per thread up to 2 10^6 cells; beyond,
-// two blocks to a CU, whose longer contiguous runs use HBM better: at 256^3 the direction takes
-// 149 us and the update 75 with 512 blocks (256: 148, 113; 768: 157, 74; 4096: 165, 87). At
-// 128^3 512 blocks take 13.1 and 9.8 us, 4096 13.7 and 9.4; a set-up is 1 % slower with 512.
-inline unsigned cg_blocks(size_t n) { return n > ((size_t)1 << 20) ? 512 : nblocks(n); }
+// Blocks of CG's vector passes over n cell pairs: a pair per thread up to 10^6 cells; beyond, two
+// blocks to a CU, whose longer contiguous runs use HBM better on large grids (256^3: direction
+// 149 us, update 75; 256 blocks 148, 113; 768: 157, 74; 4096: 165, 87) and whose partials are few
+// enough for the next pass to sum by itself (128^3: as fast as 4096 blocks before that). At
+// 96 x 112 x 80 a solve is 1 % slower with 512 than with 1680.
+inline unsigned cg_blocks(size_t n) { return n > ((size_t)1 << 19) ? 512 : nblocks(n); }
 // Entry of a batched launch that owns global block g (entries sorted by block0).
 __device__ __forceinline__ int batch_entry(const BatchEntry* e, int n, unsigned g) {
     int lo = 0, hi = n - 1;

@@ -523,7 +523,7 @@ enum GridBuf { G_R = 0, G_P = 1, G_Q = 2, G_U = 3, G_G = 4, G_T1 = 5, G_T2 = 6, 
 __global__ void k_sc_init(Scalars* sc, int project, double inv_ncell, double eBe_inv, double rtol2, double abs2,
                           int xzero) {
     sc->xzero = xzero;
-    sc->rz = 0.0;
+    sc->rz[0] = sc->rz[1] = 0.0;
     sc->pq = 0.0;
     sc->alpha = 0.0;
     sc->beta = 0.0;
@@ -931,9 +931,20 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
 template <typename T>
 bool cycle_opens_from_f(const blob_rd* H);
 
+// Partials a set of the dots behind a V-cycle: of the closing red sweep with dots, or of their own
+// pass (the tail on level 0, a box, rows that are no whole vectors).
 template <typename T>
-void precond_zdots(blob_rd* H, double alpha, const double* r, const double* q, const double* spec,
-                   bool entered, bool from_f) {
+unsigned dots_partials(const blob_rd* H) {
+    const LevelDims& d = H->P.lev[0];
+    const int VW = 16 / (int)sizeof(T), t = std::min(H->tail_level[sizeof(T) == 4 ? 0 : 1], H->P.nlev - 1);
+    if (H->box || t == 0 || d.hx % VW != 0 || d.hx < VW) return red_blocks(H->P.ncell / 2);
+    return nblocks((size_t)(d.hx / VW) * d.ny * d.nz);
+}
+
+// The V-cycle on r and the partials of (sum z, z.r, z.q), finished unless fold; returns their number.
+template <typename T>
+unsigned precond_zdots(blob_rd* H, double alpha, const double* r, const double* q, const double* spec,
+                   bool entered, bool from_f, bool fold) {
     unsigned np = vcycle<T>(H, alpha, r, H->sc(), spec, entered, q, from_f);
     if (np) {
         H->alg_bytes += (double)H->P.ncell * 16;  // r, q read by the fused sweep
@@ -943,7 +954,9 @@ void precond_zdots(blob_rd* H, double alpha, const double* r, const double* q, c
                          H->part(), H->sc(), &np);
         H->alg_bytes += (double)H->P.ncell * (H->P.esz + 16);
     }
-    launch_fin(H->st, FIN_BETA, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
+    if (np != dots_partials<T>(H)) throw Err(BLOB_RD_EDEVICE, "CG dots: unexpected number of partials");
+    if (!fold) launch_fin(H->st, FIN_BETA, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
+    return np;
 }
 
 // out = base_in + scale * S (lam + lam_shift) from the contribution lists: a
@@ -1035,7 +1048,21 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
     }
     launch_fin(st, FIN_INIT, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
     const bool from_f = cycle_opens_from_f<T>(H);
-    precond_zdots<T>(H, alpha, r, q, spec, false, from_f);
+    // Reductions that the next vector pass finishes itself, each of its blocks for itself, instead
+    // of a launch of one work-group: the dots by the direction, p.q by the update. A launch takes 3
+    // to 5 us and a gap, the sums of up to 1024 (dots: 128^3 in FP32) or 512 (p.q) partials a set or 2048
+    // blobs 1 to 2 us in every block; beyond, reading them in every block outweighs it (the dots in
+    // 1680 blocks at 96 x 112 x 80: a solve 3 % slower). A Schur solve at 128^3
+    // 14.1 -> 13.7 ms, a set-up 43.4 -> 42.3, a reactive solve at 32^3 0.73 -> 0.71. Not in a batch,
+    // whose rounds finish them.
+    const unsigned nd = dots_partials<T>(H), npv = cg_blocks(P.ncell / 2);
+    const bool room = 3 * (size_t)nd + 4 * (size_t)npv <= 3 * P.part_cap;
+    const bool few = !H->batch && room && npv <= 512;  // passes of few blocks: each repeats the sums
+    const bool fold_beta = few && nd <= 1024;
+    const bool fold_alpha = few && (!blobs || P.N <= 2048);
+    double* const part_dir = H->part() + (room ? 3 * (size_t)nd : 0);
+    double* const part_upd = part_dir + (room ? 2 * (size_t)npv : 0);
+    precond_zdots<T>(H, alpha, r, q, spec, false, from_f, fold_beta);
     int& hist = H->last_iters[(with_blobs ? 2 : 0) + project];
     int chunk = hist > 0 ? std::min(hist, maxit) : std::min(4, maxit);
     int done_iters = 0;
@@ -1047,18 +1074,18 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
         H->st = s_;
         double* p = pbuf[parity];
         launch_cg_dir<T>(s_, H->at<T>(P.off_lvl[0][0]), H->at<T>(P.off_lvl[0][1]), pbuf[parity ^ 1], p, q, x, alpha, s,
-                         d.nx, d.ny, d.nz, H->part(), H->sc(), &np, H->box);
-        if (blobs) {
-            blob_term(H, p, q, H->sc());
-            launch_fin(s_, FIN_ALPHA, H->part(), np, H->sc(), H->nv(0), H->nv(1), P.N, H->inv_h3());
-        } else {
-            launch_fin(s_, FIN_ALPHA, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
-        }
+                         d.nx, d.ny, d.nz, part_dir, H->sc(), &np, H->box,
+                         CgFold{H->part(), fold_beta ? nd : 0, nullptr, nullptr, 0, 0.0});
+        const CgFold pq = blobs ? CgFold{part_dir, np, H->nv(0), H->nv(1), P.N, H->inv_h3()}
+                                : CgFold{part_dir, np, nullptr, nullptr, 0, 0.0};
+        if (blobs) blob_term(H, p, q, H->sc());
+        if (!fold_alpha) launch_fin(s_, FIN_ALPHA, pq.in, pq.np, H->sc(), pq.na, pq.nb, pq.n, pq.inv_h3);
         launch_update2_enter<T>(s_, r, q, H->at<T>(P.off_lvl[0][2]), H->at<T>(P.off_lvl[0][3]),
                                 from_f ? nullptr : H->at<T>(P.off_lvl[0][0]), d.nx, d.ny, d.nz,
-                                1.0 / (alpha + 6.0 * s), H->part(), H->sc(), &np, H->box ? &binv : nullptr);
-        launch_fin(s_, FIN_UPDATE, H->part(), np, H->sc(), nullptr, nullptr, 0, 0.0);
-        precond_zdots<T>(H, alpha, r, q, spec, true, from_f);
+                                1.0 / (alpha + 6.0 * s), part_upd, H->sc(), &np, H->box ? &binv : nullptr,
+                                fold_alpha ? pq : CgFold{});
+        launch_fin(s_, FIN_UPDATE, part_upd, np, H->sc(), nullptr, nullptr, 0, 0.0);
+        precond_zdots<T>(H, alpha, r, q, spec, true, from_f, fold_beta);
         H->alg_bytes += (double)P.ncell * cg_vector_bytes(P.esz, from_f);
         H->st = keep;
     };

@@ -68,6 +68,100 @@ void launch_applyA(hipStream_t st, const double* p, double* q, double alpha, dou
 
 typedef double double2_t __attribute__((ext_vector_type(2)));
 
+__device__ __forceinline__ bool is_finite_d(double v) { return v == v && v - v == 0.0; }
+
+// The CG step from p.q and sum q, with its roundings fixed (formed by the finalize kernel or by
+// every block of the update). sum(r - alpha q) = sum r - alpha sum q: the mean the fused update
+// removes.
+struct CgAlpha {
+    double alpha, mean;
+    bool bad;
+};
+__device__ __forceinline__ CgAlpha cg_alpha(double pq, double qs, const Scalars* sc) {
+#pragma clang fp contract(off)
+    const double rz = sc->rz[sc->iters & 1];
+    CgAlpha c{0.0, 0.0, !(pq > 0.0) || !is_finite_d(pq) || !is_finite_d(rz)};
+    if (!c.bad) {
+        c.alpha = rz / pq;
+        if (sc->project) c.mean = fma(-c.alpha, qs, sc->rsum) * sc->inv_ncell;
+    }
+    return c;
+}
+__device__ __forceinline__ void cg_alpha_store(const CgAlpha& c, double pq, double qs, Scalars* sc) {
+    sc->pq = pq;
+    sc->qsum = qs;
+    sc->mean_next = c.mean;
+    sc->alpha = c.alpha;
+    sc->xsteps = sc->iters & ~1;  // the direction's launch has applied these
+    if (c.bad) {
+        sc->status = 1;
+        sc->done = 1;
+    } else {
+        sc->step[sc->iters & 1] = c.alpha;
+    }
+}
+
+// The direction's scalars from sum z, z.r and z.q, likewise (Polak-Ribiere form).
+struct CgBeta {
+    double shift, rz, beta;
+    bool bad;
+};
+__device__ __forceinline__ CgBeta cg_beta(double zs, double zr, double zq, const Scalars* sc) {
+#pragma clang fp contract(off)
+    CgBeta c;
+    c.shift = sc->project ? fma(sc->rsum, sc->eBe_inv, -(zs * sc->inv_ncell)) : 0.0;
+    c.rz = fma(c.shift, sc->rsum, zr);
+    const double zq_full = fma(c.shift, sc->qsum, zq);
+    c.beta = sc->iters == 0 ? 0.0 : -sc->alpha * zq_full / sc->rz[(sc->iters & 1) ^ 1];
+    c.bad = !is_finite_d(c.rz) || !is_finite_d(c.beta);
+    return c;
+}
+__device__ __forceinline__ void cg_beta_store(const CgBeta& c, Scalars* sc) {
+    sc->shift = c.shift;
+    sc->beta = c.beta;
+    sc->rz[sc->iters & 1] = c.rz;
+    if (c.bad) {
+        sc->status = 1;
+        sc->done = 1;
+    }
+}
+
+// Sums of K values per index i < n (at(i, v) adds index i's to v) by kBlock threads, in the order
+// of the finalize kernel's kFinBlock: each wave stands for four of its waves.
+template <int K, typename At>
+__device__ __forceinline__ void fold_sums(unsigned n, At at, double (&s)[K]) {
+    __shared__ double sh[K][kFinBlock / 64];
+    constexpr int J = kFinBlock / kBlock;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    double v[J][K] = {};
+    for (unsigned i0 = 0; i0 < n; i0 += kFinBlock)
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const unsigned i = i0 + (wid + j * (kBlock / 64)) * 64 + lane;
+            if (i < n) at(i, v[j]);
+        }
+#pragma unroll
+    for (int j = 0; j < J; ++j)
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const double t = wave_sum(v[j][k]);
+            if (lane == 0) sh[k][wid + j * (kBlock / 64)] = t;
+        }
+    lds_barrier();
+#pragma unroll
+    for (int k = 0; k < K; ++k) s[k] = lane_value(row_sum(lane < kFinBlock / 64 ? sh[k][lane & 15] : 0.0), 15);
+    lds_barrier();
+}
+template <int K>
+__device__ __forceinline__ void fold_partials(const CgFold& f, double (&s)[K]) {
+    const double* p = f.in;
+    const unsigned np = f.np;
+    fold_sums<K>(np, [=](unsigned i, double (&v)[K]) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] += p[(size_t)k * np + i];
+    }, s);
+}
+
 // alpha p - D L p of the cells (x even, x + 1) whose row holds xl, c[0], c[1], xr, with its
 // roundings fixed: every kernel that applies the operator to a vector gives the same bits.
 __device__ __forceinline__ double2_t stencil_pair(double2_t c, double xl, double xr, double2_t ym, double2_t yp,
@@ -184,7 +278,7 @@ __device__ __forceinline__ int cg_steps(const Scalars* sc) {
 // buffers: a block reads neighbours of po that another block would have replaced.
 // Measured per iteration, FP32 z: at 256^3 149 us and 75 us for the update (direction 57,
 // stencil 58 and update 177 apart, in 4096 blocks; 4.5 TB/s here, which writes as many bytes as
-// it reads); at 128^3 13.7 + 9.4 us (6.4 + 9.4 + 14.0) and a launch less.
+// it reads); at 128^3 13.1 + 9.8 us (6.4 + 9.4 + 14.0) and a launch less.
 template <typename T, bool BOX>
 __device__ __forceinline__ void cg_dir_body(const T* __restrict__ z0, const T* __restrict__ z1,
                                             const double* __restrict__ po, double* __restrict__ pn,
@@ -282,14 +376,29 @@ __device__ __forceinline__ void cg_dir_body(const T* __restrict__ z0, const T* _
     block_partials<2>(v, part, blk.nb, blk.b);
 }
 
-template <typename T, bool BOX>
+template <typename T, bool BOX, bool FOLD>
 __global__ void __launch_bounds__(kBlock) k_cg_dir(const T* __restrict__ z0, const T* __restrict__ z1,
                                                    const double* __restrict__ po, double* __restrict__ pn,
                                                    double* __restrict__ q, double* __restrict__ x, double alpha,
                                                    double s, int nx, int ny, int nz, unsigned npair, double* part,
-                                                   const Scalars* sc) {
+                                                   Scalars* sc, CgFold fold) {
     if (sc->done) return;
-    cg_dir_body<T, BOX>(z0, z1, po, pn, q, x, alpha, s, nx, ny, nz, npair, sc->beta, sc->shift, sc->step[0], sc->step[1],
+    double beta = 0.0, shift = 0.0;
+    if (FOLD) {
+        // every block forms beta; the first stores it, in fields that no block of this launch reads
+        // (rz of this iteration beside that of the last)
+        double t[3];
+        fold_partials<3>(fold, t);
+        const CgBeta c = cg_beta(t[0], t[1], t[2], sc);
+        if (blockIdx.x == 0 && threadIdx.x == 0) cg_beta_store(c, sc);
+        if (c.bad) return;
+        beta = c.beta;
+        shift = c.shift;
+    } else {
+        beta = sc->beta;
+        shift = sc->shift;
+    }
+    cg_dir_body<T, BOX>(z0, z1, po, pn, q, x, alpha, s, nx, ny, nz, npair, beta, shift, sc->step[0], sc->step[1],
                         cg_steps(sc), sc->iters > 0, part, Blk{blockIdx.x, gridDim.x});
 }
 
@@ -312,22 +421,21 @@ __global__ void __launch_bounds__(kBlock) kb_cg_dir(const InstDev* inst, const i
 
 template <typename T>
 void launch_cg_dir(hipStream_t st, const T* z0, const T* z1, const double* po, double* pn, double* q, double* x,
-                   double alpha, double s, int nx, int ny, int nz, double* part, const Scalars* sc, unsigned* np,
-                   bool box) {
+                   double alpha, double s, int nx, int ny, int nz, double* part, Scalars* sc, unsigned* np, bool box,
+                   const CgFold& fold) {
     const unsigned npair = (unsigned)(nx / 2) * ny * nz;
     const unsigned nb = cg_blocks(npair);
-    if (box)
-        hipLaunchKernelGGL((k_cg_dir<T, true>), dim3(nb), dim3(kBlock), 0, st, z0, z1, po, pn, q, x, alpha, s, nx, ny,
-                           nz, npair, part, sc);
-    else
-        hipLaunchKernelGGL((k_cg_dir<T, false>), dim3(nb), dim3(kBlock), 0, st, z0, z1, po, pn, q, x, alpha, s, nx, ny,
-                           nz, npair, part, sc);
+    const auto k = box ? (fold.np ? k_cg_dir<T, true, true> : k_cg_dir<T, true, false>)
+                       : (fold.np ? k_cg_dir<T, false, true> : k_cg_dir<T, false, false>);
+    hipLaunchKernelGGL(k, dim3(nb), dim3(kBlock), 0, st, z0, z1, po, pn, q, x, alpha, s, nx, ny, nz, npair, part, sc,
+                       fold);
     *np = nb;
 }
 template void launch_cg_dir<float>(hipStream_t, const float*, const float*, const double*, double*, double*, double*,
-                                   double, double, int, int, int, double*, const Scalars*, unsigned*, bool);
+                                   double, double, int, int, int, double*, Scalars*, unsigned*, bool, const CgFold&);
 template void launch_cg_dir<double>(hipStream_t, const double*, const double*, const double*, double*, double*,
-                                    double*, double, double, int, int, int, double*, const Scalars*, unsigned*, bool);
+                                    double*, double, double, int, int, int, double*, Scalars*, unsigned*, bool,
+                                    const CgFold&);
 
 // The steps of x that no further direction applies: iterations sc->xsteps .. sc->iters - 1
 // (at most two).
@@ -391,23 +499,55 @@ __device__ __forceinline__ void update2_enter_body(double* __restrict__ r, const
     block_partials<2>(v, part, blk.nb, blk.b);
 }
 
-template <typename T>
+// alpha and the removed mean for an update (false: CG has broken down): folded as in k_cg_dir.
+template <bool FOLD>
+__device__ __forceinline__ bool cg_fold_alpha(const CgFold& fold, Scalars* sc, double& alpha, double& mean) {
+    if (!FOLD) {
+        alpha = sc->alpha;
+        mean = sc->mean_next;
+        return true;
+    }
+    double t[2];
+    fold_partials<2>(fold, t);
+    if (fold.na) {
+        const double *na = fold.na, *nb = fold.nb;
+        double b[2];
+        fold_sums<2>((unsigned)fold.n, [=](unsigned i, double (&v)[2]) {
+            const double y = nb[i];
+            v[0] = fma(na[i], y, v[0]);
+            v[1] += y;
+        }, b);
+        t[0] = fma(fold.inv_h3, b[0], t[0]);
+        t[1] = fma(fold.inv_h3, b[1], t[1]);
+    }
+    const CgAlpha c = cg_alpha(t[0], t[1], sc);
+    if (blockIdx.x == 0 && threadIdx.x == 0) cg_alpha_store(c, t[0], t[1], sc);
+    alpha = c.alpha;
+    mean = c.mean;
+    return !c.bad;
+}
+
+template <typename T, bool FOLD>
 __global__ void __launch_bounds__(kBlock) k_update2_enter(double* __restrict__ r, const double* __restrict__ q,
                                                           T* __restrict__ f0, T* __restrict__ f1, T* __restrict__ u0,
                                                           int nx, int ny, unsigned npair, double inv_diag,
-                                                          double* part, const Scalars* sc) {
+                                                          double* part, Scalars* sc, CgFold fold) {
     if (sc->done) return;
-    update2_enter_body<T>(r, q, f0, f1, u0, nx, ny, npair, inv_diag, sc->alpha, sc->mean_next, part, Blk{blockIdx.x, gridDim.x});
+    double a, m;
+    if (!cg_fold_alpha<FOLD>(fold, sc, a, m)) return;
+    update2_enter_body<T>(r, q, f0, f1, u0, nx, ny, npair, inv_diag, a, m, part, Blk{blockIdx.x, gridDim.x});
 }
 
-template <typename T>
+template <typename T, bool FOLD>
 __global__ void __launch_bounds__(kBlock) k_update2_enter_box(double* __restrict__ r, const double* __restrict__ q,
                                                               T* __restrict__ f0,
                                                               T* __restrict__ f1, T* __restrict__ u0, int nx, int ny,
                                                               int nz, unsigned npair, BoxCoef binv, double* part,
-                                                              const Scalars* sc) {
+                                                              Scalars* sc, CgFold fold) {
     if (sc->done) return;
-    update2_enter_body<T, true>(r, q, f0, f1, u0, nx, ny, npair, 0.0, sc->alpha, sc->mean_next,
+    double a, m;
+    if (!cg_fold_alpha<FOLD>(fold, sc, a, m)) return;
+    update2_enter_body<T, true>(r, q, f0, f1, u0, nx, ny, npair, 0.0, a, m,
                                 part, Blk{blockIdx.x, gridDim.x}, nz, binv);
 }
 
@@ -427,24 +567,26 @@ __global__ void __launch_bounds__(kBlock) kb_update2_enter(const InstDev* inst, 
 
 template <typename T>
 void launch_update2_enter(hipStream_t st, double* r, const double* q, T* f0, T* f1, T* u0,
-                          int nx, int ny, int nz, double inv_diag, double* part, const Scalars* sc, unsigned* np,
-                          const BoxCoef* box_inv) {
+                          int nx, int ny, int nz, double inv_diag, double* part, Scalars* sc, unsigned* np,
+                          const BoxCoef* box_inv, const CgFold& fold) {
     const unsigned npair = (unsigned)(nx / 2) * ny * nz;
     const unsigned nb = cg_blocks(npair);
-    if (box_inv)
-        hipLaunchKernelGGL(k_update2_enter_box<T>, dim3(nb), dim3(kBlock), 0, st, r, q, f0, f1, u0, nx, ny, nz,
-                           npair, *box_inv, part, sc);
-    else
-        hipLaunchKernelGGL(k_update2_enter<T>, dim3(nb), dim3(kBlock), 0, st, r, q, f0, f1, u0, nx, ny, npair,
-                           inv_diag, part, sc);
+    if (box_inv) {
+        const auto k = fold.np ? k_update2_enter_box<T, true> : k_update2_enter_box<T, false>;
+        hipLaunchKernelGGL(k, dim3(nb), dim3(kBlock), 0, st, r, q, f0, f1, u0, nx, ny, nz, npair, *box_inv, part, sc,
+                           fold);
+    } else {
+        const auto k = fold.np ? k_update2_enter<T, true> : k_update2_enter<T, false>;
+        hipLaunchKernelGGL(k, dim3(nb), dim3(kBlock), 0, st, r, q, f0, f1, u0, nx, ny, npair, inv_diag, part, sc, fold);
+    }
     *np = nb;
 }
 template void launch_update2_enter<float>(hipStream_t, double*, const double*, float*, float*,
-                                          float*, int, int, int, double, double*, const Scalars*, unsigned*,
-                                          const BoxCoef*);
+                                          float*, int, int, int, double, double*, Scalars*, unsigned*,
+                                          const BoxCoef*, const CgFold&);
 template void launch_update2_enter<double>(hipStream_t, double*, const double*, double*,
-                                           double*, double*, int, int, int, double, double*, const Scalars*,
-                                           unsigned*, const BoxCoef*);
+                                           double*, double*, int, int, int, double, double*, Scalars*,
+                                           unsigned*, const BoxCoef*, const CgFold&);
 
 // partials (sum z, z.r, z.q), two cells per thread
 template <typename T>
@@ -771,8 +913,6 @@ __device__ __forceinline__ double fin_sum(const double* __restrict__ p, unsigned
     return s[0];
 }
 
-__device__ __forceinline__ bool is_finite_d(double v) { return v == v && v - v == 0.0; }
-
 __device__ __forceinline__ void fin_body(int kind, const double* __restrict__ part, unsigned np, Scalars* sc,
                                          const double* __restrict__ na, const double* __restrict__ nb, int nblob,
                                          double inv_h3) {
@@ -812,31 +952,16 @@ __device__ __forceinline__ void fin_body(int kind, const double* __restrict__ pa
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
-                    b[0] += x[u] * y[u];
+                    b[0] = fma(x[u], y[u], b[0]);
                     b[1] += y[u];
                 }
             }
             wg_sums<2>(b);
             const double ta = b[0], tc = b[1];
-            pq += inv_h3 * ta;
-            qs += inv_h3 * tc;
+            pq = fma(inv_h3, ta, pq);
+            qs = fma(inv_h3, tc, qs);
         }
-        if (threadIdx.x == 0) {
-            sc->pq = pq;
-            sc->qsum = qs;
-            sc->mean_next = 0.0;
-            sc->xsteps = sc->iters & ~1;  // the direction's launch has applied these
-            if (!(pq > 0.0) || !is_finite_d(pq) || !is_finite_d(sc->rz)) {
-                sc->status = 1;
-                sc->done = 1;
-                sc->alpha = 0.0;
-            } else {
-                sc->alpha = sc->rz / pq;
-                sc->step[sc->iters & 1] = sc->alpha;
-                // sum(r - alpha q) = sum r - alpha sum q: the mean the fused update removes
-                if (sc->project) sc->mean_next = (sc->rsum - sc->alpha * qs) * sc->inv_ncell;
-            }
-        }
+        if (threadIdx.x == 0) cg_alpha_store(cg_alpha(pq, qs, sc), pq, qs, sc);
     } else if (kind == FIN_UPDATE) {
         double t[2];
         fin_sums<2>(part, np, t);
@@ -856,23 +981,7 @@ __device__ __forceinline__ void fin_body(int kind, const double* __restrict__ pa
     } else {  // FIN_BETA
         double t[3];
         fin_sums<3>(part, np, t);
-        const double zs = t[0], zr = t[1], zq = t[2];
-        if (threadIdx.x == 0) {
-            const double shift = sc->project ? (sc->rsum * sc->eBe_inv - zs * sc->inv_ncell) : 0.0;
-            const double rz_new = zr + shift * sc->rsum;
-            const double zq_full = zq + shift * sc->qsum;
-            sc->shift = shift;
-            if (sc->iters == 0) {
-                sc->beta = 0.0;
-            } else {
-                sc->beta = -sc->alpha * zq_full / sc->rz;
-            }
-            sc->rz = rz_new;
-            if (!is_finite_d(rz_new) || !is_finite_d(sc->beta)) {
-                sc->status = 1;
-                sc->done = 1;
-            }
-        }
+        if (threadIdx.x == 0) cg_beta_store(cg_beta(t[0], t[1], t[2], sc), sc);
     }
 }
 

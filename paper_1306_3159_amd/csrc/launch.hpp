@@ -25,19 +25,20 @@ void launch_residual_from_q(hipStream_t st, const double* g, const double* q0, d
 void launch_applyA2(hipStream_t st, const double* p, double* q, double alpha, double s, int nx, int ny, int nz,
                     double* part, const Scalars* sc, unsigned* nparts_out, bool box = false);
 // pn = z + shift + beta po (z split, level-0 layout of type T) ; q = A pn with partials
-// (pn.q, sum q) ; every second iteration the last two steps of x. The scalars are read from sc.
+// (pn.q, sum q) ; every second iteration the last two steps of x. The scalars are read from sc,
+// beta and shift formed from the last cycle's dots where fold has them.
 template <typename T>
 void launch_cg_dir(hipStream_t st, const T* z0, const T* z1, const double* po, double* pn, double* q, double* x,
-                   double alpha, double s, int nx, int ny, int nz, double* part, const Scalars* sc,
-                   unsigned* nparts_out, bool box);
+                   double alpha, double s, int nx, int ny, int nz, double* part, Scalars* sc,
+                   unsigned* nparts_out, bool box, const CgFold& fold);
 // the steps of x left when the iterations end (p0, p1: directions of even and odd iterations)
 void launch_cg_last(hipStream_t st, double* x, const double* p0, const double* p1, size_t ncell, const Scalars* sc);
 // r -= alpha q with partials (r.r, sum r), and the V-cycle entry of
 // the new r (f split, first red sweep u0); box_inv: per-face-count inverse
 // diagonals of a box with fixed faces (inv_diag unused)
 template <typename T>
-void launch_update2_enter(hipStream_t st, double* r, const double* q, T* f0, T* f1, T* u0, int nx, int ny, int nz, double inv_diag, double* part, const Scalars* sc,
-                          unsigned* nparts_out, const BoxCoef* box_inv = nullptr);
+void launch_update2_enter(hipStream_t st, double* r, const double* q, T* f0, T* f1, T* u0, int nx, int ny, int nz, double inv_diag, double* part, Scalars* sc,
+                          unsigned* nparts_out, const BoxCoef* box_inv, const CgFold& fold);
 // partials (sum z, z.r, z.q) with z split of type T
 template <typename T>
 void launch_zdots2(hipStream_t st, const T* z0, const T* z1, const double* r, const double* q, int nx, int ny, int nz,

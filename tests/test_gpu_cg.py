@@ -39,3 +39,29 @@ def test_solution_holds_every_step(shape, prec, box):
             counts.add(st["outer_iters"])
         S.close()
     assert {k % 2 for k in counts} == {0, 1}, counts
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("n,blobs", [(32, 1), (32, 64), (32, 1025), (64, 2048), (64, 2049)])
+def test_sums_formed_by_the_next_pass(n, blobs, prec):
+    """A solve alone lets CG's vector passes finish the reductions before them (up to 512 blocks, 2048
+    blobs), a batch's rounds finish them in their own launches: the same bits either way."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1306_3159_amd import Batch, BlobRD
+    print("[case] CG sums", n, blobs, prec, flush=True)
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(9)
+    shape = (n, n, n)
+    f = torch.as_tensor(1.0 + 0.5 * rng.standard_normal(shape), device=dev)
+    q = torch.as_tensor(rng.uniform(0.0, n, (blobs, 3)), device=dev)
+    kappa = torch.as_tensor(rng.uniform(0.5, 2.0, blobs), device=dev)
+    S = BlobRD(shape, q, kappa, precision=prec, rtol=1e-8)
+    alone, st = S.solve_reactive(f)
+    S.close()
+    assert st["rc"] == 0
+    spec = dict(shape=shape, q=q, kappa=kappa, precision=prec, rtol=1e-8, kind=0)
+    B = Batch([spec, spec])
+    c = [torch.zeros_like(f), torch.zeros_like(f)]
+    B.solve([f, f], c, [None, None])
+    assert torch.equal(c[0], alone) and torch.equal(c[1], alone)
