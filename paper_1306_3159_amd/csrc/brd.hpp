@@ -18,6 +18,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "cg_scalars.hpp"
+
 namespace brd {
 
 constexpr int kBlock = 256;
@@ -30,34 +32,6 @@ constexpr int kTailDense = 64;       // coarsest cells up to which its inverse i
 constexpr int kMaxCoarseCols = 256;  // columns of the Schur preconditioner's Fourier coarse level
 constexpr int kCoarseChunk = 2048;   // rows per work-group in the coarse level's dot products
 constexpr int kStageBlobs = 128;   // candidate blobs staged in LDS per pass of the spread planner
-
-// Device-resident scalars of one CG solve. Every kernel of an iteration reads
-// `done` first and returns if it is set, so the host can enqueue iterations
-// without waiting for convergence.
-struct Scalars {
-    double pq;        // p . B p
-    double alpha;     // CG step
-    double beta;      // CG direction update (Polak-Ribiere form)
-    double rr;        // r . r
-    double rsum;      // sum r
-    double qsum;      // sum q
-    double tol2;      // stop when rr <= tol2
-    double shift;     // constant added to the V-cycle output z (null-space handling)
-    double mean_r;    // mean removed from r before the V-cycle (projected problems)
-    double mean_next; // mean of the next r predicted from sum r and sum q (fused update + V-cycle entry)
-    double inv_ncell; // 1 / (nx ny nz)
-    double eBe_inv;   // 1 / (e^T B e) for the reactive alpha = 0 constant mode (0 otherwise)
-    double rr0;       // r . r of the initial residual
-    double gg;        // right-hand side g . g
-    int32_t done;     // 1: converged (or failed); kernels become no-ops
-    int32_t iters;    // completed CG iterations
-    int32_t project;  // 1: alpha = 0 problem, work on mean-zero vectors
-    int32_t status;   // 0 ok, 1 breakdown/non-finite
-    int32_t xzero;    // 1: x starts at zero and its first step writes it (no prior fill)
-    int32_t xsteps;   // iterations whose steps x holds
-    double rz[2];     // z . r (with the constant shift) of the last two iterates (iteration k: rz[k & 1])
-    double step[2];   // CG steps of the last two iterations (iteration k: step[k & 1])
-};
 
 // A reduction of CG that a vector pass finishes itself (np = 0: done before it): np partials a
 // set at `in`; alpha's: the blob term's vectors Jp (na) and mu (nb) of length n.

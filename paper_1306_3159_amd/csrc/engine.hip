@@ -542,6 +542,7 @@ __global__ void k_sc_init(Scalars* sc, int project, double inv_ncell, double eBe
     sc->iters = 0;
     sc->project = project;
     sc->status = 0;
+    sc->halt[0] = sc->halt[1] = 0;
 }
 
 void sync_read(blob_rd* H, void* host, const void* dev, size_t bytes) {

@@ -68,64 +68,6 @@ void launch_applyA(hipStream_t st, const double* p, double* q, double alpha, dou
 
 typedef double double2_t __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ bool is_finite_d(double v) { return v == v && v - v == 0.0; }
-
-// The CG step from p.q and sum q, with its roundings fixed (formed by the finalize kernel or by
-// every block of the update). sum(r - alpha q) = sum r - alpha sum q: the mean the fused update
-// removes.
-struct CgAlpha {
-    double alpha, mean;
-    bool bad;
-};
-__device__ __forceinline__ CgAlpha cg_alpha(double pq, double qs, const Scalars* sc) {
-#pragma clang fp contract(off)
-    const double rz = sc->rz[sc->iters & 1];
-    CgAlpha c{0.0, 0.0, !(pq > 0.0) || !is_finite_d(pq) || !is_finite_d(rz)};
-    if (!c.bad) {
-        c.alpha = rz / pq;
-        if (sc->project) c.mean = fma(-c.alpha, qs, sc->rsum) * sc->inv_ncell;
-    }
-    return c;
-}
-__device__ __forceinline__ void cg_alpha_store(const CgAlpha& c, double pq, double qs, Scalars* sc) {
-    sc->pq = pq;
-    sc->qsum = qs;
-    sc->mean_next = c.mean;
-    sc->alpha = c.alpha;
-    sc->xsteps = sc->iters & ~1;  // the direction's launch has applied these
-    if (c.bad) {
-        sc->status = 1;
-        sc->done = 1;
-    } else {
-        sc->step[sc->iters & 1] = c.alpha;
-    }
-}
-
-// The direction's scalars from sum z, z.r and z.q, likewise (Polak-Ribiere form).
-struct CgBeta {
-    double shift, rz, beta;
-    bool bad;
-};
-__device__ __forceinline__ CgBeta cg_beta(double zs, double zr, double zq, const Scalars* sc) {
-#pragma clang fp contract(off)
-    CgBeta c;
-    c.shift = sc->project ? fma(sc->rsum, sc->eBe_inv, -(zs * sc->inv_ncell)) : 0.0;
-    c.rz = fma(c.shift, sc->rsum, zr);
-    const double zq_full = fma(c.shift, sc->qsum, zq);
-    c.beta = sc->iters == 0 ? 0.0 : -sc->alpha * zq_full / sc->rz[(sc->iters & 1) ^ 1];
-    c.bad = !is_finite_d(c.rz) || !is_finite_d(c.beta);
-    return c;
-}
-__device__ __forceinline__ void cg_beta_store(const CgBeta& c, Scalars* sc) {
-    sc->shift = c.shift;
-    sc->beta = c.beta;
-    sc->rz[sc->iters & 1] = c.rz;
-    if (c.bad) {
-        sc->status = 1;
-        sc->done = 1;
-    }
-}
-
 // Sums of K values per index i < n (at(i, v) adds index i's to v) by kBlock threads, in the order
 // of the finalize kernel's kFinBlock: each wave stands for four of its waves.
 template <int K, typename At>
@@ -382,15 +324,15 @@ __global__ void __launch_bounds__(kBlock) k_cg_dir(const T* __restrict__ z0, con
                                                    double* __restrict__ q, double* __restrict__ x, double alpha,
                                                    double s, int nx, int ny, int nz, unsigned npair, double* part,
                                                    Scalars* sc, CgFold fold) {
-    if (sc->done) return;
+    if (!cg_dir_runs(sc)) return;
     double beta = 0.0, shift = 0.0;
     if (FOLD) {
         // every block forms beta; the first stores it, in fields that no block of this launch reads
-        // (rz of this iteration beside that of the last)
+        // (rz of this iteration beside that of the last; a breakdown in halt, not in done)
         double t[3];
         fold_partials<3>(fold, t);
         const CgBeta c = cg_beta(t[0], t[1], t[2], sc);
-        if (blockIdx.x == 0 && threadIdx.x == 0) cg_beta_store(c, sc);
+        if (blockIdx.x == 0 && threadIdx.x == 0) cg_beta_store(c, sc, true);
         if (c.bad) return;
         beta = c.beta;
         shift = c.shift;
@@ -521,7 +463,7 @@ __device__ __forceinline__ bool cg_fold_alpha(const CgFold& fold, Scalars* sc, d
         t[1] = fma(fold.inv_h3, b[1], t[1]);
     }
     const CgAlpha c = cg_alpha(t[0], t[1], sc);
-    if (blockIdx.x == 0 && threadIdx.x == 0) cg_alpha_store(c, t[0], t[1], sc);
+    if (blockIdx.x == 0 && threadIdx.x == 0) cg_alpha_store(c, t[0], t[1], sc, true);
     alpha = c.alpha;
     mean = c.mean;
     return !c.bad;
@@ -532,7 +474,7 @@ __global__ void __launch_bounds__(kBlock) k_update2_enter(double* __restrict__ r
                                                           T* __restrict__ f0, T* __restrict__ f1, T* __restrict__ u0,
                                                           int nx, int ny, unsigned npair, double inv_diag,
                                                           double* part, Scalars* sc, CgFold fold) {
-    if (sc->done) return;
+    if (!cg_update_runs(sc)) return;
     double a, m;
     if (!cg_fold_alpha<FOLD>(fold, sc, a, m)) return;
     update2_enter_body<T>(r, q, f0, f1, u0, nx, ny, npair, inv_diag, a, m, part, Blk{blockIdx.x, gridDim.x});
@@ -544,7 +486,7 @@ __global__ void __launch_bounds__(kBlock) k_update2_enter_box(double* __restrict
                                                               T* __restrict__ f1, T* __restrict__ u0, int nx, int ny,
                                                               int nz, unsigned npair, BoxCoef binv, double* part,
                                                               Scalars* sc, CgFold fold) {
-    if (sc->done) return;
+    if (!cg_update_runs(sc)) return;
     double a, m;
     if (!cg_fold_alpha<FOLD>(fold, sc, a, m)) return;
     update2_enter_body<T, true>(r, q, f0, f1, u0, nx, ny, npair, 0.0, a, m,
@@ -961,7 +903,7 @@ __device__ __forceinline__ void fin_body(int kind, const double* __restrict__ pa
             pq = fma(inv_h3, ta, pq);
             qs = fma(inv_h3, tc, qs);
         }
-        if (threadIdx.x == 0) cg_alpha_store(cg_alpha(pq, qs, sc), pq, qs, sc);
+        if (threadIdx.x == 0) cg_alpha_store(cg_alpha(pq, qs, sc), pq, qs, sc, false);
     } else if (kind == FIN_UPDATE) {
         double t[2];
         fin_sums<2>(part, np, t);
@@ -981,14 +923,20 @@ __device__ __forceinline__ void fin_body(int kind, const double* __restrict__ pa
     } else {  // FIN_BETA
         double t[3];
         fin_sums<3>(part, np, t);
-        if (threadIdx.x == 0) cg_beta_store(cg_beta(t[0], t[1], t[2], sc), sc);
+        if (threadIdx.x == 0) cg_beta_store(cg_beta(t[0], t[1], t[2], sc), sc, false);
     }
 }
 
 __global__ void __launch_bounds__(kFinBlock) k_fin(int kind, const double* __restrict__ part, unsigned np,
                                                    Scalars* sc, const double* __restrict__ na,
                                                    const double* __restrict__ nb, int nblob, double inv_h3) {
-    if (kind != FIN_INIT && sc->done) return;
+    if (kind != FIN_INIT) {
+        if (sc->done) return;
+        if (cg_halted(sc)) {
+            if (threadIdx.x == 0) cg_stop(sc);  // waves that see done set return as well
+            return;
+        }
+    }
     fin_body(kind, part, np, sc, na, nb, nblob, inv_h3);
 }
 
