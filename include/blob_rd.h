@@ -543,8 +543,10 @@ int blob_rd_solve_batch(blob_rd_batch_t b, const double* const* f, double* const
  * evicted; the other kernels are each timed alone after >= 512 MB have been
  * streamed through the cache. avg_ms receives the mean time per launch and
  * bytes the algorithmic HBM bytes one launch must move (each input read once,
- * each output written once). On a Dirichlet-box handle the box forms of the
- * kernels are timed (same byte counts). */
+ * each output written once; for a V-cycle the sum over the launches it makes on
+ * this handle's levels, those that the coarse tail holds in LDS counted as
+ * nothing). On a Dirichlet-box handle the box forms of the kernels are timed
+ * (the same byte count where the same launches run). */
 int blob_rd_time_kernel(blob_rd_t h, int kernel, int reps, double* avg_ms, double* bytes);
 
 /* ---- Launch-shape autotuning ----

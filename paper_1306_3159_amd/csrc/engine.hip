@@ -3983,6 +3983,10 @@ int blob_rd_time_kernel(blob_rd_t H, int kernel, int reps, double* avg_ms, doubl
                     else vcycle<double>(H, alpha, H->grid(G_R), nullptr, spec);
             }
         };
+        // a V-cycle's bytes are those of the launches it made, as a solve counts them (levels in the
+        // coarse tail's LDS count nothing)
+        const double bytes0 = H->alg_bytes;
+        double cycle_bytes = 0.0;
         float ms = 0.f;
         if (cold && (kernel == BLOB_RD_KERNEL_GS || kernel == BLOB_RD_KERNEL_STENCIL ||
                      kernel == BLOB_RD_KERNEL_STREAM || kernel == BLOB_RD_KERNEL_STENCIL_PLAIN)) {
@@ -4026,6 +4030,7 @@ int blob_rd_time_kernel(blob_rd_t H, int kernel, int reps, double* avg_ms, doubl
             HIPCHK(hipEventElapsedTime(&ms, e0, e1));
         } else if (cold) {
             one();  // warm
+            cycle_bytes = H->alg_bytes - bytes0;
             // Evict the 256 MB Infinity Cache before every timed launch by streaming
             // through >= 512 MB of the workspace's FP64 scratch vectors.
             double* flush = H->grid(G_T1);
@@ -4042,6 +4047,7 @@ int blob_rd_time_kernel(blob_rd_t H, int kernel, int reps, double* avg_ms, doubl
             }
         } else {
             one();  // warm
+            cycle_bytes = H->alg_bytes - bytes0;
             HIPCHK(hipEventRecord(e0, H->st));
             for (int i = 0; i < reps; ++i) one();
             HIPCHK(hipEventRecord(e1, H->st));
@@ -4059,12 +4065,7 @@ int blob_rd_time_kernel(blob_rd_t H, int kernel, int reps, double* avg_ms, doubl
             case BLOB_RD_KERNEL_STENCIL_PLAIN: *bytes = n * 16; break;
             case BLOB_RD_KERNEL_RESTRICT: *bytes = n * e * 2.5 + n / 8 * e * 1.5; break;  // red u, black u, red f; red r write+read; coarse f, u
             case BLOB_RD_KERNEL_PROLONG: *bytes = n * e + n / 8 * e; break;  // red u read+write, coarse read
-            default: {
-                double b = 0.0;
-                for (int l = 0; l + 1 < P.nlev; ++l)
-                    b += n / (double)(1 << (3 * l)) * e * (kPreRestrictBytes + kProlongPostBytes);
-                *bytes = b + n * (8 + 1.5 * e);  // + entry: FP64 residual in, f and the first red sweep out
-            }
+            default: *bytes = cycle_bytes;
         }
         HIPCHK(hipGetLastError());
         return BLOB_RD_OK;
