@@ -412,7 +412,7 @@ struct blob_rd {
     double alg_bytes = 0.0;
     int inner_iters = 0;
     int last_iters[4] = {0, 0, 0, 0};  // CG iterations of the previous solve per (blobs, alpha == 0)
-    int tail_level[2] = {1 << 20, 1 << 20};  // first level of the LDS tail for FP32 / FP64 (>= nlev-1: none)
+    int tail_level[2] = {1 << 20, 1 << 20};  // first level of the LDS tail for FP32 / FP64 (above the coarsest)
     // Work-group size per (level, multigrid kernel): Gauss-Seidel, residual, restriction,
     // prolongation. kBlock until blob_rd_autotune picks others.
     int bs[kMaxLevels][4];
@@ -590,10 +590,11 @@ const double* select_spec(blob_rd* H, double alpha) {
 // (mean_r removed when the scalars say so); the result is left in level 0's
 // u arrays (split layout).
 // First level of the single-work-group LDS tail: the coarsest levels whose
-// u, f, r arrays fit the LDS budget together.
+// u, f, r arrays fit the LDS budget together (the tail's own layout, which keeps the first level's
+// right-hand sides and residual in registers, takes at most 89 KB for any of them).
 int tail_start(const Plan& P, size_t esz, size_t budget) {
     const int L = P.nlev - 1;
-    int t = L;  // never used as is: the tail always includes one smoothing level
+    int t = L;  // L: the budget does not hold one smoothing level (create refuses the device)
     size_t bytes = 2 * (size_t)P.m * esz + 64;
     for (int l = L - 1; l >= 0; --l) {
         const size_t c = (size_t)P.lev[l].nx * P.lev[l].ny * P.lev[l].nz;
@@ -678,7 +679,7 @@ void box_coefs(const blob_rd* H, int l, double alpha, BoxCoef* diag, BoxCoef* in
 template <typename T>
 bool fused(const blob_rd* H, int l) {
     const int t = H->tail_level[sizeof(T) == 4 ? 0 : 1];
-    return H->blocked && sizeof(T) == H->P.esz && l < t && t < H->P.nlev - 1 && H->tile[l].lanes > 0;
+    return H->blocked && sizeof(T) == H->P.esz && l < t && H->tile[l].lanes > 0;
 }
 // Level l, too large for two launches, in tiles cut on all axes: pre-smoothing, residual and
 // restriction in two launches, three post-smoothing half-sweeps in one (above the LDS tail
@@ -687,7 +688,7 @@ template <typename T>
 bool slab(const blob_rd* H, int l) {
     const int t = H->tail_level[sizeof(T) == 4 ? 0 : 1];
     const LevelDims& d = H->P.lev[l];
-    return H->blocked && sizeof(T) == H->P.esz && l < t && t < H->P.nlev - 1 && !fused<T>(H, l) &&
+    return H->blocked && sizeof(T) == H->P.esz && l < t && !fused<T>(H, l) &&
            slab_fits(d.nx, d.ny, d.nz, sizeof(T));
 }
 // Whether level l opens from its right-hand side (its first red sweep need not be stored).
@@ -749,17 +750,15 @@ bool level_up(blob_rd* H, int l, double alpha, int sweeps, const Scalars* sc) {
 }
 
 // The V-cycle of vcycle() below for the box operator alpha I - D L_0: the same
-// steps and order with the box kernels, down to the first level of the LDS tail or
-// to the coarsest level.
+// steps and order with the box kernels, down to the first level of the LDS tail.
 template <typename T>
 void vcycle_box(blob_rd* H, double alpha, const double* r, const Scalars* sc, const double* spec, bool entered) {
     const Plan& P = H->P;
-    const int L = P.nlev - 1;
-    const int t = std::min(H->tail_level[sizeof(T) == 4 ? 0 : 1], L);
+    const int t = H->tail_level[sizeof(T) == 4 ? 0 : 1];
     hipStream_t st = H->st;
     auto lv = [&](int l, int k) { return H->at<T>(P.off_lvl[l][k]); };  // 0 u0, 1 u1, 2 f0, 3 f1, 4 r0 (red)
     BoxCoef dg[kMaxLevels], inv[kMaxLevels];
-    for (int l = 0; l <= L; ++l) box_coefs(H, l, alpha, &dg[l], &inv[l]);
+    for (int l = 0; l <= t; ++l) box_coefs(H, l, alpha, &dg[l], &inv[l]);
     if (!entered) {
         const LevelDims& d = P.lev[0];
         launch_enter_box<T>(st, r, lv(0, 2), lv(0, 3), opens_from_f<T>(H, 0) ? nullptr : lv(0, 0), d.nx, d.ny, d.nz,
@@ -774,22 +773,16 @@ void vcycle_box(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
         launch_gs_box<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.nx, d.ny, d.nz, 0, s, inv[l], sc);
         launch_gs_box<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.nx, d.ny, d.nz, 1, s, inv[l], sc);
         launch_resid_red_box<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), lv(l, 4), d.nx, d.ny, d.nz, s, dg[l], sc);
-        if (l + 1 == L)
-            launch_restrict_box<T>(st, lv(l, 4), d.nx, d.ny, d.nz, lv(L, 2), nullptr, nullptr, 1, inv[L], sc);
-        else
-            launch_restrict_box<T>(st, lv(l, 4), d.nx, d.ny, d.nz, lv(l + 1, 2), lv(l + 1, 3), lv(l + 1, 0), 0,
-                                   inv[l + 1], sc);
+        launch_restrict_box<T>(st, lv(l, 4), d.nx, d.ny, d.nz, lv(l + 1, 2), lv(l + 1, 3), lv(l + 1, 0), 0,
+                               inv[l + 1], sc);
         H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kPreRestrictBytes;
     }
-    if (t < L) launch_tail<T>(st, lv(t, 2), lv(t, 3), lv(t, 0), lv(t, 1), make_tail<T>(H, t, alpha), spec, true, sc);
-    else launch_coarse<T>(st, lv(L, 2), lv(L, 0), spec, P.lev[L].nx, P.lev[L].ny, P.lev[L].nz, sc);
+    launch_tail<T>(st, lv(t, 2), lv(t, 3), lv(t, 0), lv(t, 1), make_tail<T>(H, t, alpha), spec, true, sc);
     for (int l = t - 1; l >= 0; --l) {
         const LevelDims& d = P.lev[l];
         const double s = H->prm.D / (d.h * d.h);
         if (level_up<T>(H, l, alpha, 4, sc)) continue;
-        const int cnat = (l + 1 == L);
-        launch_prolong_red_box<T>(st, lv(l + 1, 0), cnat ? nullptr : lv(l + 1, 1), cnat, lv(l, 0), d.nx, d.ny, d.nz,
-                                  sc);
+        launch_prolong_red_box<T>(st, lv(l + 1, 0), lv(l + 1, 1), 0, lv(l, 0), d.nx, d.ny, d.nz, sc);
         if (!slab_sweeps<T>(H, l, alpha, sc)) {
             launch_gs_box<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.nx, d.ny, d.nz, 1, s, inv[l], sc);
             launch_gs_box<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.nx, d.ny, d.nz, 0, s, inv[l], sc);
@@ -813,7 +806,6 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
         return 0;
     }
     const Plan& P = H->P;
-    const int L = P.nlev - 1;
     hipStream_t st = H->st;
     auto lv = [&](int l, int k) { return H->at<T>(P.off_lvl[l][k]); };  // 0 u0, 1 u1, 2 f0, 3 f1, 4 r0 (red)
     const double D = H->prm.D;
@@ -849,79 +841,43 @@ unsigned vcycle(blob_rd* H, double alpha, const double* r, const Scalars* sc, co
                         1.0 / (alpha + 6.0 * s), sc);
         H->alg_bytes += (double)P.ncell * (8 + P.esz * (no_u ? 1.0 : 1.5));
     }
-    if (t < L) {
-        for (int l = 0; l < t; ++l) {
-            const LevelDims& d = P.lev[l];
-            const double s = D / (d.h * d.h), diag = alpha + 6.0 * s;
-            if (level_down<T>(H, l, t, alpha, sc) || slab_down<T>(H, l, t, alpha, sc)) continue;
-            const int* b = H->bs[l];
-            first_black(l, s, diag, b);
-            launch_gs<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.hx, d.ny, d.nz, 0, s, 1.0 / diag, sc, b[0]);
-            launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
-            launch_resid_red<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), lv(l, 4), d.hx, d.ny, d.nz, s, diag, sc, b[1]);
-            const LevelDims& c = P.lev[l + 1];
-            const double sc_ = D / (c.h * c.h);
-            launch_restrict<T>(st, lv(l, 4), d.nx, d.ny, d.nz, lv(l + 1, 2), lv(l + 1, 3), lv(l + 1, 0), 0,
-                               1.0 / (alpha + 6.0 * sc_), sc, b[2]);
-            H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kPreRestrictBytes;
-        }
-        const TailDesc td = make_tail<T>(H, t, alpha);
-        launch_tail<T>(st, lv(t, 2), lv(t, 3), lv(t, 0), lv(t, 1), td, spec, false, sc);
-        for (int l = t - 1; l >= 0; --l) {
-            const LevelDims& d = P.lev[l];
-            const double s = D / (d.h * d.h), diag = alpha + 6.0 * s;
-            if (fused<T>(H, l)) {
-                // with the CG dots the closing red sweep keeps its own launch, which forms them
-                const bool dots = l == 0 && dot_q && sc && d.hx % (16 / (int)sizeof(T)) == 0;
-                level_up<T>(H, l, alpha, dots ? 3 : 4, sc);
-                if (dots) {
-                    last_red(l, s, diag, H->bs[l]);
-                    H->alg_bytes += (double)P.ncell * P.esz * 1.5;
-                }
-                continue;
-            }
-            const int* b = H->bs[l];
-            launch_prolong<T>(st, lv(l + 1, 0), lv(l + 1, 1), 0, lv(l, 0), lv(l, 1), d.nx, d.ny, d.nz, sc, b[3]);
-            if (!slab_sweeps<T>(H, l, alpha, sc)) {
-                launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
-                launch_gs<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.hx, d.ny, d.nz, 0, s, 1.0 / diag, sc, b[0]);
-                launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
-            }
-            last_red(l, s, diag, b);
-            H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kProlongPostBytes;
-        }
-        H->vcycles += 1;
-        return ndots;
-    }
-    for (int l = 0; l < L; ++l) {
+    for (int l = 0; l < t; ++l) {
         const LevelDims& d = P.lev[l];
         const double s = D / (d.h * d.h), diag = alpha + 6.0 * s;
+        if (level_down<T>(H, l, t, alpha, sc) || slab_down<T>(H, l, t, alpha, sc)) continue;
         const int* b = H->bs[l];
         first_black(l, s, diag, b);
         launch_gs<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.hx, d.ny, d.nz, 0, s, 1.0 / diag, sc, b[0]);
         launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
         launch_resid_red<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), lv(l, 4), d.hx, d.ny, d.nz, s, diag, sc, b[1]);
-        const int cnat = (l + 1 == L);
         const LevelDims& c = P.lev[l + 1];
         const double sc_ = D / (c.h * c.h);
-        if (cnat)
-            launch_restrict<T>(st, lv(l, 4), d.nx, d.ny, d.nz, lv(L, 2), nullptr, nullptr, 1, 0.0, sc, b[2]);
-        else
-            launch_restrict<T>(st, lv(l, 4), d.nx, d.ny, d.nz, lv(l + 1, 2), lv(l + 1, 3), lv(l + 1, 0), 0,
-                               1.0 / (alpha + 6.0 * sc_), sc, b[2]);
+        launch_restrict<T>(st, lv(l, 4), d.nx, d.ny, d.nz, lv(l + 1, 2), lv(l + 1, 3), lv(l + 1, 0), 0,
+                           1.0 / (alpha + 6.0 * sc_), sc, b[2]);
         H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kPreRestrictBytes;
     }
-    launch_coarse<T>(st, lv(L, 2), lv(L, 0), spec, P.lev[L].nx, P.lev[L].ny, P.lev[L].nz, sc);
-    for (int l = L - 1; l >= 0; --l) {
+    const TailDesc td = make_tail<T>(H, t, alpha);
+    launch_tail<T>(st, lv(t, 2), lv(t, 3), lv(t, 0), lv(t, 1), td, spec, false, sc);
+    for (int l = t - 1; l >= 0; --l) {
         const LevelDims& d = P.lev[l];
         const double s = D / (d.h * d.h), diag = alpha + 6.0 * s;
-        const int cnat = (l + 1 == L);
+        if (fused<T>(H, l)) {
+            // with the CG dots the closing red sweep keeps its own launch, which forms them
+            const bool dots = l == 0 && dot_q && sc && d.hx % (16 / (int)sizeof(T)) == 0;
+            level_up<T>(H, l, alpha, dots ? 3 : 4, sc);
+            if (dots) {
+                last_red(l, s, diag, H->bs[l]);
+                H->alg_bytes += (double)P.ncell * P.esz * 1.5;
+            }
+            continue;
+        }
         const int* b = H->bs[l];
-        launch_prolong<T>(st, lv(l + 1, 0), cnat ? nullptr : lv(l + 1, 1), cnat, lv(l, 0), lv(l, 1), d.nx, d.ny, d.nz,
-                          sc, b[3]);
-        launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
-        launch_gs<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.hx, d.ny, d.nz, 0, s, 1.0 / diag, sc, b[0]);
-        launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
+        launch_prolong<T>(st, lv(l + 1, 0), lv(l + 1, 1), 0, lv(l, 0), lv(l, 1), d.nx, d.ny, d.nz, sc, b[3]);
+        if (!slab_sweeps<T>(H, l, alpha, sc)) {
+            launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
+            launch_gs<T>(st, lv(l, 0), lv(l, 1), lv(l, 2), d.hx, d.ny, d.nz, 0, s, 1.0 / diag, sc, b[0]);
+            launch_gs<T>(st, lv(l, 1), lv(l, 0), lv(l, 3), d.hx, d.ny, d.nz, 1, s, 1.0 / diag, sc, b[0]);
+        }
         last_red(l, s, diag, b);
         H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * kProlongPostBytes;
     }
@@ -937,7 +893,7 @@ bool cycle_opens_from_f(const blob_rd* H);
 template <typename T>
 unsigned dots_partials(const blob_rd* H) {
     const LevelDims& d = H->P.lev[0];
-    const int VW = 16 / (int)sizeof(T), t = std::min(H->tail_level[sizeof(T) == 4 ? 0 : 1], H->P.nlev - 1);
+    const int VW = 16 / (int)sizeof(T), t = H->tail_level[sizeof(T) == 4 ? 0 : 1];
     if (H->box || t == 0 || d.hx % VW != 0 || d.hx < VW) return red_blocks(H->P.ncell / 2);
     return nblocks((size_t)(d.hx / VW) * d.ny * d.nz);
 }
@@ -996,8 +952,7 @@ double cg_vector_bytes(size_t esz, bool from_f) { return esz + 24 + 12 + 24 + (f
 // V-cycle entry, V-cycle with the fused dots).
 double iteration_bytes(const blob_rd* H) {
     const Plan& P = H->P;
-    const int L = P.nlev - 1;
-    const int t = std::min(H->tail_level[P.esz == 4 ? 0 : 1], L);
+    const int t = H->tail_level[P.esz == 4 ? 0 : 1];
     double b = (double)P.ncell * cg_vector_bytes(P.esz, false) + (double)P.ncell * 16;
     for (int l = 0; l < t; ++l) b += (double)P.ncell / (1 << (3 * l)) * P.esz * (kPreRestrictBytes + kProlongPostBytes);
     return b;
@@ -1750,7 +1705,7 @@ void fg_resid(blob_rd* H, double alpha, const double* base, const SpreadMult* M,
 template <typename T>
 bool cycle_opens_from_f(const blob_rd* H) {
     const Plan& P = H->P;
-    const int t0 = std::min(H->tail_level[sizeof(T) == 4 ? 0 : 1], P.nlev - 1);
+    const int t0 = H->tail_level[sizeof(T) == 4 ? 0 : 1];
     const int vw = 16 / (int)sizeof(T);
     if (H->batch && H->batch_v) return false;
     return opens_from_f<T>(H, 0) || (!H->box && (t0 == 0 || (P.lev[0].hx % vw == 0 && P.lev[0].hx >= vw)));
@@ -1777,7 +1732,7 @@ void fg_vcycle(blob_rd* H, double alpha, const double* r, const double* spec, bo
         H->alg_bytes += (double)P.ncell * (8 + P.esz * 1.5);
     }
     batch_run_vcycle(H);
-    const int t = std::min(H->tail_level[P.esz == 4 ? 0 : 1], P.nlev - 1);
+    const int t = H->tail_level[P.esz == 4 ? 0 : 1];
     for (int l = 0; l < t; ++l)
         H->alg_bytes += (double)P.ncell / (1 << (3 * l)) * P.esz * (kPreRestrictBytes + kProlongPostBytes);
     H->vcycles += 1;
@@ -2484,6 +2439,9 @@ int blob_rd_create(const blob_rd_params* p, blob_rd_t* out) {
         const size_t budget = std::min<size_t>((size_t)lds, 160 * 1024);
         H->tail_level[0] = tail_start(P, 4, budget);
         H->tail_level[1] = tail_start(P, 8, budget);
+        // 160 KiB hold the last two levels of every grid (at most 512 and 4096 cells: 106 KB)
+        if (std::max(H->tail_level[0], H->tail_level[1]) >= P.nlev - 1)
+            throw Err(BLOB_RD_EDEVICE, "the device's LDS per work-group is too small for the multigrid's coarse end");
         set_lds_limits(budget);
         if (H->blocked) {
             for (int l = 0; l + 1 < P.nlev; ++l)
@@ -2779,12 +2737,11 @@ void zero_levels(blob_rd* H) {
     HIPCHK(hipMemsetAsync(H->ws + P.off_lvl[L][2], 0, (size_t)P.m * P.esz, H->st));
 }
 
-// Levels above the LDS tail or the coarse solve.
-int tuned_levels(const blob_rd* H) {
-    const int L = H->P.nlev - 1;
-    const int t = H->tail_level[H->P.esz == 4 ? 0 : 1];
-    return std::max(0, std::min(t, L));
-}
+// Levels above the LDS tail. The work-group sizes hold for their per-step launches: all of them with
+// BLOB_RD_BLOCKED=0 and on levels that are neither fused nor in tiles (rows that are no whole vectors);
+// the correction and, below the finest level, the closing half-sweep of a level in tiles; none of a
+// fused level. The autotuner times every entry all the same, so that a table holds in either mode.
+int tuned_levels(const blob_rd* H) { return H->tail_level[H->P.esz == 4 ? 0 : 1]; }
 
 const char* const kTuneKind[BLOB_RD_TUNE_KINDS] = {"gs", "resid", "restrict", "prolong"};
 const int kTuneCand[4] = {64, 128, 256, 512};
@@ -2793,9 +2750,6 @@ const int kTuneCand[4] = {64, 128, 256, 512};
 template <typename T>
 void tune_launch(blob_rd* H, int l, int kind, int bs) {
     const Plan& P = H->P;
-    const int L = P.nlev - 1;
-    const bool tail = H->tail_level[sizeof(T) == 4 ? 0 : 1] < L;
-    const int cnat = (!tail && l + 1 == L);
     auto lv = [&](int ll, int k) { return H->at<T>(P.off_lvl[ll][k]); };
     const LevelDims& d = P.lev[l];
     const double s = H->prm.D / (d.h * d.h), diag = 6.0 * s;
@@ -2806,13 +2760,12 @@ void tune_launch(blob_rd* H, int l, int kind, int bs) {
             break;
         case 2: {
             const LevelDims& c = P.lev[l + 1];
-            launch_restrict<T>(H->st, lv(l, 4), d.nx, d.ny, d.nz, lv(l + 1, 2), cnat ? nullptr : lv(l + 1, 3),
-                               cnat ? nullptr : lv(l + 1, 0), cnat, 1.0 / (6.0 * H->prm.D / (c.h * c.h)), nullptr, bs);
+            launch_restrict<T>(H->st, lv(l, 4), d.nx, d.ny, d.nz, lv(l + 1, 2), lv(l + 1, 3),
+                               lv(l + 1, 0), 0, 1.0 / (6.0 * H->prm.D / (c.h * c.h)), nullptr, bs);
             break;
         }
         default:
-            launch_prolong<T>(H->st, lv(l + 1, 0), cnat ? nullptr : lv(l + 1, 1), cnat, lv(l, 0), lv(l, 1), d.nx, d.ny,
-                              d.nz, nullptr, bs);
+            launch_prolong<T>(H->st, lv(l + 1, 0), lv(l + 1, 1), 0, lv(l, 0), lv(l, 1), d.nx, d.ny, d.nz, nullptr, bs);
     }
 }
 

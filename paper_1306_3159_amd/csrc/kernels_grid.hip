@@ -58,14 +58,6 @@ __global__ void __launch_bounds__(kBlock) k_applyA(const double* __restrict__ p,
     if (part) block_partials<2>(v, part, gridDim.x, blockIdx.x);
 }
 
-void launch_applyA(hipStream_t st, const double* p, double* q, double alpha, double s, int nx, int ny, int nz,
-                   double* part, const Scalars* sc, unsigned* np) {
-    const unsigned n = (unsigned)nx * ny * nz;
-    const unsigned nb = part ? red_blocks(n) : nblocks(n);
-    hipLaunchKernelGGL(k_applyA<false>, dim3(nb), dim3(kBlock), 0, st, p, q, alpha, s, nx, ny, nz, n, part, sc);
-    if (np) *np = nb;
-}
-
 typedef double double2_t __attribute__((ext_vector_type(2)));
 
 // Sums of K values per index i < n (at(i, v) adds index i's to v) by kBlock threads, in the order

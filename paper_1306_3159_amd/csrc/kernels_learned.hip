@@ -391,21 +391,7 @@ void launch_net_assemble(hipStream_t st, const double* q, PairGeom pg, NetDev ne
 }
 
 // ---------------------------------------------------------------------------
-// CSR SpMV y = W x (FP64), one thread per row, columns ascending.
-__global__ void k_spmv(const int* __restrict__ rowptr, const int* __restrict__ col, const double* __restrict__ val,
-                       const double* __restrict__ x, double* __restrict__ y, int N) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    double acc = 0.0;
-    for (int k = rowptr[i]; k < rowptr[i + 1]; ++k) acc += val[k] * x[col[k]];
-    y[i] = acc;
-}
-void launch_spmv(hipStream_t st, const int* rowptr, const int* col, const double* val, const double* x, double* y,
-                 int N) {
-    hipLaunchKernelGGL(k_spmv, dim3(nblocks(N)), dim3(kBlock), 0, st, rowptr, col, val, x, y, N);
-}
-
-// y = W (x - mean(x)): each block sums x itself (the same order in every block,
+// CSR SpMV y = W (x - mean(x)) (FP64), columns ascending: each block sums x itself (the same order in every block,
 // so every block subtracts the same mean), then one thread per row.
 __global__ void __launch_bounds__(kBlock) k_spmv_centered(const int* __restrict__ rowptr, const int* __restrict__ col,
                                                           const double* __restrict__ val,

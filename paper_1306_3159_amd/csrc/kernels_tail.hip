@@ -571,36 +571,11 @@ hipError_t tail_set_lds(size_t bytes) {
     return hipSuccess;
 }
 
-// A grid that is itself the coarsest level: u = A^{-1} f (natural order, m <= 512 cells).
-template <typename T>
-__global__ void __launch_bounds__(kMaxCoarse) k_coarse(const T* __restrict__ f, T* __restrict__ u,
-                                                       const double* __restrict__ specg, int nx, int ny, int nz,
-                                                       int nspec, const Scalars* sc) {
-    if (sc && sc->done) return;
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int m = nx * ny * nz;
-    double* a = reinterpret_cast<double*>(smem);
-    double* spec = a + 2 * m;
-    for (int j = threadIdx.x; j < m; j += blockDim.x) a[j] = (double)f[j];
-    for (int j = threadIdx.x; j < nspec; j += blockDim.x) spec[j] = specg[j];
-    __syncthreads();
-    spectral_solve(a, a + m, spec, nx, ny, nz);
-    for (int j = threadIdx.x; j < m; j += blockDim.x) u[j] = (T)a[j];
-}
-
-template <typename T>
-void launch_coarse(hipStream_t st, const T* f, T* u, const double* spec, int nx, int ny, int nz, const Scalars* sc) {
-    const int m = nx * ny * nz, nspec = nx * nx + ny * ny + nz * nz + m;
-    hipLaunchKernelGGL(k_coarse<T>, dim3(1), dim3(kMaxCoarse), (2 * m + nspec) * sizeof(double), st, f, u, spec, nx,
-                       ny, nz, nspec, sc);
-}
-
 #define BRD_TAIL_INST(T)                                                                                            \
     template void launch_tail<T>(hipStream_t, const T*, const T*, T*, T*, const TailDesc&, const double*, bool,     \
                                  const Scalars*);                                                                   \
     template void launchb_tail<T>(hipStream_t, const InstDev*, const int*, int, unsigned);                          \
-    template hipError_t tail_set_lds<T>(size_t);                                                                    \
-    template void launch_coarse<T>(hipStream_t, const T*, T*, const double*, int, int, int, const Scalars*);
+    template hipError_t tail_set_lds<T>(size_t);
 BRD_TAIL_INST(float)
 BRD_TAIL_INST(double)
 #undef BRD_TAIL_INST

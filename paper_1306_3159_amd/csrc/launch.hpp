@@ -6,9 +6,6 @@
 namespace brd {
 
 // ---- natural-layout FP64 grid kernels ------------------------------------
-// q = alpha p - D L p ; partials (p.q, sum q) into part[0..1][nb]
-void launch_applyA(hipStream_t st, const double* p, double* q, double alpha, double s, int nx, int ny,
-                   int nz, double* part, const Scalars* sc, unsigned* nparts_out);
 // y = alpha x - D L x (no partials, no guard); box: L with homogeneous box faces
 void launch_applyA_plain(hipStream_t st, const double* x, double* y, double alpha, double s, int nx, int ny,
                          int nz, bool box = false);
@@ -131,9 +128,6 @@ void launch_restrict(hipStream_t st, const T* r0, int nx, int ny, int nz, T* cf0
 template <typename T>
 void launch_prolong(hipStream_t st, const T* cu0, const T* cu1, int coarse_natural, T* u0, T* u1, int nx, int ny,
                     int nz, const Scalars* sc, int bs = kBlock);
-// a grid that is itself the coarsest level (natural, spec: the coarsest solve's spectral tables)
-template <typename T>
-void launch_coarse(hipStream_t st, const T* f, T* u, const double* spec, int nx, int ny, int nz, const Scalars* sc);
 
 // ---- multigrid of a box with homogeneous faces (split layout, one cell per thread) ----
 // The same V-cycle steps as above with the box operator: per-cell diagonals from
@@ -271,8 +265,6 @@ void launch_pair_fill(hipStream_t st, const double* q, int N, PairGeom pg, const
 void launch_pair_nu(hipStream_t st, const double* q, PairGeom pg, const int* rowptr, const int* col, int N, float* nu);
 void launch_net_assemble(hipStream_t st, const double* q, PairGeom pg, NetDev net, const int* col, const int* rowidx,
                          long long nnz, double Dh, double diag, double* val);
-void launch_spmv(hipStream_t st, const int* rowptr, const int* col, const double* val, const double* x, double* y,
-                 int N);
 // y = W (x - mean(x))
 void launch_spmv_centered(hipStream_t st, const int* rowptr, const int* col, const double* val, const double* x,
                           double* y, int N);
