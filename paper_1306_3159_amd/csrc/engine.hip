@@ -3603,7 +3603,7 @@ int blob_rd_precond_loss_grad(blob_rd_t H, blob_rd_net_t Nt, const double* X, co
         double lsum = 0.0;
         std::vector<double> cf(S), sums(2 * (size_t)S);
         // res = P W P y - x of every sample, its |res|^2 and |x|^2 in the partial-sum buffer
-        launch_loss_rows(st, L.rowptr, L.col, L.val, X, Y, S, N, RP, YP, H->part());
+        launch_loss_rows(st, L.rowptr, L.col, L.val, L.nnz, X, Y, S, N, RP, YP, H->part());
         HIPCHK(hipMemcpyAsync(sums.data(), H->part(), 2 * (size_t)S * 8, hipMemcpyDeviceToHost, st));
         HIPCHK(hipStreamSynchronize(st));
         for (int s = 0; s < S; ++s) {

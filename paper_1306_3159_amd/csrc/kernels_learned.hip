@@ -434,32 +434,26 @@ void launch_count_bad(hipStream_t st, const double* v, long long n, int* out) {
 // ---------------------------------------------------------------------------
 // Training.
 //
-// One work-group per sample s of the loss: yp = P y, rp = P W yp - x (W and P as the solve
-// applies them), sums[2 s] = |rp|^2, sums[2 s + 1] = |x|^2, then rp's mean removed.
-// The sums run over the threads' strided entries and then the work-group, as the single-vector
-// kernels' do. One launch for all samples in place of eight launches and a host read a sample
-// (1250 blobs, 8 samples: 0.53 -> 0.09 ms for the loss and its gradient, with k_grad_reduce).
-__global__ void __launch_bounds__(kFinBlock) k_loss_rows(const int* __restrict__ rowptr, const int* __restrict__ col,
-                                                        const double* __restrict__ val, const double* __restrict__ X,
-                                                        const double* __restrict__ Y, int N, double* RP, double* YP,
-                                                        double* sums) {
-    const size_t o = (size_t)blockIdx.x * N;
-    const double *x = X + o, *y = Y + o;
-    double *rp = RP + o, *yp = YP + o;
+// The loss, per sample s: yp = P y, rp = P W yp - x (W and P as the solve applies them),
+// sums[2 s] = |rp|^2, sums[2 s + 1] = |x|^2, then rp's mean removed. The sums run over the
+// threads' strided entries of one work-group, as the single-vector kernels' do.
+__device__ __forceinline__ void loss_center(const double* __restrict__ y, int N, double* __restrict__ yp) {
     const int bd = (int)blockDim.x;
     double s = 0.0;
     for (int i = threadIdx.x; i < N; i += bd) s += y[i];
-    double m = wg_sum(s) / (double)N;
+    const double m = wg_sum(s) / (double)N;
     for (int i = threadIdx.x; i < N; i += bd) yp[i] = y[i] - m;
-    __syncthreads();
-    s = 0.0;
-    for (int i = threadIdx.x; i < N; i += bd) {
-        double acc = 0.0;
-        for (int k = rowptr[i]; k < rowptr[i + 1]; ++k) acc += val[k] * yp[col[k]];
-        rp[i] = acc;
-        s += acc;
-    }
-    m = wg_sum(s) / (double)N;
+}
+__device__ __forceinline__ double loss_row(const int* __restrict__ rowptr, const int* __restrict__ col,
+                                           const double* __restrict__ val, const double* yp, int i) {
+    double acc = 0.0;
+    for (int k = rowptr[i]; k < rowptr[i + 1]; ++k) acc += val[k] * yp[col[k]];
+    return acc;
+}
+// s: this thread's sum of rp = W yp
+__device__ __forceinline__ void loss_finish(const double* __restrict__ x, int N, double* rp, double s, double* sums) {
+    const int bd = (int)blockDim.x;
+    double m = wg_sum(s) / (double)N;
     double t[3] = {0.0, 0.0, 0.0};
     for (int i = threadIdx.x; i < N; i += bd) {
         const double xi = x[i], r = (rp[i] - m) - xi;
@@ -472,13 +466,67 @@ __global__ void __launch_bounds__(kFinBlock) k_loss_rows(const int* __restrict__
     m = t[0] / (double)N;
     for (int i = threadIdx.x; i < N; i += bd) rp[i] -= m;
     if (threadIdx.x == 0) {
-        sums[2 * blockIdx.x] = t[1];
-        sums[2 * blockIdx.x + 1] = t[2];
+        sums[0] = t[1];
+        sums[1] = t[2];
     }
 }
-void launch_loss_rows(hipStream_t st, const int* rowptr, const int* col, const double* val, const double* X,
-                      const double* Y, int S, int N, double* RP, double* YP, double* sums) {
-    hipLaunchKernelGGL(k_loss_rows, dim3(S), dim3(kFinBlock), 0, st, rowptr, col, val, X, Y, N, RP, YP, sums);
+
+// All of it in one launch, a work-group a sample.
+__global__ void __launch_bounds__(kFinBlock) k_loss_rows(const int* __restrict__ rowptr, const int* __restrict__ col,
+                                                        const double* __restrict__ val, const double* __restrict__ X,
+                                                        const double* __restrict__ Y, int N, double* RP, double* YP,
+                                                        double* sums) {
+    const size_t o = (size_t)blockIdx.x * N;
+    double *rp = RP + o, *yp = YP + o;
+    loss_center(Y + o, N, yp);
+    __syncthreads();
+    double s = 0.0;
+    for (int i = threadIdx.x; i < N; i += (int)blockDim.x) {
+        const double acc = loss_row(rowptr, col, val, yp, i);
+        rp[i] = acc;
+        s += acc;
+    }
+    loss_finish(X + o, N, rp, s, sums + 2 * blockIdx.x);
+}
+
+// The same in three, the rows of W over the whole GPU (the same bits).
+__global__ void __launch_bounds__(kFinBlock) k_loss_center(const double* __restrict__ Y, int N,
+                                                          double* __restrict__ YP) {
+    const size_t o = (size_t)blockIdx.x * N;
+    loss_center(Y + o, N, YP + o);
+}
+__global__ void __launch_bounds__(kBlock) k_loss_product(const int* __restrict__ rowptr, const int* __restrict__ col,
+                                                        const double* __restrict__ val, int N,
+                                                        const double* __restrict__ YP, double* __restrict__ RP) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t o = (size_t)blockIdx.y * N;
+    if (i < N) RP[o + i] = loss_row(rowptr, col, val, YP + o, i);
+}
+__global__ void __launch_bounds__(kFinBlock) k_loss_finish(const double* __restrict__ X, int N, double* RP,
+                                                          double* sums) {
+    const size_t o = (size_t)blockIdx.x * N;
+    double s = 0.0;
+    for (int i = threadIdx.x; i < N; i += (int)blockDim.x) s += RP[o + i];
+    loss_finish(X + o, N, RP + o, s, sums + 2 * blockIdx.x);
+}
+
+// Pair-list entries up to which one launch is taken. One launch saves two and keeps a sample's vectors
+// in one L2 (1250 blobs, 8 samples: 0.53 -> 0.09 ms for the loss and its gradient against eight launches
+// and a host read a sample, with k_grad_reduce), but a single CU walks all the rows: with one sample, loss
+// and gradient in one launch / three, us: 816 entries 72 / 75, 6600 82 / 83, 14088 101 / 96, 28474 140 / 115,
+// 52528 188 / 134, 289152 874 / 290, 1402494 4510 / 1020 (8 samples: 74 / 78, 85 / 86, 103 / 100, 142 / 118,
+// 189 / 137, 886 / 308, 4570 / 1310).
+constexpr long long kLossSplit = 1 << 13;
+
+void launch_loss_rows(hipStream_t st, const int* rowptr, const int* col, const double* val, long long nnz,
+                      const double* X, const double* Y, int S, int N, double* RP, double* YP, double* sums) {
+    if (nnz <= kLossSplit) {
+        hipLaunchKernelGGL(k_loss_rows, dim3(S), dim3(kFinBlock), 0, st, rowptr, col, val, X, Y, N, RP, YP, sums);
+        return;
+    }
+    hipLaunchKernelGGL(k_loss_center, dim3(S), dim3(kFinBlock), 0, st, Y, N, YP);
+    hipLaunchKernelGGL(k_loss_product, dim3(nblocks(N), S), dim3(kBlock), 0, st, rowptr, col, val, N, YP, RP);
+    hipLaunchKernelGGL(k_loss_finish, dim3(S), dim3(kFinBlock), 0, st, X, N, RP, sums);
 }
 
 // GW_e = sum_s c_s rp_s[row e] yp_s[col e] with c_s = 2 / (S |x_s|^2); the

@@ -270,8 +270,8 @@ void launch_spmv_centered(hipStream_t st, const int* rowptr, const int* col, con
                           double* y, int N);
 // the S samples of the loss: rp = P W P y - x with its mean removed after sums[2 s] = |rp|^2, yp = P y,
 // sums[2 s + 1] = |x|^2
-void launch_loss_rows(hipStream_t st, const int* rowptr, const int* col, const double* val, const double* X,
-                      const double* Y, int S, int N, double* RP, double* YP, double* sums);
+void launch_loss_rows(hipStream_t st, const int* rowptr, const int* col, const double* val, long long nnz,
+                      const double* X, const double* Y, int S, int N, double* RP, double* YP, double* sums);
 void launch_count_bad(hipStream_t st, const double* v, long long n, int* out);
 void launch_entry_grad(hipStream_t st, const int* rowidx, const int* col, long long nnz, const double* RP,
                        const double* YP, const double* coef, int S, int N, double half_Dh, float* dg);
