@@ -405,11 +405,14 @@ inline unsigned red_blocks(size_t n) {
     const unsigned nb = nblocks(n);
     return nb < kRedBlocks ? nb : kRedBlocks;
 }
-// Blocks of CG's vector passes over n cell pairs: a pair per thread up to 10^6 cells; beyond, two
-// blocks to a CU, whose longer contiguous runs use HBM better on large grids (256^3: direction
-// 149 us, update 75; 256 blocks 148, 113; 768: 157, 74; 4096: 165, 87) and whose partials are few
-// enough for the next pass to sum by itself (128^3: as fast as 4096 blocks before that). At
-// 96 x 112 x 80 a solve is 1 % slower with 512 than with 1680.
+// Blocks of CG's vector passes over n cell pairs: a pair per thread up to 2^19 pairs (10^6 cells);
+// beyond, two blocks to a CU, whose longer contiguous runs use HBM better on large grids (256^3:
+// direction 149 us, update 75; 256 blocks 148, 113; 768: 157, 74; 4096: 165, 87) and whose partials
+// are few enough for the next pass to sum by itself. Without that folding a set-up at 128^3 (2^20
+// pairs) was 1 % slower in 512 blocks; with it, whole reactive solves (FP32, us, a pair per thread /
+// 512 blocks): 80 x 112 x 96 1201 / 1203, 96^3 1080 / 1095, 96 x 96 x 112 1397 / 1380 (just below
+// the line), 112 x 112 x 96 1295 / 1259, 112^3 1506 / 1488, 128^3 1535 / 1495, 128 x 160 x 128
+// 1765 / 1708, 160^3 2289 / 2275, 192^3 3257 / 3294.
 inline unsigned cg_blocks(size_t n) { return n > ((size_t)1 << 19) ? 512 : nblocks(n); }
 // Entry of a batched launch that owns global block g (entries sorted by block0).
 __device__ __forceinline__ int batch_entry(const BatchEntry* e, int n, unsigned g) {

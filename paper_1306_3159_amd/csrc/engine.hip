@@ -1010,7 +1010,10 @@ PcgResult pcg(blob_rd* H, bool with_blobs, double alpha, const double* g, double
     // blobs 1 to 2 us in every block; beyond, reading them in every block outweighs it (the dots in
     // 1680 blocks at 96 x 112 x 80: a solve 3 % slower). A Schur solve at 128^3
     // 14.1 -> 13.7 ms, a set-up 43.4 -> 42.3, a reactive solve at 32^3 0.73 -> 0.71. Not in a batch,
-    // whose rounds finish them.
+    // whose rounds finish them, nor where the partial buffer (sized for the cells) does not hold the
+    // three passes' regions side by side: a box has its dots in a pass of their own with as many
+    // partials as the update, 7 npv in all, and folds up to 98304 cells (and the step alone again
+    // above 2^20, where the vector passes have 512 blocks).
     const unsigned nd = dots_partials<T>(H), npv = cg_blocks(P.ncell / 2);
     const bool room = 3 * (size_t)nd + 4 * (size_t)npv <= 3 * P.part_cap;
     const bool few = !H->batch && room && npv <= 512;  // passes of few blocks: each repeats the sums
@@ -4259,6 +4262,10 @@ struct blob_rd_batch {
     hipStream_t st = nullptr;
     char* tabs = nullptr;
     size_t tab_bytes = 0;
+    // Members up to 64^3 share the rounds, larger ones run on their own streams. Drawn when a V-cycle
+    // was ten launches a level either way (64 uneven instances, 32^3 to 128^3: 395 instances/s so, 402
+    // all in rounds, 375 all on streams). A member alone now has two-launch levels and the rounds do
+    // not: 492, 437 and 559, so streams for all are 13 % faster on that batch than this default.
     int64_t lockstep_max_cells = (int64_t)64 * 64 * 64;
     int32_t threads = 8;
 };

@@ -438,7 +438,11 @@ unsigned magic(int d) { return (unsigned)(((1ull << 32) + d - 1) / d); }  // umu
 // 77, 73, 64; 128^3 (8 x 8 does not fit its first level) 122, 107, 86, 91. FP64: 64^3 82, 50,
 // 55, 63. Box, FP32: 64^3 86, 50, 52, 58. From 512 tiles of kernels_slab.hip on (two to a CU; 8 MB
 // a level) its four launches are faster: 128^3 in FP32 down and up 12.2 + 11.2 us against
-// 15.1 + 15.5 here; at 96 x 112 x 80 (336 such tiles) a solve takes the same time in both.
+// 15.1 + 15.5 here. Around that line (V-cycle in us, two launches on the finest level / tiles), FP32:
+// 80 x 112 x 96 59 / 59, 96^3 59 / 60, 112 x 112 x 96 61 / 63 (392 tiles), 128^3 82 / 69; but rows of
+// 112 and 128 cells below it, which only the 8 x 4 tile takes: 96 x 96 x 112 77 / 63 (288 tiles),
+// 112^3 80 / 67, 112 x 128 x 128 81 / 69. FP64, 8 x 8 and 8 x 4: 80^3 64 / 69, 96^3 74 / 76, 112^3 86 / 88,
+// 112 x 128 x 128 91 / 92.
 LevelTile level_tile(int nx, int ny, int nz, size_t esz) {
     LevelTile g{};
     const int hx = nx / 2;
