@@ -558,9 +558,9 @@ int blob_rd_time_kernel(blob_rd_t h, int kernel, int reps, double* avg_ms, doubl
  * Every entry is one of 64, 128, 256, 512; the default is 256. The choice
  * changes timing only: each kernel updates every cell independently of how
  * cells are grouped, so solves are bitwise identical for any table. Entries
- * act where a level runs step by step; a level that takes its steps in one or
- * two launches from LDS windows uses only the prolongation's and, below the
- * finest level, the closing half-sweep's, or none of them. */
+ * act where a level runs step by step; a level that takes several steps in a
+ * launch uses only the prolongation's and, below the finest level, the closing
+ * half-sweep's, or none of them. */
 #define BLOB_RD_TUNE_KINDS 4
 
 /* Number of levels with per-level launches for this handle's precision
